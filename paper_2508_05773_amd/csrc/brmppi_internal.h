@@ -25,6 +25,11 @@ constexpr int kPathBack = 64;     // of which before the start progress
 constexpr int kMaxBlock = 256;    // rollout block size bound (launch_bounds)
 constexpr int kNoisePrefetch = 2;   // steps of normals loaded ahead of their use
 
+// The rows of an instance, decided once per tile so that a step loop holds only
+// the code it needs: ellipses at rest, ellipses of which some move, some
+// super-ellipses, or a footprint other than the rear axle.
+enum RowKind : uint32_t { kRowsStatic = 0, kRowsMoving = 1, kRowsE4 = 2, kRowsDisc = 3 };
+
 // Per-update descriptor read by every kernel (device memory).
 struct alignas(16) SolveDesc {
   brmppi_params prm;            // 35 floats
@@ -35,9 +40,8 @@ struct alignas(16) SolveDesc {
   uint32_t n_path, instance, seed_lo, seed_hi;
   uint32_t S_pad, n_wchunk, n_rgroup, n_ritems;
   uint32_t x0_resident, n_normals, fused, ustar_global;   // n_normals: 5 + n_obs (guided) or 3
-  uint32_t n_units, any_e4, rows_item, any_disc;   // any_e4: some obstacle has e = 4; rows_item: rows
-                                                   // of one reduce work item; any_disc: a footprint
-                                                   // other than the rear axle alone
+  uint32_t n_units, row_kind, rows_item, pad3;     // row_kind: which rows the rollout's step forms
+                                                   // (RowKind); rows_item: rows of one reduce work item
   uint32_t n_objects, pad0, pad1, pad2;          // obstacles (row r: obstacle r % n_objects, disc
                                                  // r / n_objects)
   const float4* path;           // controller path (absolute coordinates)

@@ -79,11 +79,6 @@ __device__ __forceinline__ void box_muller4(const uint32_t r[4], float* n) {
   n[3] = rad1 * __builtin_amdgcn_sinf(u3);
 }
 
-constexpr float kTwoPi = 6.283185307179586f;
-constexpr float kInvTwoPi = 0.15915494309189535f;
-
-__device__ __forceinline__ float wrap_angle(float x) { return x - kTwoPi * rintf(x * kInvTwoPi); }
-
 __device__ __forceinline__ float rcp(float x) { return __builtin_amdgcn_rcpf(x); }
 
 // Loads and stores through global-address-space pointers.  Pointers read from
@@ -113,6 +108,16 @@ __device__ __forceinline__ float4 lds(const float4* p) {
   const gvec4 v = *(const lds_vec4*)p;
   return make_float4(v.x, v.y, v.z, v.w);
 }
+// the first three floats of a 16-byte entry (one ds_read_b96: a fourth register
+// would be written late, and its next use would wait for the read)
+typedef float gvec3 __attribute__((ext_vector_type(3)));
+struct Vec3 {
+  float x, y, z;
+};
+__device__ __forceinline__ Vec3 lds3(const float4* p) {
+  const gvec3 v = *(const __attribute__((address_space(3))) gvec3*)p;
+  return Vec3{v.x, v.y, v.z};
+}
 __device__ __forceinline__ void lds_put(float* p, float v) { *(lds_float*)p = v; }
 __device__ __forceinline__ void lds_put(double* p, double v) { *(lds_double*)p = v; }
 __device__ __forceinline__ void lds_put(float4* p, float4 v) {
@@ -132,132 +137,92 @@ __device__ __forceinline__ void gst4(float4* p, float4 v) {
   *(__attribute__((address_space(1))) gvec4*)p = w;
 }
 
-// GLB: through the global address space (the multi-lane forms, whose step has
-// one wave per SIMD or so and nothing to hide a needless wait), or through the
-// pointer as it is (the one-lane forms, whose register budget is the limit:
-// the global forms let the compiler hoist loads and lengthen live ranges)
-template <bool GLB>
-__device__ __forceinline__ float ldf(const float* p) {
-  if constexpr (GLB) return gld(p);
-  else return *p;
-}
-template <bool GLB>
-__device__ __forceinline__ void stf(float* p, float v) {
-  if constexpr (GLB) gst(p, v);
-  else *p = v;
-}
-
 // Per-lane choices inside the step are written as selects marked
 // unpredictable, so that the compiler keeps them as lane selects instead of
 // divergent branches (each of which costs exec-mask instructions and splits
 // the step into separately scheduled regions).
 __device__ __forceinline__ float sel(bool c, float a, float b) { return __builtin_unpredictable(c) ? a : b; }
+// The same with the lane mask in a scalar register pair, for several selects
+// under one mask: runs of v_cndmask that read vcc were measured at 16 cycles
+// each as soon as four waves run on a CU, the form with another mask at 4.
+__device__ __forceinline__ float sel_mask(uint64_t mask, float a, float b) {
+  float r;
+  asm("v_cndmask_b32_e64 %0, %1, %2, %3" : "=v"(r) : "v"(b), "v"(a), "s"(mask));
+  return r;
+}
+
+// Units of the rollout.  Time is counted in steps, angles in revolutions and
+// progress in waypoints: vh = Ts v and ah = Ts^2 a are metres a step, the
+// inputs act as Ts^3 j on ah and Ts omega on the steer angle, and the step
+// needs no multiplication by Ts.  Revolutions are what the hardware sine and
+// cosine take, and wrapping one is x - rint(x).
+constexpr float kTurn = 6.283185307179586f;      // radians a revolution
+constexpr float kInvTurn = 0.15915494309189535f;
+__device__ __forceinline__ float wrap_rev(float x) { return x - rintf(x); }
+// absolute error of order 1e-7 (the Box-Muller check over [0, 1) revolutions)
+__device__ __forceinline__ void sincos_rev(float x, float* s, float* c) {
+  *s = __builtin_amdgcn_sinf(x);
+  *c = __builtin_amdgcn_cosf(x);
+}
 
 // Obstacle row staged in LDS: the obstacle's centre relative to the tile
-// origin, velocity; for e = 2 the shape matrix Q = R' diag((mx+r)^-2,
-// (my+r)^-2) R of eq. (16); the rotation (co, so) into the obstacle frame and
-// the per-axis coefficients k = (m+r)^-e (e4 = 1 for e = 4); the row's
-// footprint disc (dA, dB).
-struct ObsL {
-  float cx, cy, vx, vy, q11, q12, q22, e4, co, so, k0, k1;
-  float dA, dB;   // the row's footprint disc: centre p + dA e1 - dB f2
+// origin at t0 and its motion in a step; for e = 2 the shape matrix Q = R'
+// diag((mx+r)^-2, (my+r)^-2) R of eq. (16), with qa, qd the half sum and half
+// difference of its diagonal, and Q rho for the motion rho of a step; the map
+// A = diag((mx+r)^-1, (my+r)^-1) R into the obstacle's scaled frame, in which
+// h = y0^e + y1^e - 1 (e4 = 1 for e = 4); the row's footprint disc (dA, dB).
+// In the order that one 16-byte read brings what is used together.
+struct alignas(16) ObsL {
+  float cx, cy, qd, e4;
+  float q11, q12, q22, qa;
+  float mx, my, rx, ry;    // motion of a step, Q rho
+  float rr, dA, dB, pad;   // rho' Q rho; disc centre p + dA e1 - dB f2
+  float a00, a01, a10, a11;
 };
 
 struct RefPoint {
   float x, y, th1, th2;
 };
 
-// Reference zeta(psi): linear interpolation between waypoints, headings by the
-// wrapped difference, clamped to the ends.  f = phi0 + psi_rel/ds is the
-// fractional waypoint index relative to k0.
-template <bool GLB, bool SPLIT = false>
+// Reference zeta(psi): linear interpolation between waypoints, headings (in
+// revolutions; the window is staged so) by the wrapped difference, clamped to
+// the ends.  f is the fractional waypoint index relative to k0.  The window in
+// LDS serves every lane unless one leaves it: then (a wave-uniform, rare case)
+// the lanes outside read their points from HBM.  LDS is read through the local
+// address space and HBM through the global one, each consumed on its own side
+// of the branch: no flat access, whose wait would also drain the step-ahead
+// HBM loads in flight.
 __device__ __forceinline__ RefPoint reference(float f, int k0, int n_path, const float4* __restrict__ spath,
                                               int w0, int nw, const float4* __restrict__ gpath, float ox,
                                               float oy) {
   float fi = floorf(f);
   fi = fminf(fmaxf(fi, -1.0e7f), 1.0e7f);  // NaN -> -1e7 -> clamped to the start
-  float t = f - fi;
-  int gi = k0 + (int)fi;
-  if (gi < 0) {
-    gi = 0;
-    t = 0.0f;
-  } else if (gi > n_path - 2) {
-    gi = n_path - 2;
-    t = 1.0f;
-  }
-  if (!(t >= 0.0f)) t = 0.0f;
+  float t = fmaxf(f - fi, 0.0f);           // NaN -> 0
+  const int graw = k0 + (int)fi;
+  const int gi = min(max(graw, 0), n_path - 2);
+  t = sel(graw > gi, 1.0f, t);
+  t = sel(graw < 0, 0.0f, t);
   const int li = gi - w0;
-  float4 A, B;
-  if constexpr (GLB && SPLIT) {
-    // the window in LDS serves every lane unless one leaves it: then (a
-    // wave-uniform, rare case) the lanes outside read their points from HBM.
-    // LDS is read through the local address space and HBM through the global
-    // one, each consumed on its own side of the branch: no flat access, whose
-    // wait would also drain the step-ahead HBM loads in flight.
-    const int lc = min(max(li, 0), nw - 2);
-    const bool outside = !(li >= 0 && li + 1 < nw);
-    A = lds(spath + lc);
-    B = lds(spath + lc + 1);
-    if (__any(outside)) {
-      const float4 Ag = gld4(gpath + gi), Bg = gld4(gpath + gi + 1);
-      A.x = outside ? Ag.x - ox : A.x;
-      A.y = outside ? Ag.y - oy : A.y;
-      A.z = outside ? Ag.z : A.z;
-      A.w = outside ? Ag.w : A.w;
-      B.x = outside ? Bg.x - ox : B.x;
-      B.y = outside ? Bg.y - oy : B.y;
-      B.z = outside ? Bg.z : B.z;
-      B.w = outside ? Bg.w : B.w;
-    }
-  } else if constexpr (GLB) {
-    // the same through a generic pointer (the eight-lane form's choice)
-    const int lc = min(max(li, 0), nw - 2);
-    const bool outside = !(li >= 0 && li + 1 < nw);
-    if (__any(outside)) {
-      const float4* pa = outside ? gpath + gi : spath + lc;
-      A = pa[0];
-      B = pa[1];
-      const float dx = outside ? ox : 0.0f, dy = outside ? oy : 0.0f;
-      A.x -= dx;
-      A.y -= dy;
-      B.x -= dx;
-      B.y -= dy;
-    } else {
-      A = spath[lc];
-      B = spath[lc + 1];
-    }
-  } else {
-    if (li >= 0 && li + 1 < nw) {
-      A = spath[li];
-      B = spath[li + 1];
-    } else {
-      A = gpath[gi];
-      B = gpath[gi + 1];
-      A.x -= ox;
-      A.y -= oy;
-      B.x -= ox;
-      B.y -= oy;
-    }
+  const int lc = min(max(li, 0), nw - 2);
+  float4 A = lds(spath + lc), B = lds(spath + lc + 1);
+  const bool outside = li != lc;
+  if (__any(outside)) {
+    const float4 Ag = gld4(gpath + gi), Bg = gld4(gpath + gi + 1);
+    A.x = outside ? Ag.x - ox : A.x;
+    A.y = outside ? Ag.y - oy : A.y;
+    A.z = outside ? Ag.z * kInvTurn : A.z;
+    A.w = outside ? Ag.w * kInvTurn : A.w;
+    B.x = outside ? Bg.x - ox : B.x;
+    B.y = outside ? Bg.y - oy : B.y;
+    B.z = outside ? Bg.z * kInvTurn : B.z;
+    B.w = outside ? Bg.w * kInvTurn : B.w;
   }
   RefPoint r;
-  r.x = A.x + t * (B.x - A.x);
-  r.y = A.y + t * (B.y - A.y);
-  r.th1 = A.z + t * wrap_angle(B.z - A.z);
-  r.th2 = A.w + t * wrap_angle(B.w - A.w);
+  r.x = fmaf(t, B.x - A.x, A.x);
+  r.y = fmaf(t, B.y - A.y, A.y);
+  r.th1 = fmaf(t, wrap_rev(B.z - A.z), A.z);
+  r.th2 = fmaf(t, wrap_rev(B.w - A.w), A.w);
   return r;
-}
-
-// Tracking part of eq. (13): contour (14), lag (15) and heading errors.
-__device__ __forceinline__ float tracking_cost(const brmppi_params& P, const RefPoint& rf, float px, float py,
-                                               float th1, float th2) {
-  float sr, cr;
-  sincosf(rf.th1, &sr, &cr);
-  const float ex = px - rf.x, ey = py - rf.y;
-  const float ec = sr * ex - cr * ey;
-  const float el = -cr * ex - sr * ey;
-  const float e1 = wrap_angle(th1 - rf.th1);
-  const float e2 = wrap_angle(th2 - rf.th2);
-  return P.Qc * ec * ec + P.Ql * el * el + P.Qth1 * e1 * e1 + P.Qth2 * e2 * e2;
 }
 
 // ---------------------------------------------------------------------------
@@ -271,132 +236,182 @@ __device__ __forceinline__ float tracking_cost(const brmppi_params& P, const Ref
 // normals come from the noise buffer filled by k_noise (same Philox and
 // Box-Muller code) instead of being drawn in the rollout.  Results are
 // therefore bitwise identical for every (G, PRE) and block size.
+//
+// What bounds the step is the number of instructions, of any kind: a wave
+// issues at most one every 4 cycles (transcendentals 8), and with one wave per
+// SIMD (the eight-lane form at up to 8192 samples) scalar instructions, waits
+// and nops cost as much as arithmetic.  Hence the units above and the row
+// algebra below, whose obstacle rows are half the arithmetic of the
+// gradient-by-gradient expansion of eq. (17): about 290 instructions a step in
+// the eight-lane form with one row per lane, where the expansion took 430.
+// Measured with it, before -> now: closed-loop update of 8192 samples, 50
+// steps, 8 ellipses 63.7 -> 53.1 us; solve of 65536 samples, 100 steps, 32
+// ellipses 1038 -> 658 us; of 5000 samples, 120 steps, 7 super-ellipses 168 ->
+// 129 us.
 
-struct ProjConst {
-  float Ma, inv_Ma, amid, h_eps, W_a, rho;
-};
-
-// projection terms of one row of eq. (9) after eliminating its auxiliary
-// input: (M_u + c g g') u = ... + c g rr, and the quantities the next barrier
-// rate needs
+// One row of eq. (9), divided by its guarded barrier value hh and with the
+// inputs' scale factors left out: u^alpha = -(L + P U0 + Q U1) - alpha with
+// L = Lf / hh, and U0 = Ts^3 j, U1 = G1 omega (G1 of the sample's step).
 struct RowTerms {
-  float c, g0, g1, rr, Lf, ih;
+  float L, P, Q;
 };
 
-__device__ __forceinline__ RowTerms row_terms(const ProjConst& K, float hhat, float Lf, float g0, float g1,
-                                              float atil, float alpha) {
-  const float ah = fabsf(hhat);
-  const float hh = sel(ah < K.h_eps, sel(hhat < 0.0f, -K.h_eps, K.h_eps), hhat);
-  const float b = -Lf - alpha * hh;
-  const float abar = (K.W_a * atil + K.rho * (K.amid - alpha)) * K.inv_Ma;
-  RowTerms R;
-  R.rr = b - hh * abar;
-  R.ih = rcp(hh);
-  R.c = K.Ma * R.ih * R.ih;
-  R.g0 = g0;
-  R.g1 = g1;
-  R.Lf = Lf;
-  return R;
+// guarded barrier: copysign(max(|hhat|, h_eps), hhat) with 0 -> +h_eps
+__device__ __forceinline__ float barrier_rcp(float hhat, float h_eps) {
+  const float g = sel(hhat < 0.0f, -h_eps, h_eps);
+  return rcp(sel(fabsf(hhat) < h_eps, g, hhat));
 }
 
 // Row sums of the 2x2 normal equations of the eliminated projection,
-// accumulated in FP64: sum_i c_i g_i g_i' and sum_i c_i g_i rr_i
+// accumulated in FP64.  With s = L + alpha + abar (abar the auxiliary input's
+// own optimum) the equations are
+//   diag(M_j, M_w) + Ma sum (G0 P, G1 Q)(G0 P, G1 Q)',
+//   right-hand side p_u - Ma sum (G0 P, G1 Q) s,
+// so the row sums need only P, Q and s.
 struct Acc5 {
-  double N00, N01, N11, y0, y1;
+  double PP, PQ, QQ, Ps, Qs;
 };
 
 __device__ __forceinline__ Acc5 acc_zero() { return Acc5{0.0, 0.0, 0.0, 0.0, 0.0}; }
 
-__device__ __forceinline__ void acc_row(Acc5& A, const RowTerms& R) {
-  const double cg0 = (double)R.c * (double)R.g0, cg1 = (double)R.c * (double)R.g1;
-  A.N00 = fma(cg0, (double)R.g0, A.N00);
-  A.N01 = fma(cg0, (double)R.g1, A.N01);
-  A.N11 = fma(cg1, (double)R.g1, A.N11);
-  A.y0 = fma(cg0, (double)R.rr, A.y0);
-  A.y1 = fma(cg1, (double)R.rr, A.y1);
+__device__ __forceinline__ void acc_row(Acc5& A, const RowTerms& R, float s) {
+  const double p = (double)R.P, q = (double)R.Q, sd = (double)s;
+  A.PP = fma(p, p, A.PP);
+  A.PQ = fma(p, q, A.PQ);
+  A.QQ = fma(q, q, A.QQ);
+  A.Ps = fma(p, sd, A.Ps);
+  A.Qs = fma(q, sd, A.Qs);
 }
 
 __device__ __forceinline__ Acc5 acc_add(const Acc5& a, const Acc5& b) {
-  return Acc5{a.N00 + b.N00, a.N01 + b.N01, a.N11 + b.N11, a.y0 + b.y0, a.y1 + b.y1};
+  return Acc5{a.PP + b.PP, a.PQ + b.PQ, a.QQ + b.QQ, a.Ps + b.Ps, a.Qs + b.Qs};
 }
 
-// obstacle row, eqs. (16)-(17) with e = 2: with q = d + Ts d_dot,
-// hhat = q'Qq - 1 + Ts^2 d'Q d_ddot; Lf and g along f = Ts f_c, g = Ts g_c
+// Barrier value, drift term and input gradient of one row: hhat, Lf = Ts
+// (d hhat / dt along the drift), d hhat / d ah = g0, and g1 with
+// Ts d hhat / d delta = G1 g1
 struct ObsRow {
   float hhat, Lf, g0, g1;
 };
 
-__device__ __forceinline__ ObsRow obstacle_row(const ObsL& ob, float px, float py, float v, float a, float c1,
-                                               float s1, float vkd, float sec2, float t, float Ts, float Ts2,
-                                               float inv_l1) {
-  const float dx = px - (ob.cx + ob.vx * t), dy = py - (ob.cy + ob.vy * t);
-  const float ddx = v * c1 - ob.vx, ddy = v * s1 - ob.vy;
-  const float v2kd = v * vkd;
-  const float dddx = a * c1 - v2kd * s1, dddy = a * s1 + v2kd * c1;
-  const float qx = dx + Ts * ddx, qy = dy + Ts * ddy;
-  const float Qqx = ob.q11 * qx + ob.q12 * qy, Qqy = ob.q12 * qx + ob.q22 * qy;
-  const float Qdx = ob.q11 * dx + ob.q12 * dy, Qdy = ob.q12 * dx + ob.q22 * dy;
-  const float dQe1 = Qdx * c1 + Qdy * s1, dQe2 = Qdy * c1 - Qdx * s1;
-  const float qQe1 = Qqx * c1 + Qqy * s1, qQe2 = Qqy * c1 - Qqx * s1;
-  // gradient of hhat: position, speed, heading, time
-  const float gpx = 2.0f * Qqx + Ts2 * (ob.q11 * dddx + ob.q12 * dddy);
-  const float gpy = 2.0f * Qqy + Ts2 * (ob.q12 * dddx + ob.q22 * dddy);
-  const float h_v = 2.0f * Ts * qQe1 + 2.0f * Ts2 * vkd * dQe2;
-  const float h_th = 2.0f * Ts * v * qQe2 + Ts2 * (a * dQe2 - v2kd * dQe1);
-  const float h_t = -(gpx * ob.vx + gpy * ob.vy);
+// What the rear-axle rows of a sample's step share: position, e1 and vh e1
+// (e2 its left normal), heading increment w = vh tan(delta)/l1 of the step, and
+// the coefficients of the e = 2 rows.
+struct StepGeom {
+  float px, py, c1, s1, vc, vs, vh, ah, w, k2;
+  float ca, b1, b2, ha, hb, hc, la, lb, lc;
+  float m1, m2, tau;     // moving obstacles: coefficients, the step's index
+};
+
+template <bool MOV>
+__device__ __forceinline__ StepGeom step_geom(float px, float py, float c1, float s1, float vc, float vs, float vh,
+                                              float ah, float kd, float w, float tau) {
+  StepGeom g;
+  g.px = px; g.py = py; g.c1 = c1; g.s1 = s1; g.vc = vc; g.vs = vs; g.vh = vh; g.ah = ah; g.w = w; g.tau = tau;
+  const float C2 = fmaf(-2.0f * s1, s1, 1.0f), S2 = 2.0f * s1 * c1;
+  const float m = fmaf(3.0f, ah, 2.0f * vh);
+  g.k2 = vh * w;
+  g.ca = fmaf(2.0f, vh, ah);
+  g.b1 = fmaf(-w, g.k2, g.ca + ah);
+  g.b2 = kd * m;
+  g.ha = vh * vh;
+  g.hb = g.ha * C2;
+  g.hc = g.ha * S2;
+  g.la = vh * m;
+  const float l3 = 3.0f * (vh * g.k2);
+  g.lb = fmaf(g.la, C2, -(l3 * S2));
+  g.lc = fmaf(g.la, S2, l3 * C2);
+  if constexpr (MOV) {
+    g.m1 = fmaf(2.0f, vh, m);              // 4 vh + 3 ah
+    g.m2 = 3.0f * w;
+  } else {
+    g.m1 = g.m2 = 0.0f;
+  }
+  return g;
+}
+
+// Obstacle row, eqs. (16)-(17) with e = 2.  With d = p - p_o, q = d + vh e1,
+// d_dd = ah e1 + k2 e2 (k2 = vh w) and the products y1 = d'Q e1, y2 = vh d'Q e2,
+//   hhat = q'Qq - 1 + d'Q d_dd = d'Qd - 1 + (2 vh + ah) y1 + w y2 + vh^2 E11,
+//   Lf   = (2 vh + 2 ah - w k2) y1 + kd m y2 + vh m E11 + 3 vh k2 E12
+// with m = 2 vh + 3 ah, E11 = e1'Q e1 = qa + qd cos 2th + q12 sin 2th, E12 =
+// e1'Q e2 = q12 cos 2th - qd sin 2th; the last two terms of each are three
+// products with the step's coefficients.  A moving obstacle (motion rho a
+// step: d_d = vh e1 - rho) adds rho'Q rho - 2 d'Q rho - 2 vh e1'Q rho to hhat
+// and 2 rho'Q rho - 2 d'Q rho - (4 vh + 3 ah) e1'Q rho - 3 k2 e2'Q rho to Lf.
+template <bool MOV>
+__device__ __forceinline__ ObsRow obstacle_row(const ObsL& ob, const StepGeom& g) {
+  float dx = g.px - ob.cx, dy = g.py - ob.cy;
+  if constexpr (MOV) {
+    dx = fmaf(-ob.mx, g.tau, dx);
+    dy = fmaf(-ob.my, g.tau, dy);
+  }
+  const float Qx = fmaf(ob.q12, dy, ob.q11 * dx), Qy = fmaf(ob.q22, dy, ob.q12 * dx);
   ObsRow R;
-  R.hhat = qx * Qqx + qy * Qqy - 1.0f + Ts2 * (Qdx * dddx + Qdy * dddy);
-  R.Lf = Ts * (v * (gpx * c1 + gpy * s1) + h_v * a + h_th * vkd + h_t);
-  R.g0 = Ts * Ts2 * dQe1;                          // Ts d hhat/da
-  R.g1 = Ts * Ts2 * v * v * sec2 * inv_l1 * dQe2;   // Ts d hhat/d delta
+  R.g0 = fmaf(Qy, g.s1, Qx * g.c1);
+  R.g1 = fmaf(Qy, g.vc, -(Qx * g.vs));
+  float h = fmaf(dy, Qy, fmaf(dx, Qx, -1.0f));
+  h = fmaf(g.ca, R.g0, h);
+  h = fmaf(g.w, R.g1, h);
+  h = fmaf(g.ha, ob.qa, h);
+  h = fmaf(g.hb, ob.qd, h);
+  R.hhat = fmaf(g.hc, ob.q12, h);
+  float l = g.b1 * R.g0;
+  l = fmaf(g.b2, R.g1, l);
+  l = fmaf(g.la, ob.qa, l);
+  l = fmaf(g.lb, ob.qd, l);
+  R.Lf = fmaf(g.lc, ob.q12, l);
+  if constexpr (MOV) {
+    const float r1 = fmaf(ob.ry, g.s1, ob.rx * g.c1);
+    const float r2 = fmaf(ob.ry, g.vc, -(ob.rx * g.vs));     // vh e2'Q rho
+    const float dr = fmaf(ob.ry, dy, ob.rx * dx) - ob.rr;
+    // hhat: rr - 2 dR - 2 vh r1 = -2 (dr + vh r1) - rr
+    R.hhat = fmaf(-2.0f, fmaf(g.vh, r1, dr), R.hhat) - ob.rr;
+    R.Lf = fmaf(-2.0f, dr, fmaf(-g.m1, r1, fmaf(-g.m2, r2, R.Lf)));
+  }
   return R;
 }
 
-// Super-ellipse row (e = 4), eqs. (16)-(17): h = k0 y0^4 + k1 y1^4 - 1 in the
-// obstacle frame (y = R d).  Per axis the expansion hhat = h + Ts hd +
-// Ts^2/2 hdd and its partials in y, y_dot and y_ddot (third derivatives of h
-// included) are formed, then chained to the state through y_dot = v e1' - vo'
-// and y_ddot = a e1' + v^2 kd e2' (primes: obstacle frame).
-__device__ __forceinline__ ObsRow obstacle_row_e4(const ObsL& ob, float px, float py, float v, float a, float c1,
-                                                  float s1, float vkd, float sec2, float t, float Ts, float Ts2,
-                                                  float inv_l1) {
-  const float co = ob.co, so = ob.so;
-  const float dx = px - (ob.cx + ob.vx * t), dy = py - (ob.cy + ob.vy * t);
-  const float y0 = co * dx + so * dy, y1 = -so * dx + co * dy;
-  const float e10 = co * c1 + so * s1, e11 = -so * c1 + co * s1;   // R e1; R e2 = (-e11, e10)
-  const float vo0 = co * ob.vx + so * ob.vy, vo1 = -so * ob.vx + co * ob.vy;
-  const float v2kd = v * vkd;
-  const float yd0 = v * e10 - vo0, yd1 = v * e11 - vo1;
-  const float ydd0 = a * e10 - v2kd * e11, ydd1 = a * e11 + v2kd * e10;
-  float hh[2], P[2], V[2], A[2];
-  const float k[2] = {ob.k0, ob.k1}, y[2] = {y0, y1}, yd[2] = {yd0, yd1}, ydd[2] = {ydd0, ydd1};
+// Super-ellipse row (e = 4), eqs. (16)-(17), in the obstacle's scaled frame:
+// y = A d, h = y0^4 + y1^4 - 1.  Per axis, with E = A e1, F = A e2, the rate
+// dl = vh E - A rho and the drift acceleration ep = ah E + k2 F (a step's
+// units), hhat = sum y^4 + 4 y^3 (dl + ep/2) + 6 y^2 dl^2 - 1 and Lf = sum
+// P dl + V ep + (3 ah w F - k2 w E) 2 y^3, P and V the partials of hhat in y
+// and dl; g0 and g1 collect the partial 2 y^3 in ep along E and vh F.
+__device__ __forceinline__ ObsRow obstacle_row_e4(const ObsL& ob, const StepGeom& g) {
+  const float dx = fmaf(-ob.mx, g.tau, g.px - ob.cx), dy = fmaf(-ob.my, g.tau, g.py - ob.cy);
+  const float a0[2] = {ob.a00, ob.a10}, a1[2] = {ob.a01, ob.a11};
+  float h = -1.0f, l = 0.0f, g0 = 0.0f, g2 = 0.0f;
 #pragma unroll
   for (int i = 0; i < 2; ++i) {
-    const float y2 = y[i] * y[i], y3 = y2 * y[i];
-    const float f1 = 4.0f * k[i] * y3, f2 = 12.0f * k[i] * y2, f3 = 24.0f * k[i] * y[i];
-    const float hd = f1 * yd[i], hdd = f2 * yd[i] * yd[i] + f1 * ydd[i];
-    hh[i] = k[i] * y2 * y2 + Ts * hd + 0.5f * Ts2 * hdd;
-    P[i] = f1 + Ts * f2 * yd[i] + 0.5f * Ts2 * (f3 * yd[i] * yd[i] + f2 * ydd[i]);   // d hhat / d y
-    V[i] = Ts * f1 + Ts2 * f2 * yd[i];                                             // d hhat / d y_dot
-    A[i] = 0.5f * Ts2 * f1;                                                        // d hhat / d y_ddot
+    const float y = fmaf(a1[i], dy, a0[i] * dx);
+    const float E = fmaf(a1[i], g.s1, a0[i] * g.c1), F = fmaf(a1[i], g.c1, -(a0[i] * g.s1));
+    const float rho = fmaf(a1[i], ob.my, a0[i] * ob.mx);
+    const float dl = fmaf(g.vh, E, -rho), ep = fmaf(g.k2, F, g.ah * E);
+    const float c = fmaf(0.5f, ep, dl);
+    const float y2 = y * y, yc = y * c, d2 = dl * dl;
+    const float A = 2.0f * y2 * y;
+    h = fmaf(y2, fmaf(6.0f, d2, fmaf(4.0f, yc, y2)), h);
+    const float P = 4.0f * y * fmaf(3.0f, d2, fmaf(3.0f, yc, y2));
+    const float V = 4.0f * y2 * fmaf(3.0f, dl, y);
+    l = fmaf(P, dl, l);
+    l = fmaf(V, ep, l);
+    g0 = fmaf(A, E, g0);
+    g2 = fmaf(A, F, g2);
   }
-  const float Ae1 = A[0] * e10 + A[1] * e11, Ae2 = -A[0] * e11 + A[1] * e10;
-  const float Ve1 = V[0] * e10 + V[1] * e11, Ve2 = -V[0] * e11 + V[1] * e10;
-  const float Pe1 = P[0] * e10 + P[1] * e11, Pvo = P[0] * vo0 + P[1] * vo1;
-  const float h_v = Ve1 + 2.0f * vkd * Ae2;
-  const float h_th = v * Ve2 + a * Ae2 - v2kd * Ae1;
   ObsRow R;
-  R.hhat = hh[0] + hh[1] - 1.0f;
-  R.Lf = Ts * (v * Pe1 + h_v * a + h_th * vkd - Pvo);
-  R.g0 = Ts * Ae1;                                  // Ts d hhat/da
-  R.g1 = Ts * v * v * sec2 * inv_l1 * Ae2;          // Ts d hhat/d delta
+  R.hhat = h;
+  R.g0 = g0;
+  R.g1 = g.vh * g2;
+  R.Lf = fmaf(3.0f * g.ah * g.w, g2, fmaf(-(g.k2 * g.w), g0, l));
   return R;
 }
 
 // Kinematics of a footprint disc centre c = p + A e1 - B f2 along the drift
 // (inputs zero), for the rows of a footprint other than the rear axle (Sec.
-// IV-C): e1, e2 the tractor's heading and its left normal, f2, n2 the
-// trailer's; every quantity is P0 + A PA - B PB with the step's parts below.
+// IV-C), in the units of a step: e1, e2 the tractor's heading and its left
+// normal, f2, n2 the trailer's; every quantity is P0 + A PA - B PB with the
+// step's parts below.
 //   velocity  c'   = v e1 + A w1 e2 - B w2 n2
 //   accel.    c''  = a e1 + v w1 e2 + A (w1' e2 - w1^2 e1) - B (w2' n2 - w2^2 f2)
 //   jerk      c''' = -v w1^2 e1 + (2 a w1 + v w1') e2 + A (-3 w1 w1' e1 - w1^3 e2)
@@ -453,78 +468,64 @@ __device__ __forceinline__ DiscBasis disc_basis(float v, float a, float c1, floa
   return D;
 }
 
-// Row of an obstacle around a footprint disc (e = 2 or 4), eqs. (16)-(17):
-// per axis of the obstacle frame (y = R (c - p_o(t)), k = (m + r)^-e)
-// h = sum k y^e - 1 and its time derivatives along the drift from those of
-// y; hhat = h + Ts hd + Ts^2/2 hdd; Lf = Ts d hhat/dt along the drift
-// (obstacle motion included) = Ts (hd + Ts hdd + Ts^2/2 hddd); g = Ts (d
-// hhat/da, d hhat/d delta), which reach hhat through c' (delta) and c''.
+// Row of an obstacle around a footprint disc (e = 2 or 4), eqs. (16)-(17), in
+// the obstacle's scaled frame and the units of a step: h = sum y^e - 1 and its
+// time derivatives along the drift from those of y = A (c - p_o); hhat = h + hd
+// + hdd/2; Lf = d hhat/dt along the drift (obstacle motion included) = hd + hdd
+// + hddd/2; the inputs reach hhat through c' (delta) and c'' (g1: G1 = Ts).
+// The derivatives of y^e for e = 2 and 4 are one expression each in a = 1 or
+// y^2 and the exponent's coefficients: no selects.
 __device__ __forceinline__ ObsRow obstacle_row_disc(const ObsL& ob, const DiscBasis& D, float px, float py,
-                                                    float c1, float s1, float t, float Ts, float Ts2) {
+                                                    float c1, float s1, float tau) {
   const float A = ob.dA, B = ob.dB;
-  const float dx = px + A * c1 - B * D.f2x - (ob.cx + ob.vx * t);
-  const float dy = py + A * s1 - B * D.f2y - (ob.cy + ob.vy * t);
-  const float ux = D.v0x + A * D.vAx - B * D.vBx - ob.vx, uy = D.v0y + A * D.vAy - B * D.vBy - ob.vy;
+  const float dx = px + A * c1 - B * D.f2x - (ob.cx + ob.mx * tau);
+  const float dy = py + A * s1 - B * D.f2y - (ob.cy + ob.my * tau);
+  const float ux = D.v0x + A * D.vAx - B * D.vBx - ob.mx, uy = D.v0y + A * D.vAy - B * D.vBy - ob.my;
   const float wx = D.a0x + A * D.aAx - B * D.aBx, wy = D.a0y + A * D.aAy - B * D.aBy;
   const float zx = D.j0x + A * D.jAx - B * D.jBx, zy = D.j0y + A * D.jAy - B * D.jBy;
   const float gx = A * D.gAx - B * D.gBx, gy = A * D.gAy - B * D.gBy;
   const float hax = D.ha0x + A * D.haAx - B * D.haBx, hay = D.ha0y + A * D.haAy - B * D.haBy;
   const float hdx = D.hd0x + A * D.hdAx - B * D.hdBx, hdy = D.hd0y + A * D.hdAy - B * D.hdBy;
-  const float co = ob.co, so = ob.so;
-  const float y[2] = {co * dx + so * dy, -so * dx + co * dy};
-  const float yd[2] = {co * ux + so * uy, -so * ux + co * uy};
-  const float ydd[2] = {co * wx + so * wy, -so * wx + co * wy};
-  const float yddd[2] = {co * zx + so * zy, -so * zx + co * zy};
-  const float ydl[2] = {co * gx + so * gy, -so * gx + co * gy};          // d y_dot / d delta
-  const float ya[2] = {co * hax + so * hay, -so * hax + co * hay};       // d y_ddot / da
-  const float yddl[2] = {co * hdx + so * hdy, -so * hdx + co * hdy};     // d y_ddot / d delta
-  const bool e4 = ob.e4 != 0.0f;
-  const float k[2] = {ob.k0, ob.k1};
+  const float e4 = ob.e4, ne4 = 1.0f - e4;
+  const float n1 = fmaf(2.0f, e4, 2.0f), n2 = fmaf(10.0f, e4, 2.0f), n3 = 24.0f * e4;
+  const float a0[2] = {ob.a00, ob.a10}, a1[2] = {ob.a01, ob.a11};
   float h = -1.0f, hd = 0.0f, hdd = 0.0f, hddd = 0.0f, da = 0.0f, dd1 = 0.0f, dd2 = 0.0f;
 #pragma unroll
   for (int i = 0; i < 2; ++i) {
-    const float yy = y[i] * y[i];
-    // derivatives of k y^e: (f0, f1, f2, f3)
-    const float f0 = sel(e4, k[i] * yy * yy, k[i] * yy);
-    const float f1 = sel(e4, 4.0f * k[i] * yy * y[i], 2.0f * k[i] * y[i]);
-    const float f2 = sel(e4, 12.0f * k[i] * yy, 2.0f * k[i]);
-    const float f3 = sel(e4, 24.0f * k[i] * y[i], 0.0f);
+    const float y = a0[i] * dx + a1[i] * dy, yd = a0[i] * ux + a1[i] * uy;
+    const float ydd = a0[i] * wx + a1[i] * wy, yddd = a0[i] * zx + a1[i] * zy;
+    const float ydl = a0[i] * gx + a1[i] * gy;          // d y_dot / d delta
+    const float ya = a0[i] * hax + a1[i] * hay;         // d y_ddot / da
+    const float yddl = a0[i] * hdx + a1[i] * hdy;       // d y_ddot / d delta
+    const float yy = y * y;
+    const float b = fmaf(yy, e4, ne4);                  // 1 or y^2
+    const float f0 = yy * b, f1 = n1 * b * y, f2 = n2 * b, f3 = n3 * y;
     h += f0;
-    hd += f1 * yd[i];
-    hdd += f2 * yd[i] * yd[i] + f1 * ydd[i];
-    hddd += f3 * yd[i] * yd[i] * yd[i] + 3.0f * f2 * yd[i] * ydd[i] + f1 * yddd[i];
-    da += f1 * ya[i];
-    dd1 += f1 * ydl[i];
-    dd2 += 2.0f * f2 * yd[i] * ydl[i] + f1 * yddl[i];
+    hd += f1 * yd;
+    hdd += f2 * yd * yd + f1 * ydd;
+    hddd += f3 * yd * yd * yd + 3.0f * f2 * yd * ydd + f1 * yddd;
+    da += f1 * ya;
+    dd1 += f1 * ydl;
+    dd2 += 2.0f * f2 * yd * ydl + f1 * yddl;
   }
   ObsRow R;
-  R.hhat = h + Ts * hd + 0.5f * Ts2 * hdd;
-  R.Lf = Ts * (hd + Ts * hdd + 0.5f * Ts2 * hddd);
-  R.g0 = Ts * (0.5f * Ts2 * da);
-  R.g1 = Ts * (Ts * dd1 + 0.5f * Ts2 * dd2);
+  R.hhat = h + hd + 0.5f * hdd;
+  R.Lf = hd + hdd + 0.5f * hddd;
+  R.g0 = 0.5f * da;
+  R.g1 = dd1 + 0.5f * dd2;
   return R;
 }
 
-// E4: the instance has super-ellipse obstacles (decided once per tile, so that
-// ellipse-only instances run a step loop without the e = 4 code)
-template <bool E4>
-__device__ __forceinline__ ObsRow obstacle_row_any(const ObsL& ob, float px, float py, float v, float a, float c1,
-                                                   float s1, float vkd, float sec2, float t, float Ts, float Ts2,
-                                                   float inv_l1) {
-  if (E4 && ob.e4 != 0.0f) return obstacle_row_e4(ob, px, py, v, a, c1, s1, vkd, sec2, t, Ts, Ts2, inv_l1);
-  return obstacle_row(ob, px, py, v, a, c1, s1, vkd, sec2, t, Ts, Ts2, inv_l1);
-}
-
-// the row of obstacle slot `ob`: at the rear axle (e = 2, or 4 with E4) or,
-// with DISC, around the slot's footprint disc
-template <bool E4, bool DISC>
-__device__ __forceinline__ ObsRow obstacle_row_sel(const ObsL& ob, const DiscBasis& D, float px, float py, float v,
-                                                   float a, float c1, float s1, float vkd, float sec2, float t,
-                                                   float Ts, float Ts2, float inv_l1) {
-  if constexpr (DISC) {
-    return obstacle_row_disc(ob, D, px, py, c1, s1, t, Ts, Ts2);
+// the row of obstacle slot `ob`, by the instance's kind of rows
+template <int ROWS>
+__device__ __forceinline__ ObsRow obstacle_row_sel(const ObsL& ob, const DiscBasis& D, const StepGeom& g) {
+  if constexpr (ROWS == kRowsDisc) {
+    return obstacle_row_disc(ob, D, g.px, g.py, g.c1, g.s1, g.tau);
+  } else if constexpr (ROWS == kRowsE4) {
+    if (ob.e4 != 0.0f) return obstacle_row_e4(ob, g);
+    return obstacle_row<true>(ob, g);
   } else {
-    return obstacle_row_any<E4>(ob, px, py, v, a, c1, s1, vkd, sec2, t, Ts, Ts2, inv_l1);
+    return obstacle_row<ROWS == kRowsMoving>(ob, g);
   }
 }
 
@@ -558,8 +559,8 @@ __device__ __forceinline__ double dpp_f64(double x) {
 
 template <int CTRL>
 __device__ __forceinline__ Acc5 acc_partner_add(const Acc5& a) {
-  return acc_add(a, Acc5{dpp_f64<CTRL>(a.N00), dpp_f64<CTRL>(a.N01), dpp_f64<CTRL>(a.N11), dpp_f64<CTRL>(a.y0),
-                         dpp_f64<CTRL>(a.y1)});
+  return acc_add(a, Acc5{dpp_f64<CTRL>(a.PP), dpp_f64<CTRL>(a.PQ), dpp_f64<CTRL>(a.QQ), dpp_f64<CTRL>(a.Ps),
+                         dpp_f64<CTRL>(a.Qs)});
 }
 
 // Canonical accumulation order of the projection rows, independent of the
@@ -592,108 +593,104 @@ __device__ __forceinline__ Acc5 virtual_tree(Leaf& leaf) {
 // Collision-penalty baseline (the paper's second MPPI baseline, Sec. V; its
 // form is not given): sum over the obstacle rows of max(0, -h)^2 with h the
 // obstacle function of eq. (16) (e = 2 or 4) at the row's point (the rear
-// axle, or with DISC its footprint disc centre) and the current time, in row
-// order (every lane of a group sums all rows).
-template <bool E4, bool DISC>
+// axle, or its footprint disc centre) and the current time, in row order
+// (every lane of a group sums all rows of its own step).
+template <int ROWS>
 __device__ __forceinline__ float collision_pen(const ObsL* __restrict__ sobs, int n_obs, float px, float py,
-                                               float th1, float th2, float t) {
+                                               float th1, float th2, float tau) {
   float c1 = 0.0f, s1 = 0.0f, c2 = 0.0f, s2 = 0.0f;
-  if constexpr (DISC) {
-    sincosf(th1, &s1, &c1);
-    sincosf(th2, &s2, &c2);
+  if constexpr (ROWS == kRowsDisc) {
+    sincos_rev(th1, &s1, &c1);
+    sincos_rev(th2, &s2, &c2);
   }
   float pen = 0.0f;
   for (int o = 0; o < n_obs; ++o) {
     const ObsL ob = sobs[o];
     float qx = px, qy = py;
-    if constexpr (DISC) {
+    if constexpr (ROWS == kRowsDisc) {
       qx = px + ob.dA * c1 - ob.dB * c2;
       qy = py + ob.dA * s1 - ob.dB * s2;
     }
-    const float dx = qx - (ob.cx + ob.vx * t), dy = qy - (ob.cy + ob.vy * t);
+    const float dx = fmaf(-ob.mx, tau, qx - ob.cx), dy = fmaf(-ob.my, tau, qy - ob.cy);
     float h;
-    if (E4 && ob.e4 != 0.0f) {
-      const float y0 = ob.co * dx + ob.so * dy, y1 = -ob.so * dx + ob.co * dy;
+    if constexpr (ROWS >= kRowsE4) {
+      const float y0 = ob.a00 * dx + ob.a01 * dy, y1 = ob.a10 * dx + ob.a11 * dy;
       const float z0 = y0 * y0, z1 = y1 * y1;
-      h = ob.k0 * z0 * z0 + ob.k1 * z1 * z1 - 1.0f;
+      const float b = 1.0f - ob.e4;
+      h = z0 * fmaf(z0, ob.e4, b) + z1 * fmaf(z1, ob.e4, b) - 1.0f;
     } else {
       h = dx * (ob.q11 * dx + ob.q12 * dy) + dy * (ob.q12 * dx + ob.q22 * dy) - 1.0f;
     }
-    pen += (h < 0.0f) ? h * h : 0.0f;
+    h = fminf(h, 0.0f);
+    pen = fmaf(h, h, pen);
   }
   return pen;
 }
 
-// sine and cosine of the four angles a step needs (th1, th1 - th2, delta and
-// the reference heading), one pair per lane for G >= 4, then broadcast.  The
-// hardware sine and cosine (absolute error of order 1e-6 over the angles a
-// rollout reaches) keep the library's range reduction off the step's chain.
+// sine and cosine of the three angles a step needs (th1, th1 - th2, delta), one
+// pair per lane for G >= 4 (lane masks ma, mb, mc pick the angle: exact, as one
+// of them is 1 or -1 and the others 0), then broadcast.
 struct StepTrig {
-  float s1, c1, sp, cp, sd, cd, sr, cr;
+  float s1, c1, sp, cp, tn;
 };
-
-__device__ __forceinline__ void step_sincos(float x, float* s, float* c) {
-  *s = __sinf(x);
-  *c = __cosf(x);
+struct TrigMask {
+  float m1, m2, md;
+};
+template <int G>
+__device__ __forceinline__ TrigMask trig_mask(int g) {
+  const int q = g & 3;
+  return TrigMask{q < 2 ? 1.0f : 0.0f, q == 1 ? -1.0f : 0.0f, q >= 2 ? 1.0f : 0.0f};
 }
 
 template <int G>
-__device__ __forceinline__ StepTrig step_trig(int g, float a0, float a1, float a2, float a3) {
+__device__ __forceinline__ StepTrig step_trig(const TrigMask& M, float th1, float th2, float dl) {
   StepTrig t;
-  if constexpr (G == 1) {
-    step_sincos(a0, &t.s1, &t.c1);
-    step_sincos(a1, &t.sp, &t.cp);
-    step_sincos(a2, &t.sd, &t.cd);
-    step_sincos(a3, &t.sr, &t.cr);
-  } else if constexpr (G == 2) {
-    // lane g: angles g and g + 2
-    float s0, c0, s2, c2;
-    step_sincos(g == 0 ? a0 : a1, &s0, &c0);
-    step_sincos(g == 0 ? a2 : a3, &s2, &c2);
-    t.s1 = group_bcast<2, 0>(s0);
-    t.c1 = group_bcast<2, 0>(c0);
-    t.sp = group_bcast<2, 1>(s0);
-    t.cp = group_bcast<2, 1>(c0);
-    t.sd = group_bcast<2, 0>(s2);
-    t.cd = group_bcast<2, 0>(c2);
-    t.sr = group_bcast<2, 1>(s2);
-    t.cr = group_bcast<2, 1>(c2);
+  if constexpr (G < 4) {
+    float sd, cd;
+    sincos_rev(th1, &t.s1, &t.c1);
+    sincos_rev(th1 - th2, &t.sp, &t.cp);
+    sincos_rev(dl, &sd, &cd);
+    t.tn = sd * rcp(cd);      // |delta| stays far from pi/2: cos > 0
   } else {
-    // lane g of every quad: angle g mod 4
-    const bool odd = (g & 1) != 0, high = (g & 2) != 0;
-    const float a = sel(high, sel(odd, a3, a2), sel(odd, a1, a0));
+    const float a = fmaf(M.md, dl, fmaf(M.m2, th2, M.m1 * th1));
     float sa, ca;
-    step_sincos(a, &sa, &ca);
+    sincos_rev(a, &sa, &ca);
+    const float ta = sa * rcp(ca);
     t.s1 = group_bcast<G, 0>(sa);
     t.c1 = group_bcast<G, 0>(ca);
     t.sp = group_bcast<G, 1>(sa);
     t.cp = group_bcast<G, 1>(ca);
-    t.sd = group_bcast<G, 2>(sa);
-    t.cd = group_bcast<G, 2>(ca);
-    t.sr = group_bcast<G, 3>(sa);
-    t.cr = group_bcast<G, 3>(ca);
+    t.tn = group_bcast<G, 2>(ta);
   }
   return t;
 }
 
-// Tracking part of eq. (13) with the reference heading's sine and cosine given.
-__device__ __forceinline__ float tracking_cost_sc(const brmppi_params& P, const RefPoint& rf, float sr, float cr,
-                                                  float px, float py, float th1, float th2) {
+// weights of the stage cost, headings in revolutions
+struct CostConst {
+  float Qc, Ql, Q1, Q2, Rj, Rw, mu, nu_bar;
+};
+
+// Tracking part of eq. (13): contour (14), lag (15) and heading errors, with
+// the reference heading's sine and cosine given.
+__device__ __forceinline__ float tracking_cost(const CostConst& C, const RefPoint& rf, float sr, float cr,
+                                               float px, float py, float th1, float th2) {
   const float ex = px - rf.x, ey = py - rf.y;
-  const float ec = sr * ex - cr * ey;
-  const float el = -cr * ex - sr * ey;
-  const float e1 = wrap_angle(th1 - rf.th1);
-  const float e2 = wrap_angle(th2 - rf.th2);
-  return P.Qc * ec * ec + P.Ql * el * el + P.Qth1 * e1 * e1 + P.Qth2 * e2 * e2;
+  const float ec = fmaf(sr, ex, -(cr * ey));
+  const float el = fmaf(cr, ex, sr * ey);
+  const float e1 = wrap_rev(th1 - rf.th1);
+  const float e2 = wrap_rev(th2 - rf.th2);
+  return fmaf(C.Q2 * e2, e2, fmaf(C.Q1 * e1, e1, fmaf(C.Ql * el, el, C.Qc * ec * ec)));
 }
 
 // Stage cost r(x, u*, psi) of eq. (13): tracking terms, effort on (j, omega)
 // and the progress term mu (nu_bar - nu)^2.
-__device__ __forceinline__ float stage_cost(const brmppi_params& P, const RefPoint& rf, float sr, float cr, float px,
-                                            float py, float th1, float th2, float uj, float uw, float unu) {
-  const float prog = P.nu_bar - unu;
-  return tracking_cost_sc(P, rf, sr, cr, px, py, th1, th2) + P.R_j * uj * uj + P.R_w * uw * uw +
-         P.mu * prog * prog;
+__device__ __forceinline__ float stage_cost(const CostConst& C, const RefPoint& rf, float px, float py, float th1,
+                                            float th2, float uj, float uw, float unu) {
+  float sr, cr;
+  sincos_rev(rf.th1, &sr, &cr);
+  const float prog = C.nu_bar - unu;
+  return fmaf(C.mu * prog, prog,
+              fmaf(C.Rw * uw, uw, fmaf(C.Rj * uj, uj, tracking_cost(C, rf, sr, cr, px, py, th1, th2))));
 }
 
 // value held by lane Q of each G-lane group, correct in the group's lane 0
@@ -709,33 +706,55 @@ __device__ __forceinline__ float lane_value(float x) {
   }
 }
 
+// J += the costs of lanes FIRST .. G - 1 of the group, in lane order
+template <int G, int FIRST>
+__device__ __forceinline__ void add_lane_costs(double& J, float rc) {
+  if constexpr (FIRST < G) {
+    J += (double)lane_value<G, FIRST>(rc);
+    add_lane_costs<G, FIRST + 1>(J, rc);
+  }
+}
+// the same for a last, partial run of n steps
+template <int G, int FIRST>
+__device__ __forceinline__ void add_lane_costs_n(double& J, float rc, uint32_t n) {
+  if constexpr (FIRST < G) {
+    if (n > (uint32_t)FIRST) {
+      J += (double)lane_value<G, FIRST>(rc);
+      add_lane_costs_n<G, FIRST + 1>(J, rc, n);
+    }
+  }
+}
+
+// Philox blocks of four normals that a step of the kernel's largest instance needs
+template <int NOB, bool GUIDED>
+constexpr int philox_blocks() {
+  return GUIDED ? (5 + NOB + 3) / 4 : 1;
+}
+
 // One sample's rollout over T steps, run by the G lanes of its group (lane g).
 // Rows: every lane computes the hitch row g mod 2 (G = 1: both), obstacle o is
 // computed by lane o mod G in its slot o / G.  After the projection every lane
 // holds the same inputs, state and cost.
 // s_u / s_J (fused epilogue): the tile's applied inputs [3T][lds_stride] and
 // costs in LDS, at column t_local.
-template <int NOB, bool GUIDED, int G, bool PRE, bool E4, bool DISC>
+template <int NOB, bool GUIDED, int G, bool PRE, int ROWS>
 __device__ __forceinline__ void rollout_sample(const SolveDesc& d, uint32_t s, bool store, int g, const float* x0,
                                                const ObsL* __restrict__ sobs, const float4* __restrict__ spath,
-                                               const float* __restrict__ s_un, int w0, int nw, int k0, float phi0,
+                                               const float4* __restrict__ s_un, int w0, int nw, int k0, float phi0,
                                                float* s_u, uint32_t lds_stride, uint32_t t_local, float* s_J) {
   static_assert(G == 1 || G == 2 || G == 4 || G == 8, "lanes per sample");
-  static_assert(PRE || G == 1, "a sample shared by lanes reads precomputed normals");
   constexpr int NSL = GUIDED ? (NOB + G - 1) / G : 1;   // obstacle slots of this lane
   constexpr int NV = 8 / G;                            // virtual lanes of this lane
   constexpr int NH = (G == 1) ? 2 : 1;                 // hitch rows computed by this lane
-  constexpr int NBMAX = GUIDED ? (5 + NOB + 3) / 4 : 1;  // Philox blocks (fused noise)
-  // a copy: the compiler keeps the parameters in registers instead of
-  // re-reading the descriptor (a scalar load and a wait) inside the step
-  brmppi_params P = d.prm;
-  float t0 = d.t0, inv_ds = d.inv_ds;
-  float Ts = P.Ts, Ts2 = P.Ts * P.Ts;
-  float inv_l1 = 1.0f / P.l1, inv_l2 = 1.0f / P.l2, ch = P.lh / P.l1;
+  constexpr int NBMAX = philox_blocks<NOB, GUIDED>();    // Philox blocks of a step
+  static_assert(PRE || G == 1, "a sample shared by lanes reads precomputed normals");
+  const brmppi_params& P = d.prm;
+  const uint32_t T = d.T;
   const int n_obs = (int)d.n_obs;
   const bool hitch = !(d.flags & BRMPPI_HITCH_OFF);
-  // an unguided instance may share a guided launch: the flag is honoured here
-  const bool guided = GUIDED && !(d.flags & BRMPPI_GUIDANCE_OFF);
+  // an unguided instance may share a guided batched launch (which draws its
+  // normals in the kernel): the flag is honoured here
+  const bool guided = GUIDED && (PRE || !(d.flags & BRMPPI_GUIDANCE_OFF));
   const bool penalty = (d.flags & BRMPPI_COLLISION_PENALTY) != 0;
   const int nb = guided ? (5 + n_obs + 3) / 4 : 1;
   const float ox = x0[0], oy = x0[1];
@@ -743,58 +762,54 @@ __device__ __forceinline__ void rollout_sample(const SolveDesc& d, uint32_t s, b
   const int n_path = (int)d.n_path;
   const int hk0 = (G == 1) ? 0 : (g & 1);    // first hitch row of this lane
 
-  // soft-bound projection constants, eq. (11): M = W + rho I,
-  // p = W z_des + rho/2 (lo + hi)
-  ProjConst K;
-  K.Ma = P.W_a + P.rho;
-  K.inv_Ma = 1.0f / K.Ma;
-  K.amid = 0.5f * (P.alpha_lo + P.alpha_hi);
-  K.h_eps = P.h_eps;
-  K.W_a = P.W_a;
-  K.rho = P.rho;
-  float Mj = P.W_j + P.rho, Mw = P.W_w + P.rho;
-  float pj0 = 0.5f * P.rho * (P.j_lo + P.j_hi);
-  float pw0 = 0.5f * P.rho * (P.w_lo + P.w_hi);
-  if constexpr (G == 8) {
-    // The eight-lane form has vector registers to spare (one wave per SIMD)
-    // and too few scalar ones: the step's constants are held in vector
-    // registers (an empty asm makes each a per-lane value), which frees the
-    // scalar registers that were spilled to vector lanes and re-read in
-    // every step, and saves the copies a scalar operand needs when an
-    // instruction already reads one.
+  // constants of the step.  Held in vector registers (an empty asm makes each a
+  // per-lane value): an instruction with a scalar operand takes 4 cycles of
+  // its SIMD where the same on vector registers takes 2, and the eight-lane
+  // form has too few scalar registers for them.
+  const float Ts = P.Ts;
+  float sj = P.sigma_j, sw = P.sigma_w, sn = P.sigma_nu;
+  float inv_l1 = 1.0f / P.l1, inv_l2 = 1.0f / P.l2, ch = P.lh / P.l1;
+  float chl = P.lh / P.l2;                   // ch l1 / l2
+  float dmax = P.dtheta_max, kap = P.kappa / Ts;
+  float h_eps = P.h_eps;
+  // soft-bound projection, eq. (11): M = W + rho I, p = W z_des + rho/2 (lo + hi).
+  // A row's auxiliary input: s = L + alpha + abar with abar = (W_a at + rho (amid
+  // - alpha)) / Ma, at = sigma_a e, is L + nz + ka beta with beta = -alpha and
+  // nz = ke e + kc.
+  const float Ma = P.W_a + P.rho;
+  float ke = P.W_a * P.sigma_a / Ma, kc = 0.5f * P.rho * (P.alpha_lo + P.alpha_hi) / Ma, ka = -(P.W_a / Ma);
+  float Wj = P.W_j, Ww = P.W_w;
+  float pj0 = 0.5f * P.rho * (P.j_lo + P.j_hi), pw0 = 0.5f * P.rho * (P.w_lo + P.w_hi);
+  float G0 = Ts * Ts * Ts;
+  float G1k = ROWS == kRowsDisc ? Ts : Ts * inv_l1;
+  const double MG0 = (double)Ma * (double)G0, K00 = MG0 * (double)G0;
+  const double NJ = (double)(P.W_j + P.rho), NW = (double)(P.W_w + P.rho), Mad = (double)Ma;
+  float dfn = Ts * d.inv_ds, ddl = Ts * kInvTurn;
+  CostConst C;
+  C.Qc = P.Qc; C.Ql = P.Ql; C.Q1 = P.Qth1 * (kTurn * kTurn); C.Q2 = P.Qth2 * (kTurn * kTurn);
+  C.Rj = P.R_j; C.Rw = P.R_w; C.mu = P.mu; C.nu_bar = P.nu_bar;
+  const float w_col = P.w_col;
+  {
     auto vpin = [](float& x) { asm volatile("" : "+v"(x)); };
-    vpin(P.sigma_j); vpin(P.sigma_w); vpin(P.sigma_nu); vpin(P.sigma_a);
-    vpin(P.W_j); vpin(P.W_w); vpin(P.dtheta_max); vpin(P.kappa);
-    vpin(P.Qc); vpin(P.Ql); vpin(P.Qth1); vpin(P.Qth2); vpin(P.R_j); vpin(P.R_w); vpin(P.mu); vpin(P.nu_bar);
-    vpin(P.w_col); vpin(t0); vpin(inv_ds); vpin(Ts); vpin(Ts2); vpin(inv_l1); vpin(inv_l2); vpin(ch);
-    vpin(K.Ma); vpin(K.inv_Ma); vpin(K.amid); vpin(K.h_eps); vpin(K.W_a); vpin(K.rho);
-    vpin(Mj); vpin(Mw); vpin(pj0); vpin(pw0);
+    vpin(sj); vpin(sw); vpin(sn); vpin(dfn); vpin(ddl); vpin(inv_l1); vpin(inv_l2); vpin(ch);
+    if constexpr (GUIDED) {
+      vpin(chl); vpin(dmax); vpin(kap); vpin(h_eps); vpin(ke); vpin(kc); vpin(ka);
+      vpin(Wj); vpin(Ww); vpin(pj0); vpin(pw0); vpin(G0); vpin(G1k);
+    }
+    vpin(C.Qc); vpin(C.Ql); vpin(C.Q1); vpin(C.Q2); vpin(C.Rj); vpin(C.Rw); vpin(C.mu); vpin(C.nu_bar);
   }
 
-  float px = 0.0f, py = 0.0f, v = x0[2], a = x0[3], th1 = x0[4], th2 = x0[5], dl = x0[6], psi = 0.0f;
-  float alpha_h[NH];
+  float px = 0.0f, py = 0.0f, vh = Ts * x0[2], ah = Ts * Ts * x0[3];
+  float th1 = x0[4] * kInvTurn, th2 = x0[5] * kInvTurn, dl = x0[6] * kInvTurn, f = phi0;
+  // barrier rates, negated: beta = -alpha
+  float bt_h[NH];
 #pragma unroll
-  for (int k = 0; k < NH; ++k) alpha_h[k] = P.alpha0;
-  float alpha_o[NSL];
+  for (int k = 0; k < NH; ++k) bt_h[k] = -P.alpha0;
+  float bt_o[NSL];
 #pragma unroll
-  for (int j = 0; j < NSL; ++j) alpha_o[j] = P.alpha0;
+  for (int j = 0; j < NSL; ++j) bt_o[j] = -P.alpha0;
   double J = 0.0;
   const uint32_t S_pad = d.S_pad;
-  float* __restrict__ ustar = d.u_star;
-  const float* __restrict__ unom = d.u_nom_in;
-  constexpr bool kGlb = (G > 1);
-  // Two arrangements of the step's memory accesses, each the faster for its
-  // forms (measured):
-  // - eight lanes per sample (few samples: one wave per SIMD, every latency
-  //   exposed, the schedule of the step's chain what counts): the next step's
-  //   nominal inputs fetched from HBM one step ahead, the normals' queue slot
-  //   refilled as soon as it is read;
-  // - the others (several waves per SIMD, memory waits what counts): the
-  //   nominal inputs read from LDS (staged with the tile), the slot refilled
-  //   after the last use of its values, whole pairs of steps per pass of the
-  //   loop, the reference window read without flat accesses.
-  constexpr bool kAhead = (G == 8);
-  constexpr bool kLate = PRE && !kAhead;
   // Stage costs.  One lane per sample evaluates the cost of every step.  With
   // G > 1 lanes the cost is not repeated on every lane: lane g keeps the cost
   // inputs of the steps tau with tau % G == g (state, progress and applied
@@ -803,65 +818,104 @@ __device__ __forceinline__ void rollout_sample(const SolveDesc& d, uint32_t s, b
   // order.  J therefore receives the same terms in the same order as in the
   // one-lane form, and only lane 0 (the lane that stores) holds it.
   constexpr bool kBatchCost = (G > 1);
-  RefPoint rf{};
-  if constexpr (!kBatchCost) rf = reference<kGlb, !kAhead>(phi0 + psi * inv_ds, k0, n_path, spath, w0, nw, gpath, ox, oy);
-  float k_px = 0.0f, k_py = 0.0f, k_th1 = 0.0f, k_th2 = 0.0f, k_psi = 0.0f, k_uj = 0.0f, k_uw = 0.0f, k_unu = 0.0f;
-  float un_j = 0.0f, un_w = 0.0f, un_nu = 0.0f;
-  if constexpr (kAhead) {
-    un_j = ldf<kGlb>(unom + 0);
-    un_w = ldf<kGlb>(unom + 1);
-    un_nu = ldf<kGlb>(unom + 2);
+  float k_px = 0.0f, k_py = 0.0f, k_th1 = 0.0f, k_th2 = 0.0f, k_f = 0.0f, k_uj = 0.0f, k_uw = 0.0f, k_unu = 0.0f;
+  constexpr uint64_t kGroupMask = G == 8 ? 0x0101010101010101ull
+                                  : G == 4 ? 0x1111111111111111ull
+                                  : G == 2 ? 0x5555555555555555ull : ~0ull;
+  // the hitch rows: signs +1, -1; with G > 1 they are owned by lanes 0 and 1,
+  // and the others zero their copy by these factors (P = Q = 0 makes every
+  // term of the row's sums an exact zero)
+  float hs[NH], hp[NH], hq[NH];
+#pragma unroll
+  for (int k = 0; k < NH; ++k) {
+    const bool own = G == 1 || (hitch && g < 2);
+    hs[k] = (hk0 + k) == 0 ? 1.0f : -1.0f;
+    hp[k] = own ? -kap : 0.0f;
+    hq[k] = own ? hs[k] : 0.0f;
   }
-  // the hitch rows are owned by lanes 0 and 1; the others zero their copy by
-  // this factor (c = 0 makes every term of the row's sums an exact zero)
-  const float hz_own = (hitch && g < 2) ? 1.0f : 0.0f;
+  const TrigMask TM = trig_mask<G>(g);
+  // a lane's own obstacles stay in registers when it has few
+  constexpr bool kObsRegs = GUIDED && G > 1 && NSL <= 4 && ROWS != kRowsDisc;
+  ObsL ob_r[kObsRegs ? NSL : 1];
+  if constexpr (kObsRegs) {
+#pragma unroll
+    for (int j = 0; j < NSL; ++j) ob_r[j] = sobs[g + G * j];
+  }
 
-  // Precomputed normals are loaded PF = 2 steps ahead into a queue of two
-  // slots: step tau reads slot tau % 2 and refills it with step tau + 2.  The
-  // loop is unrolled by two so that the slot is a compile-time index (no
-  // register moves, which would wait for the loads in flight).  Every load is
-  // in range (step and row indices clamped), so none needs a branch; rows
-  // past the instance's own (obstacles o >= n_obs, unguided instances) feed
-  // only rows whose terms are zeroed or unused.
+  // Precomputed normals are loaded two steps ahead into a queue of two slots:
+  // step tau reads slot tau % 2 and refills it with step tau + 2.  The loop is
+  // unrolled by two so that the slot is a compile-time index (no register
+  // moves, which would wait for the loads in flight).  Every load is in range
+  // (the last step's rows are loaded again past the end, row indices are
+  // clamped), so none needs a branch; rows past the instance's own (obstacles o
+  // >= n_obs, unguided instances) feed only rows whose terms are zeroed or
+  // unused.  A load is a buffer load: the noise buffer (at most 2 GiB), a lane
+  // offset per row and a scalar offset advanced once a step, with no address
+  // arithmetic per load.
   static_assert(!PRE || kNoisePrefetch == 2, "two queue slots");
   constexpr int PF = PRE ? 2 : 1;
   float nx_in[PF][3], nx_h[PF][NH], nx_o[PF][NSL];
-  const uint32_t n_rows = d.n_normals;
-  const size_t step_stride = (size_t)n_rows * S_pad;
-  auto load_normals = [&](uint32_t tau, int q) {
+  uint32_t off_in[3], off_h[NH], off_o[NSL];
+  const uint32_t step_bytes = d.n_normals * S_pad * (uint32_t)sizeof(float);
+  const uint32_t last_bytes = step_bytes * (T - 1);
+  uint32_t at_bytes = 0;                       // the step that the next load reads
+  const __amdgpu_buffer_rsrc_t noise_rsrc =
+      __builtin_amdgcn_make_buffer_rsrc(d.noise, 0, PRE ? (int)(last_bytes + step_bytes) : 0, 0x00020000);
+  if constexpr (PRE) {
+    const uint32_t n_rows = d.n_normals;
+#pragma unroll
+    for (uint32_t k = 0; k < 3; ++k) off_in[k] = 4u * (k * S_pad + s);
+#pragma unroll
+    for (int k = 0; k < NH; ++k) off_h[k] = 4u * (min((uint32_t)(3 + hk0 + k), n_rows - 1) * S_pad + s);
+#pragma unroll
+    for (int j = 0; j < NSL; ++j) off_o[j] = 4u * (min((uint32_t)(5 + g + G * j), n_rows - 1) * S_pad + s);
+  }
+  auto load_normals = [&](int q) __attribute__((always_inline)) {
     if constexpr (PRE) {
-      const float* __restrict__ base = d.noise + (size_t)tau * step_stride + s;
+      auto ld = [&](uint32_t off) {
+        return __int_as_float(__builtin_amdgcn_raw_buffer_load_b32(noise_rsrc, (int)off, (int)at_bytes, 0));
+      };
 #pragma unroll
-      for (int k = 0; k < 3; ++k) nx_in[q][k] = ldf<kGlb>(base + (size_t)k * S_pad);
+      for (int k = 0; k < 3; ++k) nx_in[q][k] = ld(off_in[k]);
+      if constexpr (GUIDED) {
 #pragma unroll
-      for (int k = 0; k < NH; ++k)
-        nx_h[q][k] = ldf<kGlb>(base + (size_t)min((uint32_t)(3 + hk0 + k), n_rows - 1) * S_pad);
+        for (int k = 0; k < NH; ++k) nx_h[q][k] = ld(off_h[k]);
 #pragma unroll
-      for (int j = 0; j < NSL; ++j)
-        nx_o[q][j] = ldf<kGlb>(base + (size_t)min((uint32_t)(5 + g + G * j), n_rows - 1) * S_pad);
+        for (int j = 0; j < NSL; ++j) nx_o[q][j] = ld(off_o[j]);
+      }
+      at_bytes = min(at_bytes + step_bytes, last_bytes);
     }
   };
   if constexpr (PRE) {
-    // (kLate: slot 0 before slot 1, in this order, as inside the loop)
-    load_normals(0u, 0);
-    if constexpr (kLate) __builtin_amdgcn_sched_barrier(0);
-    load_normals(min(1u, d.T - 1), 1);
-    if constexpr (kLate) __builtin_amdgcn_sched_barrier(0);
+    // slot 0 before slot 1, in this order, as inside the loop
+    load_normals(0);
+    __builtin_amdgcn_sched_barrier(0);
+    load_normals(1);
+    __builtin_amdgcn_sched_barrier(0);
   }
+  Vec3 un = lds3(s_un);                        // nominal inputs, read a step ahead
+  // uniform switches, tested as scalar integers each step (as conditions they
+  // would be kept as lane masks and cost twice the instructions)
+  const int to_hbm = __builtin_amdgcn_readfirstlane((int)d.ustar_global);
+  const int to_lds = __builtin_amdgcn_readfirstlane((int)(s_u != nullptr));
+  float* su = s_u + t_local;                   // this step's place in the tile's inputs
+  float* ug = d.u_star + s;
 
   auto step = [&](const uint32_t tau, auto SLOT) __attribute__((always_inline)) {
     constexpr int q = decltype(SLOT)::value;
     // --- noise: normals 0..2 perturb the inputs, 3 and 4 the hitch rows'
     // auxiliary inputs, 5 + o obstacle o's ---
-    float e_in[3], e_h[NH], e_o[NSL];
+    float uj, uw, unu, nz_h[NH], nz_o[NSL];
     if constexpr (PRE) {
+      uj = fmaf(sj, nx_in[q][0], un.x);
+      uw = fmaf(sw, nx_in[q][1], un.y);
+      unu = fmaf(sn, nx_in[q][2], un.z);
+      if constexpr (GUIDED) {
 #pragma unroll
-      for (int k = 0; k < 3; ++k) e_in[k] = nx_in[q][k];
+        for (int k = 0; k < NH; ++k) nz_h[k] = fmaf(ke, nx_h[q][k], kc);
 #pragma unroll
-      for (int k = 0; k < NH; ++k) e_h[k] = nx_h[q][k];
-#pragma unroll
-      for (int j = 0; j < NSL; ++j) e_o[j] = nx_o[q][j];
-      if constexpr (!kLate) load_normals(min(tau + 2, d.T - 1), q);
+        for (int j = 0; j < NSL; ++j) nz_o[j] = fmaf(ke, nx_o[q][j], kc);
+      }
     } else {
       float eps[4 * NBMAX];
 #pragma unroll
@@ -870,270 +924,276 @@ __device__ __forceinline__ void rollout_sample(const SolveDesc& d, uint32_t s, b
           uint32_t r[4];
           philox4x32_10(s, tau, (uint32_t)b, d.instance, d.seed_lo, d.seed_hi, r);
           box_muller4(r, &eps[4 * b]);
+        } else {
+#pragma unroll
+          for (int k = 0; k < 4; ++k) eps[4 * b + k] = 0.0f;
         }
       }
-#pragma unroll
-      for (int k = 0; k < 3; ++k) e_in[k] = eps[k];
+      uj = fmaf(sj, eps[0], un.x);
+      uw = fmaf(sw, eps[1], un.y);
+      unu = fmaf(sn, eps[2], un.z);
       if constexpr (GUIDED) {
 #pragma unroll
-        for (int k = 0; k < NH; ++k) e_h[k] = eps[3 + k];
+        for (int k = 0; k < NH; ++k) nz_h[k] = fmaf(ke, eps[3 + k], kc);
 #pragma unroll
-        for (int j = 0; j < NSL; ++j) e_o[j] = eps[5 + j];   // G == 1: slot j is obstacle j
+        for (int j = 0; j < NSL; ++j) nz_o[j] = fmaf(ke, eps[5 + j], kc);   // G == 1: slot j is obstacle j
       }
     }
-    float uj, uw, unu;
-    if constexpr (kAhead) {
-      uj = un_j + P.sigma_j * e_in[0];
-      uw = un_w + P.sigma_w * e_in[1];
-      unu = un_nu + P.sigma_nu * e_in[2];
-      const uint32_t tn = min(tau + 1, d.T - 1);
-      un_j = ldf<kGlb>(unom + 3 * tn + 0);
-      un_w = ldf<kGlb>(unom + 3 * tn + 1);
-      un_nu = ldf<kGlb>(unom + 3 * tn + 2);
-    } else {
-      // staged in LDS with the tile: a broadcast read, no HBM load to keep in
-      // flight across the loop's back edge
-      uj = lds(s_un + 3 * tau + 0) + P.sigma_j * e_in[0];
-      uw = lds(s_un + 3 * tau + 1) + P.sigma_w * e_in[1];
-      unu = lds(s_un + 3 * tau + 2) + P.sigma_nu * e_in[2];
-    }
-    // the rows' auxiliary-input perturbations: with the inputs' above, the
-    // only uses of the step's normals (kLate: formed here, before the refill;
-    // otherwise in the rows)
-    float at_h[NH], at_o[NSL];
-    if constexpr (GUIDED && kLate) {
-#pragma unroll
-      for (int k = 0; k < NH; ++k) at_h[k] = P.sigma_a * e_h[k];
-#pragma unroll
-      for (int j = 0; j < NSL; ++j) at_o[j] = P.sigma_a * e_o[j];
-    }
-    const float psi_next = psi + Ts * unu;
-    if constexpr (!kBatchCost) {
-      if (tau > 0) rf = reference<kGlb, !kAhead>(phi0 + psi * inv_ds, k0, n_path, spath, w0, nw, gpath, ox, oy);
-    }
-    // (the fourth angle, the reference heading, only for the per-step cost)
-    const StepTrig tg = step_trig<G>(g, th1, th1 - th2, dl, kBatchCost ? dl : rf.th1);
-    const float s1 = tg.s1, c1 = tg.c1, sp = tg.sp, cp = tg.cp;
-    const float tn = tg.sd * rcp(tg.cd);    // |delta| stays far from pi/2: cos > 0
-    const float kd = tn * inv_l1;     // th1_dot = v kd
-    const float vkd = v * kd;
-    const float Aw2 = sp - ch * cp * tn;
+    un = lds3(s_un + (tau + 1));   // (past the last step: the staged array's extra entry, unused)
+    RefPoint rf{};
+    if constexpr (!kBatchCost) rf = reference(f, k0, n_path, spath, w0, nw, gpath, ox, oy);
+    const StepTrig tg = step_trig<G>(TM, th1, th2, dl);
+    const float s1 = tg.s1, c1 = tg.c1, sp = tg.sp, cp = tg.cp, tn = tg.tn;
+    const float kd = tn * inv_l1;
+    const float w = vh * kd;                   // th1 increment of the step [rad]
+    const float W2 = inv_l2 * fmaf(-(ch * cp), tn, sp);
+    const float w2 = vh * W2;                  // th2 increment
+    const float vc = vh * c1, vs = vh * s1;    // position increment
     // Refill the queue slot with step tau + 2 only now, after the last use of
-    // its values (the trigonometry above covers the nominal inputs' LDS
-    // read): a refill hoisted above a use needs a second register, and the
+    // its values: a refill hoisted above a use needs a second register, and the
     // copy back into the slot's register at the loop's back edge would wait
     // for every load in flight (the prefetch lost).  The empty asm pins the
     // normals' products here (the compiler would otherwise sink them to their
     // uses in the rows, past the refill) and the scheduling barrier keeps the
     // refill below them.
-    if constexpr (kLate) {
+    if constexpr (PRE) {
       asm volatile("" : "+v"(uj), "+v"(uw), "+v"(unu));
       if constexpr (GUIDED) {
 #pragma unroll
-        for (int k = 0; k < NH; ++k) asm volatile("" : "+v"(at_h[k]));
+        for (int k = 0; k < NH; ++k) asm volatile("" : "+v"(nz_h[k]));
 #pragma unroll
-        for (int j = 0; j < NSL; ++j) asm volatile("" : "+v"(at_o[j]));
+        for (int j = 0; j < NSL; ++j) asm volatile("" : "+v"(nz_o[j]));
       }
       __builtin_amdgcn_sched_barrier(0);
-      load_normals(min(tau + 2, d.T - 1), q);
+      load_normals(q);
     }
 
+    float U0 = 0.0f;
     if (GUIDED && guided) {
-      const float sec2 = 1.0f + tn * tn;
-      const float t = t0 + (float)tau * Ts;
+      const float sec2 = fmaf(tn, tn, 1.0f);
+      const StepGeom geo = step_geom<ROWS != kRowsStatic>(px, py, c1, s1, vc, vs, vh, ah, kd, w, (float)tau);
       DiscBasis DB;
-      if constexpr (DISC) DB = disc_basis(v, a, c1, s1, cp, sp, tn, sec2, inv_l1, inv_l2, ch);
+      if constexpr (ROWS == kRowsDisc) DB = disc_basis(vh, ah, c1, s1, cp, sp, tn, sec2, inv_l1, inv_l2, ch);
+      // Ts d hhat / d delta = G1 g1
+      const float G1 = ROWS == kRowsDisc ? G1k : G1k * (vh * sec2);
 
       // hitch rows, eq. (18) split into h_s = dth_max - kappa v + s (th1 - th2),
-      // first-order expansion hhat = h + Ts hd
+      // first-order expansion hhat = h + Ts hd = base + s (phi - Dh)
       // (with G > 1 lanes the rows are formed whether the instance has them or
-      // not, and zeroed by hz_own: no branch in the step)
+      // not, and zeroed by hp, hq: no branch in the step)
       RowTerms H[NH];
       if (G > 1 || hitch) {
-        const float D = v * inv_l2 * Aw2 - vkd;                 // th2_dot - th1_dot
-        const float D_v = inv_l2 * Aw2 - kd;
-        const float D_phi = v * inv_l2 * (cp + ch * sp * tn);
-        const float D_dl = -v * sec2 * (inv_l2 * ch * cp + inv_l1);
-        const float phi = th1 - th2;
+        const float Dh = w2 - w;
+        const float Dphi = vh * (inv_l2 * fmaf(ch * sp, tn, cp));
+        const float base = fmaf(-kap, vh + ah, dmax);
+        const float sg = fmaf(kTurn, th1 - th2, -Dh);
+        const float lsum = fmaf(W2 - kd, ah, fmaf(-Dphi, Dh, Dh));
+        const float lb = -kap * ah;
+        float qh = fmaf(cp, chl, 1.0f);
+        if constexpr (ROWS == kRowsDisc) qh *= inv_l1 * (vh * sec2);
 #pragma unroll
         for (int k = 0; k < NH; ++k) {
-          const float sg = (hk0 + k) == 0 ? 1.0f : -1.0f;
-          const float h = P.dtheta_max - P.kappa * v + sg * phi;
-          const float hd = -P.kappa * a - sg * D;
-          const float hv = -P.kappa - sg * Ts * D_v;
-          const float Lf = Ts * (hv * a - sg * (1.0f - Ts * D_phi) * D);
-          H[k] = row_terms(K, h + Ts * hd, Lf, -P.kappa * Ts2, -sg * Ts2 * D_dl,
-                         kLate ? at_h[k] : P.sigma_a * e_h[k], alpha_h[k]);
+          const float ih = barrier_rcp(fmaf(hs[k], sg, base), h_eps);
+          H[k].L = fmaf(-hs[k], lsum, lb) * ih;
+          H[k].P = hp[k] * ih;
+          H[k].Q = hq[k] * qh * ih;
         }
       }
       // rows of virtual lane g + G i: its hitch row, then obstacles in order
       RowTerms O[NSL];
-      auto leaf = [&](auto I) -> Acc5 {
-        constexpr int i = decltype(I)::value;
-        const int vl = g + G * i;
-        Acc5 A = acc_zero();
-        if constexpr (G == 1) {
-          if (hitch && vl < 2) acc_row(A, H[vl]);
-        } else if (i == 0) {
-          // lanes 0 and 1 hold the hitch rows; the others add exact zeros (c =
-          // 0 and finite g, rr give products of +-0, and an accumulator is
-          // never -0, so x + 0 keeps its bits)
-          RowTerms Hz = H[0];
-          Hz.c *= hz_own;
-          acc_row(A, Hz);
-        }
-#pragma unroll
-        for (int j = i; j < NSL; j += NV) {
-          const int o = g + G * j;
-          if constexpr (G == 1) {
-            if (o < n_obs) {
-              const ObsRow R = obstacle_row_sel<E4, DISC>(sobs[o], DB, px, py, v, a, c1, s1, vkd, sec2, t, Ts, Ts2, inv_l1);
-              O[j] = row_terms(K, R.hhat, R.Lf, R.g0, R.g1, kLate ? at_o[j] : P.sigma_a * e_o[j], alpha_o[j]);
-              acc_row(A, O[j]);
-            }
-          } else if (G * j < n_obs) {
-            // lanes past the last obstacle read a staged blank obstacle (Q =
-            // 0): its row has hhat = -1 and Lf = g = +-0, so it adds exact
-            // zeros to the sums, without a divergent branch or selects
-            const ObsRow R = obstacle_row_sel<E4, DISC>(sobs[o], DB, px, py, v, a, c1, s1, vkd, sec2, t, Ts, Ts2, inv_l1);
-            O[j] = row_terms(K, R.hhat, R.Lf, R.g0, R.g1, kLate ? at_o[j] : P.sigma_a * e_o[j], alpha_o[j]);
-            acc_row(A, O[j]);
-          }
-        }
-        return A;
+      auto obs_row = [&](int j, const ObsL& ob, Acc5& A) __attribute__((always_inline)) {
+        const ObsRow R = obstacle_row_sel<ROWS>(ob, DB, geo);
+        const float ih = barrier_rcp(R.hhat, h_eps);
+        O[j].L = R.Lf * ih;
+        O[j].P = R.g0 * ih;
+        O[j].Q = R.g1 * ih;
+        acc_row(A, O[j], O[j].L + fmaf(ka, bt_o[j], nz_o[j]));
       };
-      const Acc5 S8 = virtual_tree<G, 0, NV>(leaf);
-      const double N00 = (double)Mj + S8.N00, N01 = S8.N01, N11 = (double)Mw + S8.N11;
-      const double y0 = (double)(P.W_j * uj + pj0) + S8.y0;
-      const double y1 = (double)(P.W_w * uw + pw0) + S8.y1;
-      const double det = N00 * N11 - N01 * N01;
+      Acc5 S8;
+      if constexpr (G == 1) {
+        // The tree's first level, leaves V and V + 1: rows two at a time, so that
+        // one branch and one wait for the obstacles' LDS reads serve two rows
+        // (a row past the last obstacle reads a staged blank one and a zero
+        // normal, and adds exact zeros).  Leaves without rows are zero and left out.
+        auto node = [&](auto V) __attribute__((always_inline)) -> Acc5 {
+          constexpr int v = decltype(V)::value;
+          Acc5 A0 = acc_zero(), A1 = acc_zero();
+          if constexpr (v == 0) {
+            if (hitch) {
+              acc_row(A0, H[0], H[0].L + fmaf(ka, bt_h[0], nz_h[0]));
+              acc_row(A1, H[1], H[1].L + fmaf(ka, bt_h[1], nz_h[1]));
+            }
+          }
+          auto rows = [&](auto self, auto J) __attribute__((always_inline)) -> void {
+            constexpr int j = decltype(J)::value;
+            if constexpr (j < NSL) {
+              if (j < n_obs) {
+                const ObsL oa = sobs[j], ob = sobs[j + 1];
+                obs_row(j, oa, A0);
+                obs_row(j + 1, ob, A1);
+                self(self, std::integral_constant<int, j + 8>{});
+              }
+            }
+          };
+          rows(rows, V);
+          return acc_add(A0, A1);
+        };
+        S8 = node(std::integral_constant<int, 0>{});
+        if constexpr (NSL > 2) {
+          const Acc5 a = node(std::integral_constant<int, 2>{});
+          S8 = acc_add(S8, a);
+          const Acc5 b = node(std::integral_constant<int, 4>{});
+          const Acc5 c = node(std::integral_constant<int, 6>{});
+          S8 = acc_add(S8, acc_add(b, c));
+        }
+      } else {
+        auto leaf = [&](auto I) -> Acc5 {
+          constexpr int i = decltype(I)::value;
+          Acc5 A = acc_zero();
+          // lanes 0 and 1 hold the hitch rows; the others add exact zeros (P =
+          // Q = 0 and finite s give products of +-0, and an accumulator is
+          // never -0, so x + 0 keeps its bits)
+          if (i == 0) acc_row(A, H[0], H[0].L + fmaf(ka, bt_h[0], nz_h[0]));
+#pragma unroll
+          for (int j = i; j < NSL; j += NV) {
+            if (NSL == 1 || G * j < n_obs) {
+              // lanes past the last obstacle read a staged blank obstacle (Q = A =
+              // 0): its row has hhat = -1 and Lf = g = +-0, so it adds exact
+              // zeros to the sums, without a divergent branch or selects
+              if constexpr (kObsRegs) obs_row(j, ob_r[j], A);
+              else obs_row(j, sobs[g + G * j], A);
+            }
+          }
+          return A;
+        };
+        S8 = virtual_tree<G, 0, NV>(leaf);
+      }
+      const double G1d = (double)G1, MG1 = Mad * G1d;
+      const double N00 = fma(K00, S8.PP, NJ), N01 = (MG0 * G1d) * S8.PQ, N11 = fma(MG1 * G1d, S8.QQ, NW);
+      const double y0 = fma(-MG0, S8.Ps, (double)fmaf(Wj, uj, pj0));
+      const double y1 = fma(-MG1, S8.Qs, (double)fmaf(Ww, uw, pw0));
+      const double det = fma(N00, N11, -(N01 * N01));
       // det > 0 (N is the diagonal W + rho I plus positive semidefinite rank-one
       // terms): the hardware reciprocal and one Newton step square its relative
       // error, far below the FP32 rounding of the result (3 instructions
       // instead of the IEEE division's 12)
       double idet = __builtin_amdgcn_rcp(det);
       idet = fma(fma(-det, idet, 1.0), idet, idet);
-      uj = (float)((N11 * y0 - N01 * y1) * idet);
-      uw = (float)((N00 * y1 - N01 * y0) * idet);
-      // next barrier rates: alpha + u*alpha = -(Lf + g u*)/hh (eq. (9) holds exactly)
+      uj = (float)(fma(N11, y0, -(N01 * y1)) * idet);
+      uw = (float)(fma(N00, y1, -(N01 * y0)) * idet);
+      U0 = G0 * uj;
+      const float U1 = G1 * uw;
+      // next barrier rates: alpha + u^alpha = -(L + P U0 + Q U1) (eq. (9) holds exactly)
       if (G > 1 || hitch) {
 #pragma unroll
-        for (int k = 0; k < NH; ++k) alpha_h[k] = -(H[k].Lf + H[k].g0 * uj + H[k].g1 * uw) * H[k].ih;
+        for (int k = 0; k < NH; ++k) {
+          // (H[k].P and H[k].Q are zero on lanes that do not own the row: their rate is unused)
+          bt_h[k] = fmaf(H[k].Q, U1, fmaf(H[k].P, U0, H[k].L));
+        }
       }
 #pragma unroll
       for (int j = 0; j < NSL; ++j) {
-        const int o = g + G * j;
-        if (G == 1 ? (o < n_obs) : (G * j < n_obs)) alpha_o[j] = -(O[j].Lf + O[j].g0 * uj + O[j].g1 * uw) * O[j].ih;
+        if (G == 1 ? ((j & ~1) < n_obs) : (NSL == 1 || G * j < n_obs)) bt_o[j] = fmaf(O[j].Q, U1, fmaf(O[j].P, U0, O[j].L));
       }
+    } else {
+      U0 = G0 * uj;
     }
 
     // --- stage cost r(x_tau, u*_tau, psi_tau), eq. (13) ---
     if constexpr (!kBatchCost) {
-      float rc = stage_cost(P, rf, tg.sr, tg.cr, px, py, th1, th2, uj, uw, unu);
-      if (penalty) rc += P.w_col * collision_pen<E4, DISC>(sobs, n_obs, px, py, th1, th2, t0 + (float)tau * Ts);
+      float rc = stage_cost(C, rf, px, py, th1, th2, uj, uw, unu);
+      if (penalty) rc = fmaf(w_col, collision_pen<ROWS>(sobs, n_obs, px, py, th1, th2, (float)tau), rc);
       J += (double)rc;
     } else {
-      const bool mine = (int)(tau & (G - 1)) == g;
-      k_px = sel(mine, px, k_px);
-      k_py = sel(mine, py, k_py);
-      k_th1 = sel(mine, th1, k_th1);
-      k_th2 = sel(mine, th2, k_th2);
-      k_psi = sel(mine, psi, k_psi);
-      k_uj = sel(mine, uj, k_uj);
-      k_uw = sel(mine, uw, k_uw);
-      k_unu = sel(mine, unu, k_unu);
+      const uint64_t mine = kGroupMask << (tau & (G - 1));
+      k_px = sel_mask(mine, px, k_px);
+      k_py = sel_mask(mine, py, k_py);
+      k_th1 = sel_mask(mine, th1, k_th1);
+      k_th2 = sel_mask(mine, th2, k_th2);
+      k_f = sel_mask(mine, f, k_f);
+      k_uj = sel_mask(mine, uj, k_uj);
+      k_uw = sel_mask(mine, uw, k_uw);
+      k_unu = sel_mask(mine, unu, k_unu);
     }
 
     // --- applied inputs: [3T][S_pad] in HBM and/or the tile's LDS ---
-    if (d.ustar_global && store) {
-      stf<kGlb>(ustar + (size_t)(3 * tau + 0) * S_pad + s, uj);
-      stf<kGlb>(ustar + (size_t)(3 * tau + 1) * S_pad + s, uw);
-      stf<kGlb>(ustar + (size_t)(3 * tau + 2) * S_pad + s, unu);
+    int hbm = to_hbm, in_lds = to_lds;
+    if constexpr (G > 1) asm volatile("" : "+s"(hbm), "+s"(in_lds));
+    if (hbm) {
+      if (store) {
+        gst(ug, uj);
+        gst(ug + S_pad, uw);
+        gst(ug + 2 * (size_t)S_pad, unu);
+      }
+      ug += 3 * (size_t)S_pad;
     }
-    if (s_u) {
+    if (in_lds) {
       // every lane of the sample writes the same values to its column; the
       // column of a sample past S is never weighted
-      s_u[(3 * tau + 0) * lds_stride + t_local] = uj;
-      s_u[(3 * tau + 1) * lds_stride + t_local] = uw;
-      s_u[(3 * tau + 2) * lds_stride + t_local] = unu;
+      lds_put(su, uj);
+      lds_put(su + lds_stride, uw);
+      lds_put(su + 2 * lds_stride, unu);
+      su += 3 * lds_stride;
     }
 
     // --- explicit Euler, eq. (6), plus psi_dot = nu ---
-    const float npx = px + Ts * v * c1;
-    const float npy = py + Ts * v * s1;
-    const float nv = v + Ts * a;
-    const float na = a + Ts * uj;
-    const float nth1 = th1 + Ts * vkd;
-    const float nth2 = th2 + Ts * v * inv_l2 * Aw2;
-    const float ndl = dl + Ts * uw;
-    psi = psi_next;
-    px = npx;
-    py = npy;
-    v = nv;
-    a = na;
-    th1 = nth1;
-    th2 = nth2;
-    dl = ndl;
+    px += vc;
+    py += vs;
+    vh += ah;
+    ah += U0;
+    th1 = fmaf(w, kInvTurn, th1);
+    th2 = fmaf(w2, kInvTurn, th2);
+    dl = fmaf(ddl, uw, dl);
+    f = fmaf(dfn, unu, f);
   };
   // costs of the kept steps tau0 .. tau0 + n - 1 (lane g: step tau0 + g)
-  auto flush_costs = [&](uint32_t tau0, uint32_t n) __attribute__((always_inline)) {
-    if constexpr (kBatchCost) {
-      const RefPoint r = reference<kGlb, !kAhead>(phi0 + k_psi * inv_ds, k0, n_path, spath, w0, nw, gpath, ox, oy);
-      float sr, cr;
-      step_sincos(r.th1, &sr, &cr);
-      float rc = stage_cost(P, r, sr, cr, k_px, k_py, k_th1, k_th2, k_uj, k_uw, k_unu);
-      if (penalty)
-        rc += P.w_col * collision_pen<E4, DISC>(sobs, n_obs, k_px, k_py, k_th1, k_th2,
-                                                t0 + (float)(tau0 + (uint32_t)g) * Ts);
-      J += (double)rc;
-      if (n > 1) J += (double)lane_value<G, 1>(rc);
-      if constexpr (G >= 4) {
-        if (n > 2) J += (double)lane_value<G, 2>(rc);
-        if (n > 3) J += (double)lane_value<G, 3>(rc);
-      }
-      if constexpr (G >= 8) {
-        if (n > 4) J += (double)lane_value<G, 4>(rc);
-        if (n > 5) J += (double)lane_value<G, 5>(rc);
-        if (n > 6) J += (double)lane_value<G, 6>(rc);
-        if (n > 7) J += (double)lane_value<G, 7>(rc);
-      }
-    }
+  auto kept_cost = [&](uint32_t tau0) __attribute__((always_inline)) -> float {
+    const RefPoint r = reference(k_f, k0, n_path, spath, w0, nw, gpath, ox, oy);
+    float rc = stage_cost(C, r, k_px, k_py, k_th1, k_th2, k_uj, k_uw, k_unu);
+    if (penalty)
+      rc = fmaf(w_col, collision_pen<ROWS>(sobs, n_obs, k_px, k_py, k_th1, k_th2, (float)(tau0 + (uint32_t)g)), rc);
+    return rc;
   };
-  auto after_step = [&](uint32_t tau) __attribute__((always_inline)) {
-    if constexpr (kBatchCost) {
-      if (((tau + 1) & (G - 1)) == 0 || tau + 1 == d.T) flush_costs(tau & ~(uint32_t)(G - 1), (tau & (G - 1)) + 1);
-    }
-  };
-  if constexpr (kLate) {
+  uint32_t tau = 0;
+  if constexpr (PRE) {
     // whole pairs, then an odd last step: every pass of the loop issues both
     // slots' refills, so a step's wait for its own slot leaves the other
-    // slot's loads in flight
-    uint32_t tau = 0;
-    for (; tau + 1 < d.T; tau += 2) {
-      step(tau, std::integral_constant<int, 0>{});
-      after_step(tau);
-      step(tau + 1, std::integral_constant<int, 1>{});
-      after_step(tau + 1);
-    }
-    if (tau < d.T) {
-      step(tau, std::integral_constant<int, 0>{});
-      after_step(tau);
-    }
-  } else if constexpr (PRE) {
-    for (uint32_t tau = 0; tau < d.T; tau += 2) {
-      step(tau, std::integral_constant<int, 0>{});
-      after_step(tau);
-      if (tau + 1 < d.T) {
+    // slot's loads in flight; G is even, so only the pair's second step can
+    // complete a run of G kept steps
+    // (tested at the bottom: with the test at the top the compiler keeps two
+    // copies of the state and moves one into the other in every pass)
+    const uint32_t T2 = T & ~1u;
+    if (T2 != 0) {
+      do {
+        step(tau, std::integral_constant<int, 0>{});
         step(tau + 1, std::integral_constant<int, 1>{});
-        after_step(tau + 1);
+        tau += 2;
+        if constexpr (kBatchCost) {
+          if ((tau & (G - 1)) == 0) {
+            const float rc = kept_cost(tau - G);
+            add_lane_costs<G, 0>(J, rc);
+          }
+        }
+      } while (tau != T2);
+    }
+    if (T & 1u) step(tau, std::integral_constant<int, 0>{});
+    if constexpr (kBatchCost) {
+      const uint32_t n = T & (G - 1);
+      if (n != 0) {
+        const float rc = kept_cost(T - n);
+        add_lane_costs_n<G, 0>(J, rc, n);
       }
     }
   } else {
-    for (uint32_t tau = 0; tau < d.T; ++tau) step(tau, std::integral_constant<int, 0>{});
+    do {
+      step(tau, std::integral_constant<int, 0>{});
+    } while (++tau != T);
   }
-  rf = reference<kGlb, !kAhead>(phi0 + psi * inv_ds, k0, n_path, spath, w0, nw, gpath, ox, oy);
-  float rN = tracking_cost(P, rf, px, py, th1, th2);   // rf: the reference at psi_T
-  if (penalty) rN += P.w_col * collision_pen<E4, DISC>(sobs, n_obs, px, py, th1, th2, t0 + (float)d.T * Ts);
+  const RefPoint rT = reference(f, k0, n_path, spath, w0, nw, gpath, ox, oy);   // the reference at psi_T
+  float sr, cr;
+  sincos_rev(rT.th1, &sr, &cr);
+  float rN = tracking_cost(C, rT, sr, cr, px, py, th1, th2);
+  if (penalty) rN = fmaf(w_col, collision_pen<ROWS>(sobs, n_obs, px, py, th1, th2, (float)T), rN);
   J += (double)rN;
   float Jf = (float)J;
   if (!isfinite(Jf)) Jf = INFINITY;
@@ -1701,7 +1761,7 @@ void k_rollout(const SolveDesc* __restrict__ descs,
                                                        const Tile* __restrict__ tiles, uint32_t n_tiles,
                                                        BatchCounters* __restrict__ ctr) {
   __shared__ float4 s_path[kPathWin];
-  __shared__ float s_unom[3 * BRMPPI_MAX_T];
+  __shared__ float4 s_unom[BRMPPI_MAX_T + 1];
   __shared__ ObsL s_obs[BRMPPI_MAX_OBS];
   __shared__ uint32_t s_tile, s_flag;
   __shared__ float s_red[2 * (kMaxBlock / 64)];
@@ -1753,50 +1813,52 @@ void k_rollout(const SolveDesc* __restrict__ descs,
       float so, co;
       sincosf(o.heading, &so, &co);
       ObsL L;
-      L.cx = o.cx - ox;
-      L.cy = o.cy - oy;
-      L.vx = o.vx;
-      L.vy = o.vy;
+      L.cx = fmaf(o.vx, d.t0, o.cx - ox);
+      L.cy = fmaf(o.vy, d.t0, o.cy - oy);
+      L.mx = d.prm.Ts * o.vx;
+      L.my = d.prm.Ts * o.vy;
       L.q11 = co * co * iax + so * so * iay;
       L.q12 = co * so * (iax - iay);
       L.q22 = so * so * iax + co * co * iay;
+      L.qa = 0.5f * (iax + iay);
+      L.qd = 0.5f * (iax - iay) * (co * co - so * so);
+      L.rx = fmaf(L.q12, L.my, L.q11 * L.mx);
+      L.ry = fmaf(L.q22, L.my, L.q12 * L.mx);
+      L.rr = fmaf(L.ry, L.my, L.rx * L.mx);
       L.e4 = (o.e == 4.0f) ? 1.0f : 0.0f;
-      L.co = co;
-      L.so = so;
-      L.k0 = (o.e == 4.0f) ? iax * iax : iax;   // (m + r)^-e
-      L.k1 = (o.e == 4.0f) ? iay * iay : iay;
+      L.a00 = co / ax;
+      L.a01 = so / ax;
+      L.a10 = -so / ay;
+      L.a11 = co / ay;
+      L.pad = 0.0f;
       disc_ab(d.prm, threadIdx.x / d.n_objects, L.dA, L.dB);
       s_obs[threadIdx.x] = L;
     } else if (threadIdx.x < BRMPPI_MAX_OBS) {
-      // blank slots (Q = 0, k = 0, at rest): the rows of lanes past the last
+      // blank slots (Q = A = 0, at rest): the rows of lanes past the last
       // obstacle row
-      s_obs[threadIdx.x] = ObsL{0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
+      s_obs[threadIdx.x] = ObsL{};
     }
-    // the path window and (forms with fewer than eight lanes) the nominal
-    // inputs, 3T floats, their first loads all issued before the first store
-    // (the window's 4 per thread at 256 threads): one memory latency, not
-    // one per value a thread stages
-    const int R3 = 3 * (int)d.T, bd = (int)blockDim.x, tx = (int)threadIdx.x;
-    float un0 = 0.0f, un1 = 0.0f;
-    if constexpr (G < 8) {
-      un0 = gld(d.u_nom_in + min(tx, R3 - 1));
-      un1 = gld(d.u_nom_in + min(tx + bd, R3 - 1));
-    }
-    for (int j0 = 0; j0 < nw; j0 += 4 * (int)blockDim.x) {
+    // the path window (headings in revolutions) and the nominal inputs, their
+    // first loads all issued before the first store (the window's 4 per thread
+    // at 256 threads): one memory latency, not one per value a thread stages
+    const int Ti = (int)d.T, bd = (int)blockDim.x, tx = (int)threadIdx.x;
+    auto load_un = [&](int tau) __attribute__((always_inline)) {
+      const float* p = d.u_nom_in + 3 * min(tau, Ti - 1);
+      return make_float4(gld(p), gld(p + 1), gld(p + 2), 0.0f);
+    };
+    const float4 un0 = load_un(tx);
+    for (int j0 = 0; j0 < nw; j0 += 4 * bd) {
       float4 w[4];
 #pragma unroll
-      for (int k = 0; k < 4; ++k) w[k] = d.path[w0 + min(j0 + k * (int)blockDim.x + (int)threadIdx.x, nw - 1)];
+      for (int k = 0; k < 4; ++k) w[k] = d.path[w0 + min(j0 + k * bd + tx, nw - 1)];
 #pragma unroll
       for (int k = 0; k < 4; ++k) {
-        const int j = j0 + k * (int)blockDim.x + (int)threadIdx.x;
-        if (j < nw) s_path[j] = make_float4(w[k].x - ox, w[k].y - oy, w[k].z, w[k].w);
+        const int j = j0 + k * bd + tx;
+        if (j < nw) s_path[j] = make_float4(w[k].x - ox, w[k].y - oy, w[k].z * kInvTurn, w[k].w * kInvTurn);
       }
     }
-    if constexpr (G < 8) {
-      if (tx < R3) s_unom[tx] = un0;
-      if (tx + bd < R3) s_unom[tx + bd] = un1;
-      for (int r = tx + 2 * bd; r < R3; r += bd) s_unom[r] = gld(d.u_nom_in + r);
-    }
+    if (tx < Ti) s_unom[tx] = un0;
+    for (int tau = tx + bd; tau < Ti; tau += bd) s_unom[tau] = load_un(tau);
     // fused epilogue (direct launch of one instance): LDS for the tile's
     // applied inputs, costs (+inf where no sample stores), weights, units
     const bool fused = (ctr == nullptr) && d.fused;
@@ -1820,21 +1882,19 @@ void k_rollout(const SolveDesc* __restrict__ descs,
     const int g = (int)(threadIdx.x % G);
     const bool valid = s_raw < d.S;
     const uint32_t s = valid ? s_raw : d.S - 1;
-    bool done = false;
+    auto rollout = [&](auto ROWS) __attribute__((always_inline)) {
+      rollout_sample<NOB, GUIDED, G, PRE, decltype(ROWS)::value>(d, s, valid && g == 0, g, x0, s_obs, s_path, s_unom,
+                                                                w0, nw, k0, phi0, s_u, lds_stride, t_local, s_J);
+    };
     if constexpr (GUIDED) {
-      if (d.any_disc) {
-        rollout_sample<NOB, GUIDED, G, PRE, true, true>(d, s, valid && g == 0, g, x0, s_obs, s_path, s_unom, w0, nw, k0,
-                                                        phi0, s_u, lds_stride, t_local, s_J);
-        done = true;
-      }
-    }
-    if (!done) {
-      if (d.any_e4)
-        rollout_sample<NOB, GUIDED, G, PRE, true, false>(d, s, valid && g == 0, g, x0, s_obs, s_path, s_unom, w0, nw, k0,
-                                                         phi0, s_u, lds_stride, t_local, s_J);
-      else
-        rollout_sample<NOB, GUIDED, G, PRE, false, false>(d, s, valid && g == 0, g, x0, s_obs, s_path, s_unom, w0, nw, k0,
-                                                          phi0, s_u, lds_stride, t_local, s_J);
+      if (d.row_kind == kRowsDisc) rollout(std::integral_constant<int, kRowsDisc>{});
+      else if (d.row_kind == kRowsE4) rollout(std::integral_constant<int, kRowsE4>{});
+      else if (d.row_kind == kRowsMoving) rollout(std::integral_constant<int, kRowsMoving>{});
+      else rollout(std::integral_constant<int, kRowsStatic>{});
+    } else {
+      // no rows: the kinds matter to the collision penalty alone
+      if (d.row_kind == kRowsDisc) rollout(std::integral_constant<int, kRowsDisc>{});
+      else rollout(std::integral_constant<int, kRowsE4>{});
     }
     __syncthreads();
     if (fused)

@@ -268,9 +268,32 @@ struct HipServed {
 // in-kernel noise; 1 = one lane, precomputed noise; 2 / 3 / 4 = two / four /
 // eight lanes per sample, precomputed noise).  No shape changes any result bit.
 struct LaunchShape {
-  uint32_t block = 128;
+  uint32_t block = 0;    // 0: not set
   int variant = 0;
 };
+
+// The shape of a plain solve that is neither tuned nor forced.  Blocks of 256:
+// the dispatcher spreads a block's waves over its CU's SIMDs, and two blocks of
+// two waves can land on the same two (65536 samples, 32 rows, one lane: 610 us
+// at 128 threads, 330 at 256).  Lanes: as many as put one wave on each of the
+// 1024 SIMDs (65536 lanes), since a wave issues at most one instruction every
+// 4 cycles whatever else its SIMD holds; beyond that a lane keeps at most
+// eight rows, because the one- and two-lane forms with more rows run out of
+// registers.  Measured (us a solve, T = 40; 2/8/16/32 rows; two, four, eight
+// lanes): 12000 samples 64 63 75 / 87 75 81 / 119 88 91 / 165 115 106; 20011
+// samples 69 79 98 / 92 95 103 / 124 111 116 / 173 146 141; 32768 samples 74 85
+// 121 / 95 98 122 / 128 113 138 / 179 152 172; 65536 samples with one lane and
+// precomputed normals 89 / 128 / 650 / 333, with four lanes 124 / 152 / 186 / 280.
+LaunchShape default_shape(int bucket, uint32_t S) {
+  LaunchShape s;
+  s.block = 256;
+  if (bucket == 0) s.variant = S <= 8192 ? 1 : 0;
+  else if (S <= 8192) s.variant = 4;
+  else if (bucket == 32) s.variant = S <= 24576 ? 4 : 3;
+  else if (bucket == 16) s.variant = 3;
+  else s.variant = S <= 16384 ? 3 : (S <= 32768 ? 2 : 1);
+  return s;
+}
 
 constexpr int kBuckets[5] = {0, 2, 8, 16, 32};
 int bucket_index(int bucket) {
@@ -292,8 +315,8 @@ struct brmppi_ctx {
   int n_cu = 256;
   std::string tune_path;
   std::vector<Controller> ctrl;
-  LaunchShape shape[5][4];      // plain-path table: [bucket index][S class]
-  uint32_t batch_block[5] = {256, 128, 128, 128, 128};  // persistent (variant 0) block per bucket
+  LaunchShape shape[5][4];      // plain-path table, tuned entries: [bucket index][S class]
+  uint32_t batch_block[5] = {256, 256, 256, 256, 256};  // persistent (variant 0) block per bucket
   LaunchShape forced{0, 0};     // block 0 = not forced
   Block counters_blk;           // BatchCounters per stream + spare
   BatchCounters* counters = nullptr;
@@ -450,7 +473,6 @@ void fill_desc(SolveDesc& d, const brmppi_problem& p, const Controller& c, const
   d.T = p.T;
   d.n_obs = p.n_obs * n_discs(d.prm);      // obstacle rows
   d.n_objects = p.n_obs;
-  d.any_disc = footprint_is_rear_axle(d.prm) ? 0u : 1u;
   d.flags = p.flags;
   d.n_path = c.n_path;
   d.instance = p.instance;
@@ -482,10 +504,14 @@ void fill_desc(SolveDesc& d, const brmppi_problem& p, const Controller& c, const
   d.plant_x = c.plant;
   d.n_normals = (p.flags & BRMPPI_GUIDANCE_OFF) ? 3u : 5u + d.n_obs;
   d.noise = L.n_normals ? reinterpret_cast<float*>(base + L.off_noise) : nullptr;
+  uint32_t kind = kRowsStatic;
   for (uint32_t i = 0; i < p.n_obs; ++i) {
-    d.obs[i] = p.obs[i];
-    if (p.obs[i].e == 4.0f) d.any_e4 = 1u;
+    const brmppi_obstacle& o = p.obs[i];
+    d.obs[i] = o;
+    if (o.e == 4.0f) kind = kRowsE4;
+    else if ((o.vx != 0.0f || o.vy != 0.0f) && kind == kRowsStatic) kind = kRowsMoving;
   }
+  d.row_kind = footprint_is_rear_axle(d.prm) ? kind : (uint32_t)kRowsDisc;
 }
 
 // launch shape of a plain (single-instance) rollout
@@ -493,8 +519,10 @@ LaunchShape plain_shape(brmppi_ctx* ctx, const brmppi_problem& p) {
   const int bucket = bucket_for(obstacle_rows(ctx, p), p.flags);
   LaunchShape s = ctx->forced.block ? ctx->forced : ctx->shape[bucket_index(bucket)][s_class(p.S)];
   if (bucket == 0 && s.variant > 1) s.variant = 1;        // unguided: one lane per sample
+  if (s.block == 0) s = default_shape(bucket, p.S);
   const size_t noise = (size_t)normals_per_step(ctx, p) * p.T * round_up(p.S, 256) * sizeof(float);
-  if (variant_pre(s.variant) && noise > std::min(kMaxNoiseBytes, ctx->arena.size() / 2)) s.variant = 0;
+  if (variant_pre(s.variant) && noise > std::min(kMaxNoiseBytes, ctx->arena.size() / 2))
+    s.variant = 0;
   return s;
 }
 
@@ -1355,15 +1383,6 @@ int brmppi_create(const brmppi_config* cfg, brmppi_ctx** out) {
   int ncu = 0;
   HIPCHK(hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, cfg->device));
   ctx->n_cu = ncu > 0 ? ncu : 256;
-  // untuned defaults: few samples -> several lanes per sample so that the
-  // launch still covers the device; many samples -> one lane, in-kernel noise
-  for (int bi = 0; bi < 5; ++bi) {
-    const bool guided = kBuckets[bi] > 0;
-    ctx->shape[bi][0] = LaunchShape{256, guided ? 4 : 1};
-    ctx->shape[bi][1] = LaunchShape{256, guided ? 4 : 1};
-    ctx->shape[bi][2] = LaunchShape{256, guided ? 2 : 0};
-    ctx->shape[bi][3] = LaunchShape{128, 0};
-  }
   ctx->ctrl.resize(cfg->max_controllers);
   const brmppi_params defaults = default_params();
   for (Controller& c : ctx->ctrl) c.params = defaults;
@@ -1737,8 +1756,8 @@ int brmppi_autotune(brmppi_ctx* ctx) {
       uint32_t best_v0_block = ctx->batch_block[bi];
       std::string times;             // [block, variant, ms per noise + rollout + reduce] of every candidate
       for (int variant = 0; variant <= kMaxVariant; ++variant) {
-        if (bucket == 0 && variant > 1) continue;
         const uint32_t lanes = (uint32_t)variant_lanes(variant);
+        if (bucket == 0 && variant > 1) continue;
         for (uint32_t block : {64u, 128u, 256u}) {
           const uint32_t per_tile = block / lanes;
           const uint32_t grid = (S + per_tile - 1) / per_tile;
