@@ -284,11 +284,14 @@ struct LaunchShape {
 // samples 69 79 98 / 92 95 103 / 124 111 116 / 173 146 141; 32768 samples 74 85
 // 121 / 95 98 122 / 128 113 138 / 179 152 172; 65536 samples with one lane and
 // precomputed normals 89 / 128 / 650 / 333, with four lanes 124 / 152 / 186 / 280.
-LaunchShape default_shape(int bucket, uint32_t S) {
+// Without guidance the lanes share the stage costs, which the collision penalty
+// makes the largest part: 20011 samples, two / four / eight lanes 51 / 52 / 54,
+// with the penalty 67 / 58 / 58; 65536 with one / four 69 / 83 and 93 / 95.
+LaunchShape default_shape(int bucket, uint32_t S, bool penalty) {
   LaunchShape s;
   s.block = 256;
-  if (bucket == 0) s.variant = S <= 8192 ? 1 : 0;
-  else if (S <= 8192) s.variant = 4;
+  if (S <= 8192) s.variant = 4;
+  else if (bucket == 0 && penalty) s.variant = S <= 24576 ? 4 : 3;
   else if (bucket == 32) s.variant = S <= 24576 ? 4 : 3;
   else if (bucket == 16) s.variant = 3;
   else s.variant = S <= 16384 ? 3 : (S <= 32768 ? 2 : 1);
@@ -518,8 +521,7 @@ void fill_desc(SolveDesc& d, const brmppi_problem& p, const Controller& c, const
 LaunchShape plain_shape(brmppi_ctx* ctx, const brmppi_problem& p) {
   const int bucket = bucket_for(obstacle_rows(ctx, p), p.flags);
   LaunchShape s = ctx->forced.block ? ctx->forced : ctx->shape[bucket_index(bucket)][s_class(p.S)];
-  if (bucket == 0 && s.variant > 1) s.variant = 1;        // unguided: one lane per sample
-  if (s.block == 0) s = default_shape(bucket, p.S);
+  if (s.block == 0) s = default_shape(bucket, p.S, (p.flags & BRMPPI_COLLISION_PENALTY) != 0);
   const size_t noise = (size_t)normals_per_step(ctx, p) * p.T * round_up(p.S, 256) * sizeof(float);
   if (variant_pre(s.variant) && noise > std::min(kMaxNoiseBytes, ctx->arena.size() / 2))
     s.variant = 0;
@@ -1316,8 +1318,7 @@ int load_tune(brmppi_ctx* ctx) {
       if (comma == std::string::npos) continue;
       const long var = std::strtol(s.c_str() + comma + 1, nullptr, 10);
       const int lanes = variant_lanes((int)var);
-      if (valid_block(blk) && var >= 0 && var <= kMaxVariant && (kBuckets[bi] > 0 || var <= 1) &&
-          blk % lanes == 0)
+      if (valid_block(blk) && var >= 0 && var <= kMaxVariant && blk % lanes == 0)
         ctx->shape[bi][sc] = LaunchShape{(uint32_t)blk, (int)var};
     }
     const std::string kb = "\"batch_" + std::to_string(kBuckets[bi]) + "\"";
@@ -1757,7 +1758,6 @@ int brmppi_autotune(brmppi_ctx* ctx) {
       std::string times;             // [block, variant, ms per noise + rollout + reduce] of every candidate
       for (int variant = 0; variant <= kMaxVariant; ++variant) {
         const uint32_t lanes = (uint32_t)variant_lanes(variant);
-        if (bucket == 0 && variant > 1) continue;
         for (uint32_t block : {64u, 128u, 256u}) {
           const uint32_t per_tile = block / lanes;
           const uint32_t grid = (S + per_tile - 1) / per_tile;
