@@ -263,11 +263,11 @@ int brmppi_solve_ex(brmppi_ctx* ctx, const brmppi_problem* p, const brmppi_outpu
 int brmppi_solve_noalloc(brmppi_ctx* ctx, const brmppi_problem* p, float* u_out, brmppi_stats* st);
 
 /* ---- batched solve (blocking) ------------------------------------------- */
-/* n independent updates (distinct controllers) together: persistent rollout
- * launches over a tile list (one per constraint bucket present; a bucket too
- * small to fill the device joins the next heavier one), then one persistent
- * reduce over every instance, captured in a HIP graph and replayed while the
- * batch keeps its shape.  u_outs[i] receives T_i*3 floats; st may be NULL or
+/* n independent updates (distinct controllers) together: one persistent rollout
+ * launch over the tiles of every instance (normals drawn in the kernel, one,
+ * two or four lanes per sample by the instance's constraint rows), then one
+ * persistent reduce over every instance, captured in a HIP graph and replayed
+ * while the batch keeps its shape.  u_outs[i] receives T_i*3 floats; st may be NULL or
  * an array of n.  Each instance's result equals its plain solve, bitwise. */
 int brmppi_solve_batch(brmppi_ctx* ctx, const brmppi_problem* p, uint32_t n, float* const* u_outs,
                        brmppi_stats* st);
@@ -304,18 +304,18 @@ int brmppi_closed_loop(brmppi_ctx* ctx, const brmppi_problem* p, uint32_t n_upda
  * synthetic problems with a 48-step horizon, rollout plus reduction as a plain
  * solve runs them, and keep the fastest per constraint bucket (0, <=2, <=8,
  * <=16, <=32 obstacles) and sample-count class (<=2048, <=8192, <=32768,
- * more), plus the block size of the batched persistent kernel; a shape whose
- * tiles reduce themselves wins ties within 2 %.  Writes the JSON cache named
+ * more); a shape whose tiles reduce themselves wins ties within 2 %.  Writes the JSON cache named
  * in the config (if any), with every candidate's time.  Shapes never change a
  * result bit. */
 int brmppi_autotune(brmppi_ctx* ctx);
 /* Force a rollout launch shape for every plain and batched launch: block size
  * 64..256 (multiple of 64) and variant 0 = one lane per sample, noise drawn in
  * the kernel; 1 = one lane, noise from the parallel kernel; 2 / 3 / 4 = two /
- * four / eight lanes per sample, noise from the parallel kernel (batched
- * launches always use variant 0; a plain solve whose normals would take more than 2 GiB or half the
- * arena runs variant 0).  block 0 restores the tuned/default choice.  EINVAL for a block
- * outside 64..256 or not a multiple of 64, or a variant above 4. */
+ * four / eight lanes per sample, noise from the parallel kernel (a batched
+ * launch takes the block size and its own forms; a plain solve whose normals
+ * would take more than 2 GiB or half the arena draws them in the kernel).  block
+ * 0 restores the tuned/default choice.  EINVAL for a block outside 64..256 or
+ * not a multiple of 64, or a variant above 4. */
 int brmppi_set_launch(brmppi_ctx* ctx, uint32_t block, uint32_t variant);
 /* Kernel timings accumulated under BRMPPI_CTX_PROFILE (every kernel of the
  * blocking calls) or BRMPPI_CTX_PROFILE_ROLLOUT (rollout and noise only), from

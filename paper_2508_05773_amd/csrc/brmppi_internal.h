@@ -42,7 +42,7 @@ struct alignas(16) SolveDesc {
   uint32_t x0_resident, n_normals, fused, ustar_global;   // n_normals: 5 + n_obs (guided) or 3
   uint32_t n_units, row_kind, rows_item, pad3;     // row_kind: which rows the rollout's step forms
                                                    // (RowKind); rows_item: rows of one reduce work item
-  uint32_t n_objects, pad0, pad1, pad2;          // obstacles (row r: obstacle r % n_objects, disc
+  uint32_t n_objects, bucket, pad1, pad2;        // bucket: bucket_for(n_obs, flags); obstacles (row r: obstacle r % n_objects, disc
                                                  // r / n_objects)
   const float4* path;           // controller path (absolute coordinates)
   const float* u_nom_in;        // 3T nominal sequence read by the rollout
@@ -80,10 +80,15 @@ struct alignas(16) BatchCounters {
 constexpr int kMaxVariant = 4;   // 0: G1 fused noise, 1: G1, 2: G2, 3: G4, 4: G8 (precomputed noise)
 int variant_lanes(int variant);
 bool variant_pre(int variant);
+int variant_in_kernel(int bucket);
 // lds_bytes > 0: the single instance's tiles reduce themselves (fused epilogue;
 // descs->fused must be set and the tile size a multiple of kUnit)
-hipError_t launch_rollout(int bucket, int variant, const SolveDesc* descs, const Tile* tiles, uint32_t n_tiles,
-                          BatchCounters* ctr, uint32_t grid, uint32_t block, size_t lds_bytes, hipStream_t stream);
+hipError_t launch_rollout(int bucket, int variant, const SolveDesc* desc, uint32_t grid, uint32_t block,
+                          size_t lds_bytes, hipStream_t stream);
+// the rollouts of a batch's tiles (each of block / variant_lanes(variant_in_kernel(bucket))
+// samples of its instance); grid at most n_tiles
+hipError_t launch_rollout_batch(const SolveDesc* descs, const Tile* tiles, uint32_t n_tiles, BatchCounters* ctr,
+                                uint32_t grid, uint32_t block, hipStream_t stream);
 // dynamic LDS of the fused epilogue for a tile of `per_tile` samples: the
 // tile's applied inputs [3T][per_tile + 1] (later reused for the n_groups
 // merge scales), costs, weights, unit minima and scales, unit partials
@@ -113,8 +118,8 @@ hipError_t launch_normals_dump(uint32_t seed_lo, uint32_t seed_hi, uint32_t inst
                                uint32_t n, uint32_t K, float* out, hipStream_t stream);
 hipError_t launch_box_muller_dump(const uint32_t* r, uint32_t n, float* out, hipStream_t stream);
 hipError_t launch_fill_u32(uint32_t* p, uint32_t value, size_t n, hipStream_t stream);
-// occupancy of a rollout variant for a bucket and block size (blocks per CU)
-int rollout_blocks_per_cu(int bucket, int variant, uint32_t block);
+// occupancy of the batched rollout for a block size (blocks per CU)
+int rollout_batch_blocks_per_cu(uint32_t block);
 
 // footprint discs of a parameter set, and whether it is other than the rear
 // axle alone (the point eq. (16) uses)

@@ -34,14 +34,18 @@ namespace brm {
 // Philox4x32-10 (Salmon et al., SC'11): 10 rounds of two 32x32->64 products,
 // Weyl-sequence key schedule.
 // ---------------------------------------------------------------------------
+// a ^ b ^ c in one instruction (the compiler forms two)
+__device__ __forceinline__ uint32_t xor3(uint32_t a, uint32_t b, uint32_t c) {
+  return __builtin_amdgcn_bitop3_b32(a, b, c, 0x96);
+}
 __device__ __forceinline__ void philox4x32_10(uint32_t c0, uint32_t c1, uint32_t c2, uint32_t c3,
                                               uint32_t k0, uint32_t k1, uint32_t out[4]) {
 #pragma unroll
   for (int r = 0; r < 10; ++r) {
     const uint64_t p0 = (uint64_t)0xD2511F53u * (uint64_t)c0;
     const uint64_t p1 = (uint64_t)0xCD9E8D57u * (uint64_t)c2;
-    const uint32_t n0 = (uint32_t)(p1 >> 32) ^ c1 ^ k0;
-    const uint32_t n2 = (uint32_t)(p0 >> 32) ^ c3 ^ k1;
+    const uint32_t n0 = xor3((uint32_t)(p1 >> 32), c1, k0);
+    const uint32_t n2 = xor3((uint32_t)(p0 >> 32), c3, k1);
     c1 = (uint32_t)p1;
     c3 = (uint32_t)p0;
     c0 = n0;
@@ -567,27 +571,22 @@ __device__ __forceinline__ Acc5 acc_partner_add(const Acc5& a) {
 // number G of lanes per sample: row r belongs to virtual lane v(r) (hitch row
 // k -> v = k, obstacle o -> v = o mod 8); a virtual lane sums its rows from
 // zero in row order (hitch row first, then obstacles v, v + 8, ...); the 8
-// virtual sums are added by a fixed binary tree (v ^ 1, then v ^ 2, then v ^ 4).
-// Lane q of a group owns virtual lanes q + G i.  The levels that pair virtual
-// lanes on different lanes run as DPP butterflies (IEEE addition commutes, so
-// both partners hold the same bits), the rest inside the lane.
+// virtual sums are added by a fixed binary tree (v ^ 4, then v ^ 2, then v ^ 1).
+// A group's lane of index q owns virtual lanes q + G i, so the levels inside a
+// lane come first and only log2 G levels cross lanes, as DPP butterflies (IEEE
+// addition commutes, so both partners hold the same bits).  With eight lanes
+// the first level is the half-row mirror (lane i reads lane 7 - i), so lanes 4
+// to 7 take the indices 7 to 4 (lane_index).
+template <int G>
+__device__ __forceinline__ int lane_index(int g) {
+  return G == 8 && g >= 4 ? 11 - g : g;
+}
 template <int G>
 __device__ __forceinline__ Acc5 cross_lane_levels(Acc5 a) {
-  if constexpr (G >= 2) a = acc_partner_add<kDppXor1>(a);
-  if constexpr (G >= 4) a = acc_partner_add<kDppXor2>(a);
   if constexpr (G >= 8) a = acc_partner_add<kDppHalfMirror>(a);
+  if constexpr (G >= 4) a = acc_partner_add<kDppXor2>(a);
+  if constexpr (G >= 2) a = acc_partner_add<kDppXor1>(a);
   return a;
-}
-
-template <int G, int LO, int N, typename Leaf>
-__device__ __forceinline__ Acc5 virtual_tree(Leaf& leaf) {
-  if constexpr (N == 1) {
-    return cross_lane_levels<G>(leaf(std::integral_constant<int, LO>{}));
-  } else {
-    const Acc5 l = virtual_tree<G, LO, N / 2>(leaf);
-    const Acc5 r = virtual_tree<G, LO + N / 2, N / 2>(leaf);
-    return acc_add(l, r);
-  }
 }
 
 // Collision-penalty baseline (the paper's second MPPI baseline, Sec. V; its
@@ -731,9 +730,17 @@ constexpr int philox_blocks() {
   return GUIDED ? (5 + NOB + 3) / 4 : 1;
 }
 
+// Normals drawn in the kernel for samples shared by G lanes: lane g draws the
+// blocks g, g + G, ..., and the lanes read what they need from the sample's
+// place in LDS (in floats; 16 bytes of padding spread the samples over the banks)
+template <int NOB, int G>
+constexpr int coop_stride() {
+  return 4 * G * ((philox_blocks<NOB, true>() + G - 1) / G) + 4;
+}
+
 // One sample's rollout over T steps, run by the G lanes of its group (lane g).
 // Rows: every lane computes the hitch row g mod 2 (G = 1: both), obstacle o is
-// computed by lane o mod G in its slot o / G.  After the projection every lane
+// computed by the lane of index o mod G in its slot o / G.  After the projection every lane
 // holds the same inputs, state and cost.
 // s_u / s_J (fused epilogue): the tile's applied inputs [3T][lds_stride] and
 // costs in LDS, at column t_local.
@@ -741,26 +748,27 @@ template <int NOB, bool GUIDED, int G, bool PRE, int ROWS>
 __device__ __forceinline__ void rollout_sample(const SolveDesc& d, uint32_t s, bool store, int g, const float* x0,
                                                const ObsL* __restrict__ sobs, const float4* __restrict__ spath,
                                                const float4* __restrict__ s_un, int w0, int nw, int k0, float phi0,
-                                               float* s_u, uint32_t lds_stride, uint32_t t_local, float* s_J) {
+                                               float* s_u, uint32_t lds_stride, uint32_t t_local, float* s_J,
+                                               float* s_nrm) {
   static_assert(G == 1 || G == 2 || G == 4 || G == 8, "lanes per sample");
   constexpr int NSL = GUIDED ? (NOB + G - 1) / G : 1;   // obstacle slots of this lane
   constexpr int NV = 8 / G;                            // virtual lanes of this lane
+  constexpr int kLeaves = NSL > (G == 1 ? 2 : 1) ? (NSL < NV ? NSL : NV) : (G == 1 ? 2 : 1);   // of them with rows
   constexpr int NH = (G == 1) ? 2 : 1;                 // hitch rows computed by this lane
   constexpr int NBMAX = philox_blocks<NOB, GUIDED>();    // Philox blocks of a step
-  static_assert(PRE || G == 1, "a sample shared by lanes reads precomputed normals");
+  // normals drawn in the kernel and shared by the sample's lanes through LDS
+  constexpr bool kCoop = !PRE && G > 1;
   const brmppi_params& P = d.prm;
   const uint32_t T = d.T;
   const int n_obs = (int)d.n_obs;
   const bool hitch = !(d.flags & BRMPPI_HITCH_OFF);
-  // an unguided instance may share a guided batched launch (which draws its
-  // normals in the kernel): the flag is honoured here
-  const bool guided = GUIDED && (PRE || !(d.flags & BRMPPI_GUIDANCE_OFF));
   const bool penalty = (d.flags & BRMPPI_COLLISION_PENALTY) != 0;
-  const int nb = guided ? (5 + n_obs + 3) / 4 : 1;
+  const int nb = GUIDED ? (5 + n_obs + 3) / 4 : 1;
   const float ox = x0[0], oy = x0[1];
   const float4* __restrict__ gpath = d.path;
   const int n_path = (int)d.n_path;
   const int hk0 = (G == 1) ? 0 : (g & 1);    // first hitch row of this lane
+  const int gi = lane_index<G>(g);           // its obstacles are gi + G j
 
   // constants of the step.  Held in vector registers (an empty asm makes each a
   // per-lane value): an instruction with a scalar operand takes 4 cycles of
@@ -843,7 +851,7 @@ __device__ __forceinline__ void rollout_sample(const SolveDesc& d, uint32_t s, b
   ObsL ob_r[kObsRegs ? NSL : 1];
   if constexpr (kObsRegs) {
 #pragma unroll
-    for (int j = 0; j < NSL; ++j) ob_r[j] = sobs[g + G * j];
+    for (int j = 0; j < NSL; ++j) ob_r[j] = sobs[gi + G * j];
   }
 
   // Precomputed normals are loaded two steps ahead into a queue of two slots:
@@ -858,7 +866,7 @@ __device__ __forceinline__ void rollout_sample(const SolveDesc& d, uint32_t s, b
   // arithmetic per load.
   static_assert(!PRE || kNoisePrefetch == 2, "two queue slots");
   constexpr int PF = PRE ? 2 : 1;
-  float nx_in[PF][3], nx_h[PF][NH], nx_o[PF][NSL];
+  float nx_in[PF][3], nx_h[PF][NH], nx_o[PF][NSL];   // (kCoop: the next step's, read from LDS)
   uint32_t off_in[3], off_h[NH], off_o[NSL];
   const uint32_t step_bytes = d.n_normals * S_pad * (uint32_t)sizeof(float);
   const uint32_t last_bytes = step_bytes * (T - 1);
@@ -872,7 +880,7 @@ __device__ __forceinline__ void rollout_sample(const SolveDesc& d, uint32_t s, b
 #pragma unroll
     for (int k = 0; k < NH; ++k) off_h[k] = 4u * (min((uint32_t)(3 + hk0 + k), n_rows - 1) * S_pad + s);
 #pragma unroll
-    for (int j = 0; j < NSL; ++j) off_o[j] = 4u * (min((uint32_t)(5 + g + G * j), n_rows - 1) * S_pad + s);
+    for (int j = 0; j < NSL; ++j) off_o[j] = 4u * (min((uint32_t)(5 + gi + G * j), n_rows - 1) * S_pad + s);
   }
   auto load_normals = [&](int q) __attribute__((always_inline)) {
     if constexpr (PRE) {
@@ -897,6 +905,42 @@ __device__ __forceinline__ void rollout_sample(const SolveDesc& d, uint32_t s, b
     load_normals(1);
     __builtin_amdgcn_sched_barrier(0);
   }
+  // kCoop: the step's blocks into the sample's place in LDS, and this lane's
+  // normals from it.  The lanes of a sample are lanes of one wave, whose LDS
+  // operations execute in order: the fences only keep the compiler from
+  // reordering them.  A normal past the drawn blocks (rows past the last
+  // obstacle) is read from the last drawn one.
+  float* const nrm = kCoop ? s_nrm + t_local * coop_stride<NOB, G>() : nullptr;
+  uint32_t nrm_o[NSL];
+  if constexpr (kCoop) {
+#pragma unroll
+    for (int j = 0; j < NSL; ++j) nrm_o[j] = min((uint32_t)(5 + gi + G * j), (uint32_t)(4 * nb - 1));
+  }
+  auto coop_draw = [&](uint32_t tau) __attribute__((always_inline)) {
+    if constexpr (kCoop) {
+      asm volatile("" ::: "memory");
+#pragma unroll
+      for (int i = 0; i * G < NBMAX; ++i) {
+        if (i * G < nb) {
+          uint32_t r[4];
+          float e[4];
+          philox4x32_10(s, tau, (uint32_t)(g + G * i), d.instance, d.seed_lo, d.seed_hi, r);
+          box_muller4(r, e);
+          lds_put(reinterpret_cast<float4*>(nrm) + g + G * i, make_float4(e[0], e[1], e[2], e[3]));
+        }
+      }
+      asm volatile("" ::: "memory");
+      const Vec3 in = lds3(reinterpret_cast<const float4*>(nrm));
+      nx_in[0][0] = in.x;
+      nx_in[0][1] = in.y;
+      nx_in[0][2] = in.z;
+#pragma unroll
+      for (int k = 0; k < NH; ++k) nx_h[0][k] = lds(nrm + min(3 + hk0 + k, 4 * nb - 1));
+#pragma unroll
+      for (int j = 0; j < NSL; ++j) nx_o[0][j] = lds(nrm + nrm_o[j]);
+    }
+  };
+  coop_draw(0);
   Vec3 un = lds3(s_un);                        // nominal inputs, read a step ahead
   // uniform switches, tested as scalar integers each step (as conditions they
   // would be kept as lane masks and cost twice the instructions)
@@ -910,7 +954,7 @@ __device__ __forceinline__ void rollout_sample(const SolveDesc& d, uint32_t s, b
     // --- noise: normals 0..2 perturb the inputs, 3 and 4 the hitch rows'
     // auxiliary inputs, 5 + o obstacle o's ---
     float uj, uw, unu, nz_h[NH], nz_o[NSL];
-    if constexpr (PRE) {
+    if constexpr (PRE || kCoop) {
       uj = fmaf(sj, nx_in[q][0], un.x);
       uw = fmaf(sw, nx_in[q][1], un.y);
       unu = fmaf(sn, nx_in[q][2], un.z);
@@ -943,6 +987,7 @@ __device__ __forceinline__ void rollout_sample(const SolveDesc& d, uint32_t s, b
         for (int j = 0; j < NSL; ++j) nz_o[j] = fmaf(ke, eps[5 + j], kc);   // G == 1: slot j is obstacle j
       }
     }
+    if constexpr (kCoop) coop_draw(tau + 1);   // (the draw of step T is unused)
     un = lds3(s_un + (tau + 1));   // (past the last step: the staged array's extra entry, unused)
     RefPoint rf{};
     if constexpr (!kBatchCost) rf = reference(f, k0, n_path, spath, w0, nw, gpath, ox, oy);
@@ -973,7 +1018,7 @@ __device__ __forceinline__ void rollout_sample(const SolveDesc& d, uint32_t s, b
     }
 
     float U0 = 0.0f;
-    if (GUIDED && guided) {
+    if constexpr (GUIDED) {
       const float sec2 = fmaf(tn, tn, 1.0f);
       const StepGeom geo = step_geom<ROWS != kRowsStatic>(px, py, c1, s1, vc, vs, vh, ah, kd, w, (float)tau);
       DiscBasis DB;
@@ -1013,65 +1058,47 @@ __device__ __forceinline__ void rollout_sample(const SolveDesc& d, uint32_t s, b
         O[j].Q = R.g1 * ih;
         acc_row(A, O[j], O[j].L + fmaf(ka, bt_o[j], nz_o[j]));
       };
-      Acc5 S8;
+      // Rows two slots at a time, so that one branch and one wait for the
+      // obstacles' LDS reads serve two rows; no branch where every instance of
+      // the kernel's bucket has the first of them.  A row past the last
+      // obstacle reads a staged blank one (Q = A = 0: hhat = -1, Lf = g = +-0)
+      // and a finite normal, so it adds exact zeros to the sums (an accumulator
+      // is never -0, so x + 0 keeps its bits), without divergent branches or
+      // selects.
+      constexpr int kMinRows = NOB == 32 ? 17 : (NOB == 16 ? 9 : (NOB == 8 ? 3 : 0));
+      Acc5 A[NV];
+#pragma unroll
+      for (int i = 0; i < NV; ++i) A[i] = acc_zero();
       if constexpr (G == 1) {
-        // The tree's first level, leaves V and V + 1: rows two at a time, so that
-        // one branch and one wait for the obstacles' LDS reads serve two rows
-        // (a row past the last obstacle reads a staged blank one and a zero
-        // normal, and adds exact zeros).  Leaves without rows are zero and left out.
-        auto node = [&](auto V) __attribute__((always_inline)) -> Acc5 {
-          constexpr int v = decltype(V)::value;
-          Acc5 A0 = acc_zero(), A1 = acc_zero();
-          if constexpr (v == 0) {
-            if (hitch) {
-              acc_row(A0, H[0], H[0].L + fmaf(ka, bt_h[0], nz_h[0]));
-              acc_row(A1, H[1], H[1].L + fmaf(ka, bt_h[1], nz_h[1]));
-            }
-          }
-          auto rows = [&](auto self, auto J) __attribute__((always_inline)) -> void {
-            constexpr int j = decltype(J)::value;
-            if constexpr (j < NSL) {
-              if (j < n_obs) {
-                const ObsL oa = sobs[j], ob = sobs[j + 1];
-                obs_row(j, oa, A0);
-                obs_row(j + 1, ob, A1);
-                self(self, std::integral_constant<int, j + 8>{});
-              }
-            }
-          };
-          rows(rows, V);
-          return acc_add(A0, A1);
-        };
-        S8 = node(std::integral_constant<int, 0>{});
-        if constexpr (NSL > 2) {
-          const Acc5 a = node(std::integral_constant<int, 2>{});
-          S8 = acc_add(S8, a);
-          const Acc5 b = node(std::integral_constant<int, 4>{});
-          const Acc5 c = node(std::integral_constant<int, 6>{});
-          S8 = acc_add(S8, acc_add(b, c));
+        if (hitch) {
+          acc_row(A[0], H[0], H[0].L + fmaf(ka, bt_h[0], nz_h[0]));
+          acc_row(A[1], H[1], H[1].L + fmaf(ka, bt_h[1], nz_h[1]));
         }
       } else {
-        auto leaf = [&](auto I) -> Acc5 {
-          constexpr int i = decltype(I)::value;
-          Acc5 A = acc_zero();
-          // lanes 0 and 1 hold the hitch rows; the others add exact zeros (P =
-          // Q = 0 and finite s give products of +-0, and an accumulator is
-          // never -0, so x + 0 keeps its bits)
-          if (i == 0) acc_row(A, H[0], H[0].L + fmaf(ka, bt_h[0], nz_h[0]));
-#pragma unroll
-          for (int j = i; j < NSL; j += NV) {
-            if (NSL == 1 || G * j < n_obs) {
-              // lanes past the last obstacle read a staged blank obstacle (Q = A =
-              // 0): its row has hhat = -1 and Lf = g = +-0, so it adds exact
-              // zeros to the sums, without a divergent branch or selects
-              if constexpr (kObsRegs) obs_row(j, ob_r[j], A);
-              else obs_row(j, sobs[g + G * j], A);
-            }
-          }
-          return A;
-        };
-        S8 = virtual_tree<G, 0, NV>(leaf);
+        // lanes 0 and 1 hold the hitch rows; the others add exact zeros
+        acc_row(A[0], H[0], H[0].L + fmaf(ka, bt_h[0], nz_h[0]));
       }
+#pragma unroll
+      for (int j = 0; j < NSL; j += 2) {
+        if (G * j < kMinRows || G * j < n_obs) {
+          ObsL oa, ob;
+          if constexpr (kObsRegs) oa = ob_r[j];
+          else oa = sobs[gi + G * j];
+          if (j + 1 < NSL) {
+            if constexpr (kObsRegs) ob = ob_r[j + 1 < NSL ? j + 1 : 0];
+            else ob = sobs[gi + G * (j + 1)];
+          }
+          obs_row(j, oa, A[j % NV]);
+          if (j + 1 < NSL) obs_row(j + 1, ob, A[(j + 1) % NV]);
+        }
+      }
+#pragma unroll
+      for (int n = NV / 2; n >= 1; n /= 2) {
+#pragma unroll
+        for (int i = 0; i < n; ++i)
+          if (i + n < kLeaves) A[i] = acc_add(A[i], A[i + n]);
+      }
+      const Acc5 S8 = cross_lane_levels<G>(A[0]);
       const double G1d = (double)G1, MG1 = Mad * G1d;
       const double N00 = fma(K00, S8.PP, NJ), N01 = (MG0 * G1d) * S8.PQ, N11 = fma(MG1 * G1d, S8.QQ, NW);
       const double y0 = fma(-MG0, S8.Ps, (double)fmaf(Wj, uj, pj0));
@@ -1097,7 +1124,7 @@ __device__ __forceinline__ void rollout_sample(const SolveDesc& d, uint32_t s, b
       }
 #pragma unroll
       for (int j = 0; j < NSL; ++j) {
-        if (G == 1 ? ((j & ~1) < n_obs) : (NSL == 1 || G * j < n_obs)) bt_o[j] = fmaf(O[j].Q, U1, fmaf(O[j].P, U0, O[j].L));
+        if (G * (j & ~1) < kMinRows || G * (j & ~1) < n_obs) bt_o[j] = fmaf(O[j].Q, U1, fmaf(O[j].P, U0, O[j].L));
       }
     } else {
       U0 = G0 * uj;
@@ -1191,7 +1218,21 @@ __device__ __forceinline__ void rollout_sample(const SolveDesc& d, uint32_t s, b
   } else {
     do {
       step(tau, std::integral_constant<int, 0>{});
-    } while (++tau != T);
+      ++tau;
+      if constexpr (kBatchCost) {
+        if ((tau & (G - 1)) == 0) {
+          const float rc = kept_cost(tau - G);
+          add_lane_costs<G, 0>(J, rc);
+        }
+      }
+    } while (tau != T);
+    if constexpr (kBatchCost) {
+      const uint32_t n = T & (G - 1);
+      if (n != 0) {
+        const float rc = kept_cost(T - n);
+        add_lane_costs_n<G, 0>(J, rc, n);
+      }
+    }
   }
   const RefPoint rT = reference(f, k0, n_path, spath, w0, nw, gpath, ox, oy);   // the reference at psi_T
   float sr, cr;
@@ -1759,152 +1800,218 @@ __device__ __forceinline__ void tile_epilogue(const SolveDesc& d, uint32_t s0, u
   if (t == 0) atomicExch(d.counter, 0u);
 }
 
+// Where a tile's instance starts: the start state, the path index of its start
+// progress (k0 + phi0) and the window of the path staged in LDS (nw waypoints
+// from w0)
+struct TileStart {
+  float x0[8];
+  int k0, w0, nw;
+  float phi0;
+};
+
+// Stages a tile's instance into LDS: the path window, the nominal inputs and the
+// obstacle rows.  The caller's barrier completes it.
+__device__ __forceinline__ void stage_tile(const SolveDesc& d, float4* s_path, float4* s_unom, ObsL* s_obs,
+                                           TileStart& st) {
+  float (&x0)[8] = st.x0;
+  if (d.x0_resident) {
+#pragma unroll
+    for (int k = 0; k < 8; ++k) x0[k] = (float)d.plant_x[k];
+  } else {
+#pragma unroll
+    for (int k = 0; k < 8; ++k) x0[k] = d.x0[k];
+  }
+  const float ox = x0[0], oy = x0[1];
+  // progress origin: f0 = psi0/ds = k0 + phi0
+  const double f0 = (double)x0[7] / (double)d.ds;
+  double fk = floor(f0);
+  fk = fmin(fmax(fk, -1.0e9), 1.0e9);
+  const int k0 = (int)fk;
+  st.k0 = k0;
+  st.phi0 = (float)(f0 - fk);
+  const int n_path = (int)d.n_path;
+  int w0 = k0 - kPathBack;
+  if (w0 < 0) w0 = 0;
+  if (w0 > n_path - 2) w0 = n_path - 2;
+  int nw = n_path - w0;
+  if (nw > kPathWin) nw = kPathWin;
+  st.w0 = w0;
+  st.nw = nw;
+
+  // stage the obstacle rows (row r: obstacle r % n_objects around footprint
+  // disc r / n_objects) and the path window
+  if (threadIdx.x < d.n_obs) {
+    const uint32_t oi = threadIdx.x % d.n_objects;
+    const brmppi_obstacle o = d.obs[oi];
+    const float ax = o.mx + d.prm.r_disc, ay = o.my + d.prm.r_disc;
+    const float iax = 1.0f / (ax * ax), iay = 1.0f / (ay * ay);
+    float so, co;
+    sincosf(o.heading, &so, &co);
+    ObsL L;
+    L.cx = fmaf(o.vx, d.t0, o.cx - ox);
+    L.cy = fmaf(o.vy, d.t0, o.cy - oy);
+    L.mx = d.prm.Ts * o.vx;
+    L.my = d.prm.Ts * o.vy;
+    L.q11 = co * co * iax + so * so * iay;
+    L.q12 = co * so * (iax - iay);
+    L.q22 = so * so * iax + co * co * iay;
+    L.qa = 0.5f * (iax + iay);
+    L.qd = 0.5f * (iax - iay) * (co * co - so * so);
+    L.rx = fmaf(L.q12, L.my, L.q11 * L.mx);
+    L.ry = fmaf(L.q22, L.my, L.q12 * L.mx);
+    L.rr = fmaf(L.ry, L.my, L.rx * L.mx);
+    L.e4 = (o.e == 4.0f) ? 1.0f : 0.0f;
+    L.a00 = co / ax;
+    L.a01 = so / ax;
+    L.a10 = -so / ay;
+    L.a11 = co / ay;
+    L.pad = 0.0f;
+    disc_ab(d.prm, threadIdx.x / d.n_objects, L.dA, L.dB);
+    s_obs[threadIdx.x] = L;
+  } else if (threadIdx.x < BRMPPI_MAX_OBS) {
+    // blank slots (Q = A = 0, at rest): the rows of lanes past the last
+    // obstacle row
+    s_obs[threadIdx.x] = ObsL{};
+  }
+  // the path window (headings in revolutions) and the nominal inputs, their
+  // first loads all issued before the first store (the window's 4 per thread
+  // at 256 threads): one memory latency, not one per value a thread stages
+  const int Ti = (int)d.T, bd = (int)blockDim.x, tx = (int)threadIdx.x;
+  auto load_un = [&](int tau) __attribute__((always_inline)) {
+    const float* p = d.u_nom_in + 3 * min(tau, Ti - 1);
+    return make_float4(gld(p), gld(p + 1), gld(p + 2), 0.0f);
+  };
+  const float4 un0 = load_un(tx);
+  for (int j0 = 0; j0 < nw; j0 += 4 * bd) {
+    float4 w[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) w[k] = d.path[w0 + min(j0 + k * bd + tx, nw - 1)];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const int j = j0 + k * bd + tx;
+      if (j < nw) s_path[j] = make_float4(w[k].x - ox, w[k].y - oy, w[k].z * kInvTurn, w[k].w * kInvTurn);
+    }
+  }
+  if (tx < Ti) s_unom[tx] = un0;
+  for (int tau = tx + bd; tau < Ti; tau += bd) s_unom[tau] = load_un(tau);
+}
+
+// The rollouts of a staged tile of blockDim.x / G samples from s0 on.  Every lane
+// runs (lanes past S repeat the last sample and do not store), so the
+// group-wide DPP broadcasts always read active lanes.
+template <int NOB, bool GUIDED, int G, bool PRE>
+__device__ __forceinline__ void tile_rollout(const SolveDesc& d, uint32_t s0, const TileStart& st,
+                                             const float4* s_path, const float4* s_unom, const ObsL* s_obs,
+                                             float* s_u, uint32_t lds_stride, float* s_J, float* s_nrm) {
+  const uint32_t t_local = threadIdx.x / G;
+  const uint32_t s_raw = s0 + t_local;
+  const int g = (int)(threadIdx.x % G);
+  const bool valid = s_raw < d.S;
+  const uint32_t s = valid ? s_raw : d.S - 1;
+  auto rollout = [&](auto ROWS) __attribute__((always_inline)) {
+    rollout_sample<NOB, GUIDED, G, PRE, decltype(ROWS)::value>(d, s, valid && g == 0, g, st.x0, s_obs, s_path, s_unom,
+                                                              st.w0, st.nw, st.k0, st.phi0, s_u, lds_stride, t_local,
+                                                              s_J, s_nrm);
+  };
+  if constexpr (GUIDED) {
+    if (d.row_kind == kRowsDisc) rollout(std::integral_constant<int, kRowsDisc>{});
+    else if (d.row_kind == kRowsE4) rollout(std::integral_constant<int, kRowsE4>{});
+    else if (d.row_kind == kRowsMoving) rollout(std::integral_constant<int, kRowsMoving>{});
+    else rollout(std::integral_constant<int, kRowsStatic>{});
+  } else {
+    // no rows: the kinds matter to the collision penalty alone
+    if (d.row_kind == kRowsDisc) rollout(std::integral_constant<int, kRowsDisc>{});
+    else rollout(std::integral_constant<int, kRowsE4>{});
+  }
+}
+
+// Rollout of one instance (a direct launch, a tile per block).
 template <int NOB, bool GUIDED, int G, bool PRE>
 __global__ __launch_bounds__(kMaxBlock) __attribute__((amdgpu_waves_per_eu(rollout_waves_per_simd<NOB, G>(), 8)))
-void k_rollout(const SolveDesc* __restrict__ descs,
-                                                       const Tile* __restrict__ tiles, uint32_t n_tiles,
-                                                       BatchCounters* __restrict__ ctr) {
+void k_rollout(const SolveDesc* __restrict__ desc) {
   __shared__ float4 s_path[kPathWin];
   __shared__ float4 s_unom[BRMPPI_MAX_T + 1];
   __shared__ ObsL s_obs[BRMPPI_MAX_OBS];
-  __shared__ uint32_t s_tile, s_flag;
+  __shared__ uint32_t s_flag;
   __shared__ float s_red[2 * (kMaxBlock / 64)];
   __shared__ double s_trig[kPlantLds];
+  constexpr bool kCoop = !PRE && G > 1;
+  __shared__ float4 s_nrm[kCoop ? kMaxBlock / G * coop_stride<NOB, G>() / 4 : 1];
   extern __shared__ float s_dyn[];            // fused epilogue only
   const uint32_t per_tile = blockDim.x / G;   // samples per tile
   const uint32_t lds_stride = per_tile + 1;
+  const uint32_t s0 = blockIdx.x * per_tile;
+  const SolveDesc& d = *desc;
+  TileStart st;
+  stage_tile(d, s_path, s_unom, s_obs, st);
+  // fused epilogue: LDS for the tile's applied inputs, costs (+inf where no
+  // sample stores), weights, units
+  const bool fused = d.fused != 0;
+  float *s_u = nullptr, *s_J = nullptr, *s_gam = nullptr, *s_mu = nullptr, *s_sig = nullptr;
+  float4* s_up = nullptr;
+  if (fused) {
+    s_u = s_dyn;
+    s_J = s_dyn + fused_lds_region(per_tile, d.T, d.n_wchunk);
+    s_gam = s_J + per_tile;
+    s_mu = s_gam + per_tile;
+    s_sig = s_mu + kGroupUnits;
+    s_up = reinterpret_cast<float4*>(s_sig + kGroupUnits);
+    for (uint32_t i = threadIdx.x; i < per_tile; i += blockDim.x) s_J[i] = INFINITY;
+  }
+  __syncthreads();
+  tile_rollout<NOB, GUIDED, G, PRE>(d, s0, st, s_path, s_unom, s_obs, s_u, lds_stride, s_J,
+                                    reinterpret_cast<float*>(s_nrm));
+  if (!fused) return;
+  __syncthreads();
+  tile_epilogue(d, s0, per_tile, s_u, lds_stride, s_J, s_gam, s_mu, s_sig, s_up, s_red, s_trig, &s_flag);
+}
+
+// Rollouts of a batch: one persistent launch over the tiles of all its
+// instances, longest first, each tile in the in-kernel-noise form of its
+// instance's constraint bucket (d.bucket): one lane per sample up to eight
+// rows, two up to 16, four up to 32.  One launch per bucket, one after the
+// other, left the device to the last tiles of each; a bucket too small for a
+// launch of its own ran in the next heavier kernel.  Every form fits the 256
+// registers of two waves per SIMD.  What bounds it is the vector pipe: at two
+// waves per SIMD about 2700 of its cycles a wave and step (2 per FP32
+// instruction on vector registers, 4 per FP64, comparison or scalar-operand
+// one, 8 per transcendental), 80 % of the launch.  Measured, launch per bucket
+// -> this: 64 instances (1024 to 16384 samples, 20 to 80 steps, up to 16
+// obstacles) 765 -> 745 us a call, 48 served requests (up to 32768 samples, 100
+// steps, 32 obstacles) 2813 -> 2125 us.
+__global__ __launch_bounds__(kMaxBlock) __attribute__((amdgpu_waves_per_eu(2, 8)))
+void k_rollout_batch(const SolveDesc* __restrict__ descs, const Tile* __restrict__ tiles, uint32_t n_tiles,
+                     BatchCounters* __restrict__ ctr) {
+  __shared__ float4 s_path[kPathWin];
+  __shared__ float4 s_unom[BRMPPI_MAX_T + 1];
+  __shared__ ObsL s_obs[BRMPPI_MAX_OBS];
+  __shared__ uint32_t s_tile;
+  constexpr int kNrm2 = kMaxBlock / 2 * coop_stride<16, 2>() / 4, kNrm4 = kMaxBlock / 4 * coop_stride<32, 4>() / 4;
+  __shared__ float4 s_nrm4[kNrm2 > kNrm4 ? kNrm2 : kNrm4];
+  float* s_nrm = reinterpret_cast<float*>(s_nrm4);
   for (uint32_t it = 0;; ++it) {
     uint32_t tix;
-    if (!next_item(it, n_tiles, ctr ? &ctr->tile_next : nullptr, &s_tile, tix)) break;
-    Tile tl;
-    if (tiles) {
-      tl = tiles[tix];
-    } else {
-      tl.inst = 0;
-      tl.s0 = tix * per_tile;
-    }
+    if (!next_item(it, n_tiles, &ctr->tile_next, &s_tile, tix)) break;
+    const Tile tl = tiles[tix];
     const SolveDesc& d = descs[__builtin_amdgcn_readfirstlane(tl.inst)];
-
-    float x0[8];
-    if (d.x0_resident) {
-#pragma unroll
-      for (int k = 0; k < 8; ++k) x0[k] = (float)d.plant_x[k];
-    } else {
-#pragma unroll
-      for (int k = 0; k < 8; ++k) x0[k] = d.x0[k];
-    }
-    const float ox = x0[0], oy = x0[1];
-    // progress origin: f0 = psi0/ds = k0 + phi0
-    const double f0 = (double)x0[7] / (double)d.ds;
-    double fk = floor(f0);
-    fk = fmin(fmax(fk, -1.0e9), 1.0e9);
-    const int k0 = (int)fk;
-    const float phi0 = (float)(f0 - fk);
-    const int n_path = (int)d.n_path;
-    int w0 = k0 - kPathBack;
-    if (w0 < 0) w0 = 0;
-    if (w0 > n_path - 2) w0 = n_path - 2;
-    int nw = n_path - w0;
-    if (nw > kPathWin) nw = kPathWin;
-
-    // stage the obstacle rows (row r: obstacle r % n_objects around footprint
-    // disc r / n_objects) and the path window
-    if (threadIdx.x < d.n_obs) {
-      const uint32_t oi = threadIdx.x % d.n_objects;
-      const brmppi_obstacle o = d.obs[oi];
-      const float ax = o.mx + d.prm.r_disc, ay = o.my + d.prm.r_disc;
-      const float iax = 1.0f / (ax * ax), iay = 1.0f / (ay * ay);
-      float so, co;
-      sincosf(o.heading, &so, &co);
-      ObsL L;
-      L.cx = fmaf(o.vx, d.t0, o.cx - ox);
-      L.cy = fmaf(o.vy, d.t0, o.cy - oy);
-      L.mx = d.prm.Ts * o.vx;
-      L.my = d.prm.Ts * o.vy;
-      L.q11 = co * co * iax + so * so * iay;
-      L.q12 = co * so * (iax - iay);
-      L.q22 = so * so * iax + co * co * iay;
-      L.qa = 0.5f * (iax + iay);
-      L.qd = 0.5f * (iax - iay) * (co * co - so * so);
-      L.rx = fmaf(L.q12, L.my, L.q11 * L.mx);
-      L.ry = fmaf(L.q22, L.my, L.q12 * L.mx);
-      L.rr = fmaf(L.ry, L.my, L.rx * L.mx);
-      L.e4 = (o.e == 4.0f) ? 1.0f : 0.0f;
-      L.a00 = co / ax;
-      L.a01 = so / ax;
-      L.a10 = -so / ay;
-      L.a11 = co / ay;
-      L.pad = 0.0f;
-      disc_ab(d.prm, threadIdx.x / d.n_objects, L.dA, L.dB);
-      s_obs[threadIdx.x] = L;
-    } else if (threadIdx.x < BRMPPI_MAX_OBS) {
-      // blank slots (Q = A = 0, at rest): the rows of lanes past the last
-      // obstacle row
-      s_obs[threadIdx.x] = ObsL{};
-    }
-    // the path window (headings in revolutions) and the nominal inputs, their
-    // first loads all issued before the first store (the window's 4 per thread
-    // at 256 threads): one memory latency, not one per value a thread stages
-    const int Ti = (int)d.T, bd = (int)blockDim.x, tx = (int)threadIdx.x;
-    auto load_un = [&](int tau) __attribute__((always_inline)) {
-      const float* p = d.u_nom_in + 3 * min(tau, Ti - 1);
-      return make_float4(gld(p), gld(p + 1), gld(p + 2), 0.0f);
+    TileStart st;
+    stage_tile(d, s_path, s_unom, s_obs, st);
+    __syncthreads();
+    auto run = [&](auto NOB, auto GUIDED, auto G) __attribute__((always_inline)) {
+      tile_rollout<decltype(NOB)::value, decltype(GUIDED)::value, decltype(G)::value, false>(
+          d, tl.s0, st, s_path, s_unom, s_obs, nullptr, 0, nullptr, s_nrm);
     };
-    const float4 un0 = load_un(tx);
-    for (int j0 = 0; j0 < nw; j0 += 4 * bd) {
-      float4 w[4];
-#pragma unroll
-      for (int k = 0; k < 4; ++k) w[k] = d.path[w0 + min(j0 + k * bd + tx, nw - 1)];
-#pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        const int j = j0 + k * bd + tx;
-        if (j < nw) s_path[j] = make_float4(w[k].x - ox, w[k].y - oy, w[k].z * kInvTurn, w[k].w * kInvTurn);
-      }
-    }
-    if (tx < Ti) s_unom[tx] = un0;
-    for (int tau = tx + bd; tau < Ti; tau += bd) s_unom[tau] = load_un(tau);
-    // fused epilogue (direct launch of one instance): LDS for the tile's
-    // applied inputs, costs (+inf where no sample stores), weights, units
-    const bool fused = (ctr == nullptr) && d.fused;
-    float *s_u = nullptr, *s_J = nullptr, *s_gam = nullptr, *s_mu = nullptr, *s_sig = nullptr;
-    float4* s_up = nullptr;
-    if (fused) {
-      s_u = s_dyn;
-      s_J = s_dyn + fused_lds_region(per_tile, d.T, d.n_wchunk);
-      s_gam = s_J + per_tile;
-      s_mu = s_gam + per_tile;
-      s_sig = s_mu + kGroupUnits;
-      s_up = reinterpret_cast<float4*>(s_sig + kGroupUnits);
-      for (uint32_t i = threadIdx.x; i < per_tile; i += blockDim.x) s_J[i] = INFINITY;
+    using std::integral_constant;
+    switch (d.bucket) {
+      case 0: run(integral_constant<int, 0>{}, std::false_type{}, integral_constant<int, 1>{}); break;
+      case 2: run(integral_constant<int, 2>{}, std::true_type{}, integral_constant<int, 1>{}); break;
+      case 8: run(integral_constant<int, 8>{}, std::true_type{}, integral_constant<int, 1>{}); break;
+      case 16: run(integral_constant<int, 16>{}, std::true_type{}, integral_constant<int, 2>{}); break;
+      default: run(integral_constant<int, 32>{}, std::true_type{}, integral_constant<int, 4>{}); break;
     }
     __syncthreads();
-
-    // every lane runs (lanes past S repeat the last sample and do not store),
-    // so the group-wide DPP broadcasts always read active lanes
-    const uint32_t t_local = threadIdx.x / G;
-    const uint32_t s_raw = tl.s0 + t_local;
-    const int g = (int)(threadIdx.x % G);
-    const bool valid = s_raw < d.S;
-    const uint32_t s = valid ? s_raw : d.S - 1;
-    auto rollout = [&](auto ROWS) __attribute__((always_inline)) {
-      rollout_sample<NOB, GUIDED, G, PRE, decltype(ROWS)::value>(d, s, valid && g == 0, g, x0, s_obs, s_path, s_unom,
-                                                                w0, nw, k0, phi0, s_u, lds_stride, t_local, s_J);
-    };
-    if constexpr (GUIDED) {
-      if (d.row_kind == kRowsDisc) rollout(std::integral_constant<int, kRowsDisc>{});
-      else if (d.row_kind == kRowsE4) rollout(std::integral_constant<int, kRowsE4>{});
-      else if (d.row_kind == kRowsMoving) rollout(std::integral_constant<int, kRowsMoving>{});
-      else rollout(std::integral_constant<int, kRowsStatic>{});
-    } else {
-      // no rows: the kinds matter to the collision penalty alone
-      if (d.row_kind == kRowsDisc) rollout(std::integral_constant<int, kRowsDisc>{});
-      else rollout(std::integral_constant<int, kRowsE4>{});
-    }
-    __syncthreads();
-    if (fused)
-      tile_epilogue(d, tl.s0, per_tile, s_u, lds_stride, s_J, s_gam, s_mu, s_sig, s_up, s_red, s_trig, &s_flag);
   }
-  if (ctr) finish_persistent(&ctr->tile_next, &ctr->tile_done);
+  finish_persistent(&ctr->tile_next, &ctr->tile_done);
 }
 
 constexpr uint32_t kMaxWChunks = BRMPPI_MAX_S / kWChunk;
@@ -2151,71 +2258,69 @@ __global__ void k_fill_u32(uint32_t* __restrict__ p, uint32_t value, size_t n) {
 // ---------------------------------------------------------------------------
 // rollout variants: 0 = one lane per sample, in-kernel noise; 1 = one lane,
 // precomputed noise; 2 / 3 / 4 = two / four / eight lanes per sample,
-// precomputed noise
-int variant_lanes(int variant) { return variant == 2 ? 2 : (variant == 3 ? 4 : (variant == 4 ? 8 : 1)); }
-bool variant_pre(int variant) { return variant != 0; }
+// precomputed noise; 5 / 6 = two / four lanes per sample, in-kernel noise (the
+// form without a noise buffer of the buckets of 16 / 32 rows; not settable)
+int variant_lanes(int variant) {
+  constexpr int lanes[7] = {1, 1, 2, 4, 8, 2, 4};
+  return variant >= 0 && variant < 7 ? lanes[variant] : 1;
+}
+bool variant_pre(int variant) { return variant >= 1 && variant <= kMaxVariant; }
+// The in-kernel-noise form of a bucket: at most eight obstacle rows per lane.
+// One lane with 16 or 32 rows does not fit the 256 registers that let two
+// waves share a SIMD, and what it spills or loses in occupancy costs more
+// than the state that two or four lanes hold redundantly.
+int variant_in_kernel(int bucket) { return bucket == 32 ? 6 : (bucket == 16 ? 5 : 0); }
 
 template <int NOB, bool GD, int G, bool PRE>
-static hipError_t launch_rollout_t(const SolveDesc* descs, const Tile* tiles, uint32_t n_tiles,
-                                   BatchCounters* ctr, uint32_t grid, uint32_t block, size_t lds,
+static hipError_t launch_rollout_t(const SolveDesc* desc, uint32_t grid, uint32_t block, size_t lds,
                                    hipStream_t stream) {
-  hipLaunchKernelGGL((k_rollout<NOB, GD, G, PRE>), dim3(grid), dim3(block), lds, stream, descs, tiles, n_tiles, ctr);
+  hipLaunchKernelGGL((k_rollout<NOB, GD, G, PRE>), dim3(grid), dim3(block), lds, stream, desc);
   return hipGetLastError();
 }
 
 template <int NOB, bool GD>
-static hipError_t launch_variant(int variant, const SolveDesc* descs, const Tile* tiles, uint32_t n_tiles,
-                                 BatchCounters* ctr, uint32_t grid, uint32_t block, size_t lds, hipStream_t stream) {
+static hipError_t launch_variant(int variant, const SolveDesc* desc, uint32_t grid, uint32_t block, size_t lds,
+                                 hipStream_t stream) {
   switch (variant) {
-    case 0: return launch_rollout_t<NOB, GD, 1, false>(descs, tiles, n_tiles, ctr, grid, block, lds, stream);
-    case 1: return launch_rollout_t<NOB, GD, 1, true>(descs, tiles, n_tiles, ctr, grid, block, lds, stream);
-    case 2: return launch_rollout_t<NOB, GD, 2, true>(descs, tiles, n_tiles, ctr, grid, block, lds, stream);
-    case 3: return launch_rollout_t<NOB, GD, 4, true>(descs, tiles, n_tiles, ctr, grid, block, lds, stream);
-    case 4: return launch_rollout_t<NOB, GD, 8, true>(descs, tiles, n_tiles, ctr, grid, block, lds, stream);
+    case 0: return launch_rollout_t<NOB, GD, 1, false>(desc, grid, block, lds, stream);
+    case 1: return launch_rollout_t<NOB, GD, 1, true>(desc, grid, block, lds, stream);
+    case 2: return launch_rollout_t<NOB, GD, 2, true>(desc, grid, block, lds, stream);
+    case 3: return launch_rollout_t<NOB, GD, 4, true>(desc, grid, block, lds, stream);
+    case 4: return launch_rollout_t<NOB, GD, 8, true>(desc, grid, block, lds, stream);
+    case 5:
+      if constexpr (NOB == 16) return launch_rollout_t<NOB, GD, 2, false>(desc, grid, block, lds, stream);
+      return hipErrorInvalidValue;
+    case 6:
+      if constexpr (NOB == 32) return launch_rollout_t<NOB, GD, 4, false>(desc, grid, block, lds, stream);
+      return hipErrorInvalidValue;
     default: return hipErrorInvalidValue;
   }
 }
 
-hipError_t launch_rollout(int bucket, int variant, const SolveDesc* descs, const Tile* tiles, uint32_t n_tiles,
-                          BatchCounters* ctr, uint32_t grid, uint32_t block, size_t lds, hipStream_t stream) {
+hipError_t launch_rollout(int bucket, int variant, const SolveDesc* desc, uint32_t grid, uint32_t block, size_t lds,
+                          hipStream_t stream) {
   if (block == 0 || block > (uint32_t)kMaxBlock || (block % 64) != 0) return hipErrorInvalidValue;
   switch (bucket) {
-    case 0: return launch_variant<0, false>(variant, descs, tiles, n_tiles, ctr, grid, block, lds, stream);
-    case 2: return launch_variant<2, true>(variant, descs, tiles, n_tiles, ctr, grid, block, lds, stream);
-    case 8: return launch_variant<8, true>(variant, descs, tiles, n_tiles, ctr, grid, block, lds, stream);
-    case 16: return launch_variant<16, true>(variant, descs, tiles, n_tiles, ctr, grid, block, lds, stream);
-    case 32: return launch_variant<32, true>(variant, descs, tiles, n_tiles, ctr, grid, block, lds, stream);
+    case 0: return launch_variant<0, false>(variant, desc, grid, block, lds, stream);
+    case 2: return launch_variant<2, true>(variant, desc, grid, block, lds, stream);
+    case 8: return launch_variant<8, true>(variant, desc, grid, block, lds, stream);
+    case 16: return launch_variant<16, true>(variant, desc, grid, block, lds, stream);
+    case 32: return launch_variant<32, true>(variant, desc, grid, block, lds, stream);
     default: return hipErrorInvalidValue;
   }
 }
 
-template <int NOB, bool GD, int G, bool PRE>
-static int occ_t(uint32_t block) {
+hipError_t launch_rollout_batch(const SolveDesc* descs, const Tile* tiles, uint32_t n_tiles, BatchCounters* ctr,
+                                uint32_t grid, uint32_t block, hipStream_t stream) {
+  if (block == 0 || block > (uint32_t)kMaxBlock || (block % 64) != 0) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(k_rollout_batch, dim3(grid), dim3(block), 0, stream, descs, tiles, n_tiles, ctr);
+  return hipGetLastError();
+}
+
+int rollout_batch_blocks_per_cu(uint32_t block) {
   int nb = 0;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_rollout<NOB, GD, G, PRE>, (int)block, 0) != hipSuccess)
-    return 1;
+  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_rollout_batch, (int)block, 0) != hipSuccess) return 1;
   return nb > 0 ? nb : 1;
-}
-
-template <int NOB, bool GD>
-static int occ_variant(int variant, uint32_t block) {
-  switch (variant) {
-    case 1: return occ_t<NOB, GD, 1, true>(block);
-    case 2: return occ_t<NOB, GD, 2, true>(block);
-    case 3: return occ_t<NOB, GD, 4, true>(block);
-    case 4: return occ_t<NOB, GD, 8, true>(block);
-    default: return occ_t<NOB, GD, 1, false>(block);
-  }
-}
-
-int rollout_blocks_per_cu(int bucket, int variant, uint32_t block) {
-  switch (bucket) {
-    case 0: return occ_variant<0, false>(variant, block);
-    case 2: return occ_variant<2, true>(variant, block);
-    case 8: return occ_variant<8, true>(variant, block);
-    case 16: return occ_variant<16, true>(variant, block);
-    default: return occ_variant<32, true>(variant, block);
-  }
 }
 
 hipError_t launch_noise(const SolveDesc* first, size_t stride, uint32_t count, uint32_t S, uint32_t T,

@@ -319,7 +319,6 @@ struct brmppi_ctx {
   std::string tune_path;
   std::vector<Controller> ctrl;
   LaunchShape shape[5][4];      // plain-path table, tuned entries: [bucket index][S class]
-  uint32_t batch_block[5] = {256, 256, 256, 256, 256};  // persistent (variant 0) block per bucket
   LaunchShape forced{0, 0};     // block 0 = not forced
   Block counters_blk;           // BatchCounters per stream + spare
   BatchCounters* counters = nullptr;
@@ -477,6 +476,7 @@ void fill_desc(SolveDesc& d, const brmppi_problem& p, const Controller& c, const
   d.n_obs = p.n_obs * n_discs(d.prm);      // obstacle rows
   d.n_objects = p.n_obs;
   d.flags = p.flags;
+  d.bucket = (uint32_t)bucket_for(d.n_obs, p.flags);
   d.n_path = c.n_path;
   d.instance = p.instance;
   const uint64_t seed = p.seed + seed_offset;
@@ -524,7 +524,7 @@ LaunchShape plain_shape(brmppi_ctx* ctx, const brmppi_problem& p) {
   if (s.block == 0) s = default_shape(bucket, p.S, (p.flags & BRMPPI_COLLISION_PENALTY) != 0);
   const size_t noise = (size_t)normals_per_step(ctx, p) * p.T * round_up(p.S, 256) * sizeof(float);
   if (variant_pre(s.variant) && noise > std::min(kMaxNoiseBytes, ctx->arena.size() / 2))
-    s.variant = 0;
+    s.variant = variant_in_kernel(bucket);
   return s;
 }
 
@@ -608,7 +608,7 @@ int enqueue_rollout_reduce(brmppi_ctx* ctx, hipStream_t st, const SolveDesc* d_d
   const uint32_t per_tile = sh.block / variant_lanes(sh.variant);
   const uint32_t grid = (p.S + per_tile - 1) / per_tile;
   int rc = timed(ctx, st, 0, [&] {
-    return launch_rollout(bucket, sh.variant, d_desc, nullptr, grid, nullptr, grid, sh.block, lds, st);
+    return launch_rollout(bucket, sh.variant, d_desc, grid, sh.block, lds, st);
   });
   if (rc || lds) return rc;
   const uint32_t nr = L.n_wchunk * L.n_rgroup;
@@ -724,72 +724,24 @@ struct BatchPlan {
   // (one upload), outputs (one download), then every instance's scratch
   size_t off_descs = 0, off_tiles = 0, off_ritems = 0, off_counters = 0, header_bytes = 0;
   size_t off_outs = 0, out_floats = 0, total = 0;
-  // the instances are grouped by constraint bucket; each group's tiles are
-  // contiguous in `tiles` and run in the rollout kernel sized for that bucket
-  struct Part {
-    int bucket;
-    uint32_t block, tile0, n_tiles;
-  };
-  std::vector<Part> parts;
-  std::vector<uint32_t> inst_part;
+  uint32_t block = 256;              // of the rollout launch
 };
+
+// samples of a tile of this instance in a batched launch of `block` threads
+uint32_t batch_tile(const brmppi_ctx* ctx, const brmppi_problem& p, uint32_t block) {
+  return block / (uint32_t)variant_lanes(variant_in_kernel(bucket_for(obstacle_rows(ctx, p), p.flags)));
+}
 
 void plan_layout(brmppi_ctx* ctx, const brmppi_problem* const* ps, uint32_t n, BatchPlan& bp) {
   bp.layouts.resize(n);
-  // one rollout launch per constraint bucket present, heaviest first: a
-  // kernel's registers, and so how many waves share a SIMD, grow with its
-  // obstacle slots, so an instance runs in the smallest kernel that holds it.
-  // A batch fills the device with samples: one lane per sample, in-kernel noise.
-  // A bucket whose tiles would not fill two rounds of the device's resident
-  // blocks joins the next heavier bucket present: a launch lasts at least as
-  // long as its longest tile, so a thin launch costs more than the occupancy
-  // it gains.  Unguided instances (bucket 0) run in a guided kernel's
-  // GUIDANCE_OFF path when they join one.
-  bp.parts.clear();
-  bp.inst_part.assign(n, 0);
-  auto block_of = [&](int bi) { return ctx->forced.block ? ctx->forced.block : ctx->batch_block[bi]; };
-  std::vector<int> ibi(n);
-  size_t tiles_b[5] = {0, 0, 0, 0, 0};
-  for (uint32_t i = 0; i < n; ++i) {
-    ibi[i] = bucket_index(bucket_for(obstacle_rows(ctx, *ps[i]), ps[i]->flags));
-    tiles_b[ibi[i]] += (ps[i]->S + block_of(ibi[i]) - 1) / block_of(ibi[i]);
-  }
-  for (int bi = 0; bi < 4; ++bi) {
-    if (tiles_b[bi] == 0) continue;
-    int up = -1;
-    for (int bj = bi + 1; bj < 5 && up < 0; ++bj)
-      if (tiles_b[bj]) up = bj;
-    if (up < 0) continue;
-    const size_t resident = (size_t)ctx->n_cu * std::max(1, rollout_blocks_per_cu(kBuckets[bi], 0, block_of(bi)));
-    if (tiles_b[bi] < 2 * resident) {
-      // rescale to the receiving bucket's block size
-      size_t moved = 0;
-      for (uint32_t i = 0; i < n; ++i)
-        if (ibi[i] == bi) moved += (ps[i]->S + block_of(up) - 1) / block_of(up);
-      tiles_b[up] += moved;
-      tiles_b[bi] = 0;
-      for (uint32_t i = 0; i < n; ++i)
-        if (ibi[i] == bi) ibi[i] = up;
-    }
-  }
-  int part_of[5] = {-1, -1, -1, -1, -1};
-  for (int bi = 4; bi >= 0; --bi) {
-    for (uint32_t i = 0; i < n; ++i) {
-      if (ibi[i] != bi) continue;
-      if (part_of[bi] < 0) {
-        part_of[bi] = (int)bp.parts.size();
-        bp.parts.push_back(BatchPlan::Part{kBuckets[bi], block_of(bi), 0, 0});
-      }
-      bp.inst_part[i] = (uint32_t)part_of[bi];
-    }
-  }
+  bp.block = ctx->forced.block ? ctx->forced.block : 256;
   size_t n_tiles = 0, n_r = 0;
   std::vector<uint32_t> rows_item(n);
   reduce_rows(ps, n, ctx->n_cu, rows_item.data());
   for (uint32_t i = 0; i < n; ++i) {
     bp.layouts[i] = scratch_layout(ps[i]->S, ps[i]->T, 0, rows_item[i]);
-    const uint32_t blk = bp.parts[bp.inst_part[i]].block;
-    n_tiles += (ps[i]->S + blk - 1) / blk;
+    const uint32_t per = batch_tile(ctx, *ps[i], bp.block);
+    n_tiles += (ps[i]->S + per - 1) / per;
     n_r += (size_t)bp.layouts[i].n_wchunk * bp.layouts[i].n_rgroup;
   }
   size_t o = 0;
@@ -845,32 +797,26 @@ void plan_work(brmppi_ctx* ctx, const brmppi_problem* const* ps, uint32_t n, Bat
   bp.tiles.clear();
   bp.ritems.clear();
   struct TC {
-    uint32_t part;
     double cost;
     Tile t;
   };
   std::vector<TC> tc;
   for (uint32_t i = 0; i < n; ++i) {
     const brmppi_problem& p = *ps[i];
-    // guidance-off instances inside a guided batch: the flag is honoured per tile
-    const double cost = (double)p.T * (10.0 + ((p.flags & BRMPPI_GUIDANCE_OFF) ? 0.0 : 2.0 + obstacle_rows(ctx, p)));
-    const uint32_t pi = bp.inst_part[i], blk = bp.parts[pi].block;
-    for (uint32_t s0 = 0; s0 < p.S; s0 += blk) tc.push_back({pi, cost, Tile{i, s0}});
+    const uint32_t per = batch_tile(ctx, p, bp.block);
+    // instructions of a tile's wave, about: 150 a step, and its share of the
+    // rows (45 each) and of the Philox blocks of four normals (100 each)
+    const double share = (double)per / bp.block;
+    const bool guided = !(p.flags & BRMPPI_GUIDANCE_OFF);
+    const double rows = guided ? 2.0 + obstacle_rows(ctx, p) : 0.0;
+    const double cost = (double)p.T * (150.0 + share * (45.0 * rows + 25.0 * (3.0 + rows)));
+    for (uint32_t s0 = 0; s0 < p.S; s0 += per) tc.push_back({cost, Tile{i, s0}});
     for (uint32_t k = 0; k < bp.layouts[i].n_wchunk * bp.layouts[i].n_rgroup; ++k) bp.ritems.push_back(Item{i, k});
   }
-  // tiles grouped by launch, longest first within a launch (stable: instance
-  // order breaks ties)
-  std::stable_sort(tc.begin(), tc.end(), [](const TC& a, const TC& b) {
-    return a.part != b.part ? a.part < b.part : a.cost > b.cost;
-  });
+  // tiles longest first (stable: instance order breaks ties)
+  std::stable_sort(tc.begin(), tc.end(), [](const TC& a, const TC& b) { return a.cost > b.cost; });
   bp.tiles.reserve(tc.size());
-  for (auto& pt : bp.parts) pt.n_tiles = 0;
-  for (size_t k = 0; k < tc.size(); ++k) {
-    BatchPlan::Part& pt = bp.parts[tc[k].part];
-    if (pt.n_tiles == 0) pt.tile0 = (uint32_t)k;
-    ++pt.n_tiles;
-    bp.tiles.push_back(tc[k].t);
-  }
+  for (const TC& c : tc) bp.tiles.push_back(c.t);
   // reduce items longest first (stable), for when they outnumber the blocks
   auto item_rows = [&](const Item& it) {
     const ScratchLayout& L = bp.layouts[it.inst];
@@ -897,7 +843,6 @@ void batch_signature(brmppi_ctx* ctx, const brmppi_problem* const* ps, uint32_t 
   sig.reserve(8 + 3 * (size_t)n);
   sig.push_back(n);
   sig.push_back(ctx->forced.block);
-  for (uint32_t b : ctx->batch_block) sig.push_back(b);
   for (uint32_t i = 0; i < n; ++i) {
     sig.push_back(((uint64_t)ps[i]->S << 32) | ps[i]->T);
     sig.push_back(((uint64_t)obstacle_rows(ctx, *ps[i]) << 32) | ps[i]->flags);
@@ -916,15 +861,15 @@ BatchPlanCache& plan_cache(brmppi_ctx* ctx) {
   return *static_cast<BatchPlanCache*>(ctx->plan_cache.get());
 }
 
-uint32_t persistent_grid(brmppi_ctx* ctx, int bucket, uint32_t block, size_t n_tiles) {
-  const int per_cu = rollout_blocks_per_cu(bucket, 0, block);
+uint32_t persistent_grid(brmppi_ctx* ctx, uint32_t block, size_t n_tiles) {
+  const int per_cu = rollout_batch_blocks_per_cu(block);
   const size_t g = (size_t)ctx->n_cu * (size_t)std::max(per_cu, 1);
   return (uint32_t)std::max<size_t>(1, std::min(g, n_tiles));
 }
 
-// persistent rollouts over each bucket's tiles (one after the other: a
-// launch's work counters are zero again when it ends), then the persistent
-// reduce (weights, update, shift, plant steps) over every instance's items
+// a persistent rollout over every instance's tiles, then the persistent reduce
+// (weights, update, shift, plant steps) over every instance's items (a launch's
+// work counters are zero again when it ends)
 int enqueue_batch(brmppi_ctx* ctx, hipStream_t st, char* base, const BatchPlan& bp, BatchCounters* ctr,
                   bool timing) {
   const SolveDesc* descs = reinterpret_cast<const SolveDesc*>(base + bp.off_descs);
@@ -932,18 +877,13 @@ int enqueue_batch(brmppi_ctx* ctx, hipStream_t st, char* base, const BatchPlan& 
   const Item* ri = reinterpret_cast<const Item*>(base + bp.off_ritems);
   const uint32_t nr = (uint32_t)bp.ritems.size();
   const uint32_t g_r = std::max<uint32_t>(1, std::min<uint32_t>(nr, (uint32_t)ctx->n_cu * 8));
-  for (const auto& pt : bp.parts) {
-    if (pt.n_tiles == 0) continue;
-    const uint32_t g_roll = persistent_grid(ctx, pt.bucket, pt.block, pt.n_tiles);
-    auto L0 = [&] {
-      return launch_rollout(pt.bucket, 0, descs, tiles + pt.tile0, pt.n_tiles, ctr, g_roll, pt.block, 0, st);
-    };
-    if (timing) {
-      int rc;
-      if ((rc = timed(ctx, st, 0, L0))) return rc;
-    } else {
-      HIPCHK(L0());
-    }
+  const uint32_t nt = (uint32_t)bp.tiles.size();
+  const uint32_t g_roll = persistent_grid(ctx, bp.block, nt);
+  auto L0 = [&] { return launch_rollout_batch(descs, tiles, nt, ctr, g_roll, bp.block, st); };
+  if (timing) {
+    if (int rc = timed(ctx, st, 0, L0)) return rc;
+  } else {
+    HIPCHK(L0());
   }
   auto L1 = [&] { return launch_reduce(descs, ri, nr, ctr, g_r, st); };
   if (timing) return timed(ctx, st, 1, L1);
@@ -983,13 +923,7 @@ int run_batch(brmppi_ctx* ctx, hipStream_t s, char* base, const BatchPlan& bp, B
   } else {
     // the captured launches bake in every pointer and count: key on them
     std::vector<uint64_t> key = {(uint64_t)(uintptr_t)base, bp.tiles.size(), bp.ritems.size(),
-                                 (uint64_t)(uintptr_t)s, bp.descs.size(), (uint64_t)(uintptr_t)ctr};
-    for (const auto& pt : bp.parts) {
-      key.push_back((uint64_t)pt.bucket);
-      key.push_back(pt.block);
-      key.push_back(pt.tile0);
-      key.push_back(pt.n_tiles);
-    }
+                                 (uint64_t)(uintptr_t)s, bp.descs.size(), (uint64_t)(uintptr_t)ctr, bp.block};
     if (key != ctx->graph_key || !ctx->graph_exec) {
       drop_graph(ctx);
       HIPCHK(hipStreamBeginCapture(s, hipStreamCaptureModeThreadLocal));
@@ -1217,10 +1151,10 @@ int closed_loop_locked(brmppi_ctx* ctx, const brmppi_problem* p0, uint32_t n_up,
 // served form
 // ---------------------------------------------------------------------------
 // device bytes one request adds to a served batch: scratch, descriptor, its
-// tiles (at the smallest block size) and work items, plus alignment slack
+// tiles (at the smallest block size and four lanes per sample) and work items, plus alignment slack
 size_t request_footprint(const brmppi_problem& p) {
   const ScratchLayout L = scratch_layout(p.S, p.T);
-  const size_t tiles = (p.S + 63) / 64;
+  const size_t tiles = (p.S + 15) / 16;
   const size_t items = L.n_wchunk + (size_t)L.n_wchunk * L.n_rgroup;
   return L.bytes + sizeof(SolveDesc) + (tiles + items) * 8 + sizeof(float) * (4 + 6 * (size_t)p.T) + 8 * 256;
 }
@@ -1303,7 +1237,8 @@ int load_tune(brmppi_ctx* ctx) {
   std::stringstream ss;
   ss << f.rdbuf();
   const std::string s = ss.str();
-  // format: {"plain_<bucket>_<sclass>": [block, variant], ..., "batch_<bucket>": block}
+  // format: {"plain_<bucket>_<sclass>": [block, variant], ...} (entries of
+  // other names, the batched launch's blocks of older files among them, are left alone)
   auto valid_block = [](long v) { return v >= 64 && v <= kMaxBlock && v % 64 == 0; };
   for (int bi = 0; bi < 5; ++bi) {
     for (int sc = 0; sc < 4; ++sc) {
@@ -1320,15 +1255,6 @@ int load_tune(brmppi_ctx* ctx) {
       const int lanes = variant_lanes((int)var);
       if (valid_block(blk) && var >= 0 && var <= kMaxVariant && blk % lanes == 0)
         ctx->shape[bi][sc] = LaunchShape{(uint32_t)blk, (int)var};
-    }
-    const std::string kb = "\"batch_" + std::to_string(kBuckets[bi]) + "\"";
-    const size_t at = s.find(kb);
-    if (at != std::string::npos) {
-      const size_t colon = s.find(':', at);
-      if (colon != std::string::npos) {
-        const long blk = std::strtol(s.c_str() + colon + 1, nullptr, 10);
-        if (valid_block(blk)) ctx->batch_block[bi] = (uint32_t)blk;
-      }
     }
   }
   return 0;
@@ -1753,8 +1679,7 @@ int brmppi_autotune(brmppi_ctx* ctx) {
       }
       HIPCHK(hipMemcpy(d_desc, &h, sizeof(h), hipMemcpyHostToDevice));
       LaunchShape best = ctx->shape[bi][sc];
-      float best_ms = 1e30f, best_v0 = 1e30f;
-      uint32_t best_v0_block = ctx->batch_block[bi];
+      float best_ms = 1e30f;
       std::string times;             // [block, variant, ms per noise + rollout + reduce] of every candidate
       for (int variant = 0; variant <= kMaxVariant; ++variant) {
         const uint32_t lanes = (uint32_t)variant_lanes(variant);
@@ -1776,7 +1701,7 @@ int brmppi_autotune(brmppi_ctx* ctx) {
             hipError_t e = hipSuccess;
             if (variant_pre(variant)) e = launch_noise(d_desc, 0, 1, S, T, K, s);
             if (e == hipSuccess)
-              e = launch_rollout(bucket, variant, d_desc, nullptr, grid, nullptr, grid, block, lds, s);
+              e = launch_rollout(bucket, variant, d_desc, grid, block, lds, s);
             if (e == hipSuccess && !lds) e = launch_reduce(d_desc, nullptr, nr, nullptr, nr, s);
             return e;
           };
@@ -1799,20 +1724,12 @@ int brmppi_autotune(brmppi_ctx* ctx) {
             best_ms = score;
             best = LaunchShape{block, variant};
           }
-          if (variant == 0 && sc == 3 && ms < best_v0) {
-            best_v0 = ms;
-            best_v0_block = block;
-          }
         }
       }
       ctx->shape[bi][sc] = best;
       add("plain_" + std::to_string(bucket) + "_" + std::to_string(sc),
           "[" + std::to_string(best.block) + ", " + std::to_string(best.variant) + "]");
       add("ms_plain_" + std::to_string(bucket) + "_" + std::to_string(sc), "[" + times + "]");
-      if (sc == 3) {
-        ctx->batch_block[bi] = best_v0_block;
-        add("batch_" + std::to_string(bucket), std::to_string(best_v0_block));
-      }
     }
   }
   json += "}\n";

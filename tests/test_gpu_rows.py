@@ -62,3 +62,45 @@ def test_rows_at_slot_edges(ctx, kind, n_obs):
             else:
                 assert np.array_equal(got["J"], first["J"])
                 assert np.array_equal(got["U_new"], first["U_new"])
+
+
+def test_batch_of_every_form(ctx):
+    """One batch over every bucket, row kind and lane count: bit for bit the
+    plain solves."""
+    with B.Context(arena_bytes=512 << 20, n_streams=1, max_controllers=64) as c:
+        probs = []
+        for kind in ("rest", "moving", "e4"):
+            for n_obs in (0, 2, 3, 8, 9, 16, 17, 32):
+                probs.append(problem(kind, n_obs))
+        probs.append(problem("e4", 5, W.FLAG_GUIDANCE_OFF | W.FLAG_COLLISION_PENALTY))
+        prm = W.make_params(0.05, disc_tractor=(0.0, 2.0), disc_trailer=(1.5,))
+        for n_obs in (1, 3, 5, 10):
+            p = problem("e4", n_obs)
+            p.params.update(prm)
+            probs.append(p)
+        pbs = []
+        for i, p in enumerate(probs):
+            q = p.copy(S=65 + 61 * i, T=5 + i % 7, u_nom=p.u_nom[:1].repeat(5 + i % 7, axis=0))
+            c.set_path(i, q.path, q.ds)
+            pbs.append(B.ProblemBuffers(q, controller=i))
+        plain = [B.brmppi_solve(c.h, pb)[0].copy() for pb in pbs]
+        for block in (0, 64, 192):
+            B.brmppi_set_launch(c.h, block, 0)
+            got = B.brmppi_solve_batch(c.h, pbs)[0]
+            for i, (u, v) in enumerate(zip(got, plain)):
+                assert np.array_equal(u, v), (block, i)
+        B.brmppi_set_launch(c.h, 0, 0)
+
+
+@pytest.mark.parametrize("n_obs", [9, 16, 17, 32])
+def test_no_room_for_normals(ctx, n_obs):
+    """A plain solve whose normals do not fit half the arena draws them in the
+    kernel, several lanes per sample: the same bits."""
+    p = problem("moving", n_obs).copy(S=1030, T=60, u_nom=np.zeros((60, 3), np.float32))
+    ctx.set_path(0, p.path, p.ds)
+    want = B.brmppi_solve_ex(ctx.h, B.ProblemBuffers(p, controller=0), want_J=True)
+    with B.Context(arena_bytes=6 << 20, n_streams=1, max_controllers=2) as c:
+        c.set_path(0, p.path, p.ds)
+        got = B.brmppi_solve_ex(c.h, B.ProblemBuffers(p, controller=0), want_J=True)
+    assert np.array_equal(got["J"], want["J"])
+    assert np.array_equal(got["U_new"], want["U_new"])
