@@ -30,6 +30,8 @@ constexpr int kNoisePrefetch = 2;   // steps of normals loaded ahead of their us
 // super-ellipses, or a footprint other than the rear axle.
 enum RowKind : uint32_t { kRowsStatic = 0, kRowsMoving = 1, kRowsE4 = 2, kRowsDisc = 3 };
 
+constexpr int kLogRecord = 10;   // doubles of a closed-loop log record
+
 // Per-update descriptor read by every kernel (device memory).
 struct alignas(16) SolveDesc {
   brmppi_params prm;            // 35 floats
@@ -42,8 +44,10 @@ struct alignas(16) SolveDesc {
   uint32_t x0_resident, n_normals, fused, ustar_global;   // n_normals: 5 + n_obs (guided) or 3
   uint32_t n_units, row_kind, rows_item, pad3;     // row_kind: which rows the rollout's step forms
                                                    // (RowKind); rows_item: rows of one reduce work item
-  uint32_t n_objects, bucket, pad1, pad2;        // bucket: bucket_for(n_obs, flags); obstacles (row r: obstacle r % n_objects, disc
-                                                 // r / n_objects)
+  uint32_t n_objects, bucket;   // obstacles (row r: obstacle r % n_objects, disc r / n_objects);
+                                // bucket_for(n_obs, flags)
+  double* log;                  // closed loop: the update's log record (kLogRecord doubles: the plant
+                                // state after it, the three floats of the averaged first input), or NULL
   const float4* path;           // controller path (absolute coordinates)
   const float* u_nom_in;        // 3T nominal sequence read by the rollout
   float* u_nom_out;             // 3T warm-start slot of the controller (shift target)

@@ -1493,6 +1493,12 @@ __device__ __forceinline__ void plant_finish(const SolveDesc& d, const double* s
   xn[6] = x[6] + Ts * w;
   xn[7] = x[7] + Ts * nu;
   for (int k = 0; k < 8; ++k) d.plant_x[k] = xn[k];
+  // closed loop: the state after the update and the averaged first input
+  if (d.log) {
+    for (int k = 0; k < 8; ++k) d.log[k] = xn[k];
+    float* u = reinterpret_cast<float*>(d.log + 8);
+    for (int k = 0; k < 3; ++k) u[k] = (float)lds(s_plant + 14 + k);
+  }
 }
 
 // block-wide reductions in a fixed order (thread stride, wave butterfly, waves
@@ -1524,6 +1530,38 @@ __device__ __forceinline__ void block_sum2(float& a, float& b, float* s_red) {
   }
   a = ra;
   b = rb;
+}
+
+// One row of the result: the new nominal sequence, the log and plant step of its
+// first input, and the receding-horizon shift U_nom <- [U[1:], U[T-1]]
+__device__ __forceinline__ void put_result(const SolveDesc& d, uint32_t r, uint32_t R, float U, bool plant,
+                                           double* s_plant) {
+  gst(d.u_new + r, U);
+  if (plant && r < 3) lds_put(s_plant + 14 + r, (double)U);
+  if (r >= 3) gst(d.u_nom_out + r - 3, U);
+  if (r + 3 >= R) gst(d.u_nom_out + r, U);
+}
+// every cost non-finite: return the nominal sequence, keep the warm start
+__device__ __forceinline__ void put_nominal(const SolveDesc& d, uint32_t R, bool plant, double* s_plant) {
+  for (uint32_t r = threadIdx.x; r < R; r += blockDim.x) {
+    const float U = gld(d.u_nom_in + r);
+    gst(d.u_new + r, U);
+    if (plant && r < 3) lds_put(s_plant + 14 + r, (double)U);
+  }
+}
+// statistics, plant step and its logs
+__device__ __forceinline__ void finish_instance(const SolveDesc& d, float m, float Z, float Z2, bool ok, bool plant,
+                                                double* s_plant) {
+  if (threadIdx.x == 0) {
+    d.stats[0] = m;
+    d.stats[1] = Z;
+    d.stats[2] = ok ? Z * Z / Z2 : 0.0f;
+    d.stats[3] = ok ? (float)BRMPPI_OK : (float)BRMPPI_ENONFINITE;
+  }
+  if (plant) {
+    __syncthreads();                 // U_new[0] from threads 0..2, the state and sines
+    if (threadIdx.x == 0) plant_finish(d, s_plant);
+  }
 }
 
 // Merge of the group partials (a group = 1024 samples) by the last block of an
@@ -1583,31 +1621,12 @@ __device__ void finalize_instance(const SolveDesc& d, float* s_scale, float* s_r
           acc += lds(s_scale + c + k) * vk;
         }
       }
-      const float U = acc * iZ;
-      gst(d.u_new + r, U);
-      if (plant && r < 3) lds_put(s_plant + 14 + r, (double)U);
-      // receding-horizon shift: U_nom <- [U[1:], U[T-1]]
-      if (r >= 3) gst(d.u_nom_out + r - 3, U);
-      if (r + 3 >= R) gst(d.u_nom_out + r, U);
+      put_result(d, r, R, acc * iZ, plant, s_plant);
     }
   } else {
-    // every cost non-finite: return the nominal sequence, keep the warm start
-    for (uint32_t r = threadIdx.x; r < R; r += nt) {
-      const float U = gld(d.u_nom_in + r);
-      gst(d.u_new + r, U);
-      if (plant && r < 3) lds_put(s_plant + 14 + r, (double)U);
-    }
+    put_nominal(d, R, plant, s_plant);
   }
-  if (threadIdx.x == 0) {
-    d.stats[0] = m;
-    d.stats[1] = Z;
-    d.stats[2] = ok ? Z * Z / Z2 : 0.0f;
-    d.stats[3] = ok ? (float)BRMPPI_OK : (float)BRMPPI_ENONFINITE;
-  }
-  if (plant) {
-    __syncthreads();                 // U_new[0] from threads 0..2, the state and sines
-    if (threadIdx.x == 0) plant_finish(d, s_plant);
-  }
+  finish_instance(d, m, Z, Z2, ok, plant, s_plant);
 }
 
 // ---------------------------------------------------------------------------
@@ -1668,8 +1687,10 @@ __device__ __forceinline__ void group_sums(const float4* up, const float* sig, u
 
 // Group merge by the last tile of the group: m_g, unit scales, (Z_g, Z2_g)
 // and the group row sums from the units' partials.
-__device__ __forceinline__ void group_merge(const SolveDesc& d, uint32_t grp, uint32_t gu0, uint32_t nu_g, float* s_sig,
-                            float4* s_up, float* s_red) {
+// put_part(m_g, Z_g, Z2_g) runs on one thread, put_row(r, sum) on the row's.
+template <typename PutPart, typename PutRow>
+__device__ __forceinline__ void group_merge(const SolveDesc& d, uint32_t gu0, uint32_t nu_g, float* s_sig,
+                                            float4* s_up, float* s_red, PutPart put_part, PutRow put_row) {
   const uint32_t t = threadIdx.x, nt = blockDim.x, R = 3 * d.T;
   // this thread's first row: all the group's unit sums, loaded before the
   // minimum (they do not depend on it)
@@ -1695,7 +1716,7 @@ __device__ __forceinline__ void group_merge(const SolveDesc& d, uint32_t grp, ui
   if (t == tz) {
     float z, z2;
     group_sums(s_up, s_sig, nu_g, z, z2);
-    pub_st4(d.wpart + grp, make_float4(mg, z, z2, 0.0f));
+    put_part(mg, z, z2);
   }
   // one row: its unit sums in v, the scales read kChunk at a time (in bounds,
   // before any of them is used)
@@ -1710,7 +1731,7 @@ __device__ __forceinline__ void group_merge(const SolveDesc& d, uint32_t grp, ui
       for (int k = 0; k < kChunk; ++k)
         if ((uint32_t)(c + k) < nu_g) acc = unit_row_term(acc, sg[k], v[c + k]);
     }
-    pub_st(d.rpart + (size_t)grp * R + r, acc);
+    put_row(r, acc);
   };
   if (t < R) row_sum(t, v0);
   for (uint32_t r = t + nt; r < R; r += nt) {
@@ -1788,16 +1809,24 @@ __device__ __forceinline__ void tile_epilogue(const SolveDesc& d, uint32_t s0, u
   if (t == 0) *s_flag = (atomicAdd(&d.gctr[grp * kCtrStride], 1u) == tiles_g - 1) ? 1u : 0u;
   __syncthreads();
   if (*s_flag == 0u) return;
-  group_merge(d, grp, gu0, nu_g, s_sig, s_up, s_red);
   if (t == 0) atomicExch(&d.gctr[grp * kCtrStride], 0u);
+  group_merge(
+      d, gu0, nu_g, s_sig, s_up, s_red,
+      [&](float m, float z, float z2) { pub_st4(d.wpart + grp, make_float4(m, z, z2, 0.0f)); },
+      [&](uint32_t r, float sum) { pub_st(d.rpart + (size_t)grp * R + r, sum); });
   // publish the group; the last group merges the instance
   pub_complete();
   __syncthreads();
-  if (t == 0) *s_flag = (atomicAdd(d.counter, 1u) == d.n_wchunk - 1) ? 1u : 0u;
-  __syncthreads();
-  if (*s_flag == 0u) return;
+  if (d.n_wchunk > 1) {
+    if (t == 0) {
+      const bool last = atomicAdd(d.counter, 1u) == d.n_wchunk - 1;
+      if (last) atomicExch(d.counter, 0u);
+      *s_flag = last ? 1u : 0u;
+    }
+    __syncthreads();
+    if (*s_flag == 0u) return;
+  }
   finalize_instance(d, s_u, s_red, s_trig);   // the inputs' LDS is free: merge scales
-  if (t == 0) atomicExch(d.counter, 0u);
 }
 
 // Where a tile's instance starts: the start state, the path index of its start

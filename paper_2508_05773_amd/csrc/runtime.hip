@@ -1053,8 +1053,7 @@ int closed_loop_locked(brmppi_ctx* ctx, const brmppi_problem* p0, uint32_t n_up,
   const bool logs = x_out || u_applied;
   const size_t desc_bytes = round_up(sizeof(SolveDesc), 256);
   const size_t unom_bytes = p.u_nom ? sizeof(float) * 3 * p.T : 0;
-  const size_t xlog_bytes = round_up(sizeof(double) * 8 * C, 256);
-  const size_t half_bytes = desc_bytes * C + xlog_bytes + round_up(sizeof(float) * 3 * C, 256);
+  const size_t half_bytes = desc_bytes * C + round_up(sizeof(double) * kLogRecord * C, 256);
   // device: [scratch | counters (zero) | nominal | half 0 | half 1 | normals of C updates]
   // pinned: [counters | nominal | half 0 | half 1 | start state]; a half holds
   // the chunk's descriptors, then its plant states and applied inputs
@@ -1092,10 +1091,11 @@ int closed_loop_locked(brmppi_ctx* ctx, const brmppi_problem* p0, uint32_t n_up,
   auto take_logs = [&](uint32_t j) {
     const char* hp = half_pin((int)(j % 2));
     const uint32_t k0 = j * C, cnt = std::min(C, n_up - k0);
-    if (x_out)
-      std::memcpy(x_out + 8 * (size_t)(k0 + 1), hp + desc_bytes * C, sizeof(double) * 8 * cnt);
-    if (u_applied)
-      std::memcpy(u_applied + 3 * (size_t)k0, hp + desc_bytes * C + xlog_bytes, sizeof(float) * 3 * cnt);
+    const double* rec = reinterpret_cast<const double*>(hp + desc_bytes * C);
+    for (uint32_t i = 0; i < cnt; ++i, rec += kLogRecord) {
+      if (x_out) std::memcpy(x_out + 8 * (size_t)(k0 + i + 1), rec, sizeof(double) * 8);
+      if (u_applied) std::memcpy(u_applied + 3 * (size_t)(k0 + i), rec + 8, sizeof(float) * 3);
+    }
   };
   for (uint32_t j = 0; j < n_chunks; ++j) {
     const int h = (int)(j % 2);
@@ -1112,6 +1112,9 @@ int closed_loop_locked(brmppi_ctx* ctx, const brmppi_problem* p0, uint32_t n_up,
       // only the first update reads the caller's sequence; later ones the shifted result
       fill_desc(*d, p, c, L, base, k, (k == 0 && p.u_nom) ? d_unom : nullptr, d_ctr, d_out, lds > 0, false);
       if (pre) d->noise = reinterpret_cast<float*>(base + noise_off + i * noise_bytes);
+      // the update's last block writes the log (two device copies an update
+      // took 2.6 us of it)
+      if (logs) d->log = reinterpret_cast<double*>(hd + desc_bytes * C) + kLogRecord * i;
     }
     HIPCHK(hipMemcpyAsync(hd, hp, desc_bytes * cnt, hipMemcpyHostToDevice, s));
     const SolveDesc* first = reinterpret_cast<const SolveDesc*>(hd);
@@ -1119,8 +1122,6 @@ int closed_loop_locked(brmppi_ctx* ctx, const brmppi_problem* p0, uint32_t n_up,
       rc = timed(ctx, s, 4, [&] { return launch_noise(first, desc_bytes, cnt, p.S, p.T, L.n_normals, s); });
       if (rc) return rc;
     }
-    double* xlog = reinterpret_cast<double*>(hd + desc_bytes * C);
-    float* ulog = reinterpret_cast<float*>(hd + desc_bytes * C + xlog_bytes);
     for (uint32_t i = 0; i < cnt; ++i) {
       const SolveDesc* dd = reinterpret_cast<const SolveDesc*>(hd + desc_bytes * i);
       if (!pre) {
@@ -1128,8 +1129,6 @@ int closed_loop_locked(brmppi_ctx* ctx, const brmppi_problem* p0, uint32_t n_up,
       } else {
         if ((rc = enqueue_rollout_reduce(ctx, s, dd, p, L, sh, lds))) return rc;
       }
-      if (x_out) HIPCHK(hipMemcpyAsync(xlog + 8 * i, c.plant, sizeof(double) * 8, hipMemcpyDeviceToDevice, s));
-      if (u_applied) HIPCHK(hipMemcpyAsync(ulog + 3 * i, d_out + 4, sizeof(float) * 3, hipMemcpyDeviceToDevice, s));
     }
     if (logs)
       HIPCHK(hipMemcpyAsync(hp + desc_bytes * C, hd + desc_bytes * C, half_bytes - desc_bytes * C,

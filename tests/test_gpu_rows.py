@@ -104,3 +104,24 @@ def test_no_room_for_normals(ctx, n_obs):
         got = B.brmppi_solve_ex(c.h, B.ProblemBuffers(p, controller=0), want_J=True)
     assert np.array_equal(got["J"], want["J"])
     assert np.array_equal(got["U_new"], want["U_new"])
+
+
+@pytest.mark.parametrize("S", [1, 33, 1024, 1025])
+def test_one_group_and_two(ctx, S):
+    """Up to 1024 samples an instance is merged by the block that merges its one
+    group: bit for bit the batch's separate reduction, update after update, with
+    either log of the closed loop."""
+    p = problem("moving", 3).copy(S=S)
+    ctx.set_path(0, p.path, p.ds)
+    ctx.set_path(1, p.path, p.ds)
+    x, u = B.brmppi_closed_loop(ctx.h, B.ProblemBuffers(p, controller=0), 3)
+    B.brmppi_set_state(ctx.h, 1, p.x0.astype(np.float64))
+    for k in range(3):
+        pb = B.ProblemBuffers(p, controller=1, with_nominal=(k == 0), seed=p.seed + k,
+                              flags=p.flags | B.X0_RESIDENT | B.ADVANCE_PLANT)
+        assert np.array_equal(B.brmppi_solve_batch(ctx.h, [pb])[0][0][0], u[k])
+        assert np.array_equal(B.brmppi_get_state(ctx.h, 1), x[k + 1])
+    ctx.set_path(0, p.path, p.ds)
+    assert np.array_equal(B.brmppi_closed_loop(ctx.h, B.ProblemBuffers(p, controller=0), 3, want_u=False)[0], x)
+    ctx.set_path(0, p.path, p.ds)
+    assert np.array_equal(B.brmppi_closed_loop(ctx.h, B.ProblemBuffers(p, controller=0), 3, want_x=False)[1], u)
