@@ -110,10 +110,22 @@ __host__ __device__ inline size_t fused_lds_bytes(uint32_t per_tile, uint32_t T,
   return sizeof(float) * (fused_lds_region(per_tile, T, n_groups) + 2 * (size_t)per_tile + 2 * kGroupUnits) +
          16 * kGroupUnits;
 }
-// normals of `count` instances whose descriptors start at `first`, `stride`
-// bytes apart (all with the same S, T and normals per step)
-hipError_t launch_noise(const SolveDesc* first, size_t stride, uint32_t count, uint32_t S, uint32_t T,
-                        uint32_t n_normals, hipStream_t stream);
+// inputs a launch copies from pinned host memory to the device (n 16-byte units)
+struct Upload {
+  const void* src;
+  void* dst;
+  size_t n;
+};
+hipError_t launch_upload(const Upload& up, hipStream_t stream);
+// normals of `count` updates (update u: seed + u, its buffer u * stride floats
+// on); the launch also makes the upload
+struct NoiseArgs {
+  float* noise;
+  size_t stride;
+  uint64_t seed;
+  uint32_t S_pad, n_normals, instance;
+};
+hipError_t launch_noise(const NoiseArgs& a, uint32_t count, uint32_t T, const Upload& up, hipStream_t stream);
 hipError_t launch_reduce(const SolveDesc* descs, const Item* items, uint32_t n_items,
                          BatchCounters* ctr, uint32_t grid, hipStream_t stream);
 hipError_t launch_philox_dump(const uint32_t* ctr, uint32_t k0, uint32_t k1, uint32_t n, uint32_t* out,

@@ -119,7 +119,7 @@ struct ScratchLayout {
 };
 
 // one instance's uploaded inputs: [descriptor | reduce counter (zero) | nominal
-// sequence]; a single host-to-device copy carries all three
+// sequence], staged together in pinned memory
 struct InputBlock {
   size_t counter, unom, bytes;
 };
@@ -591,13 +591,16 @@ void collect_timing(brmppi_ctx* ctx) {
   ctx->pending_timing.clear();
 }
 
-// enqueue (noise +) rollout + weights + reduce (+ plant) of one instance whose
-// descriptor is at d_desc, with launch shape sh and scratch layout L
-int enqueue_noise(brmppi_ctx* ctx, hipStream_t st, const SolveDesc* d_desc, const brmppi_problem& p,
-                  const ScratchLayout& L) {
-  if (!L.n_normals) return fail(BRMPPI_EINVAL, "internal: noise buffer missing");
-  return timed(ctx, st, 4, [&] { return launch_noise(d_desc, 0, 1, p.S, p.T, L.n_normals, st); });
+// the normals of `count` updates from the one of descriptor h on, buffers
+// `stride` floats apart, and the upload of their inputs, in one launch
+int enqueue_noise(brmppi_ctx* ctx, hipStream_t st, const SolveDesc& h, uint32_t count, size_t stride,
+                  const Upload& up) {
+  if (!h.noise) return fail(BRMPPI_EINVAL, "internal: noise buffer missing");
+  const NoiseArgs a{h.noise, stride, (uint64_t)h.seed_hi << 32 | h.seed_lo, h.S_pad, h.n_normals, h.instance};
+  return timed(ctx, st, 4, [&] { return launch_noise(a, count, h.T, up, st); });
 }
+
+Upload upload(const char* src, char* dst, size_t bytes) { return Upload{src, dst, (bytes + 15) / 16}; }
 
 // rollout + weights + reduce (+ plant) of one instance whose normals, if the
 // shape reads them, are already in its noise buffer (or ordered before on st);
@@ -615,16 +618,6 @@ int enqueue_rollout_reduce(brmppi_ctx* ctx, hipStream_t st, const SolveDesc* d_d
   return timed(ctx, st, 1, [&] { return launch_reduce(d_desc, nullptr, nr, nullptr, nr, st); });
 }
 
-// (noise +) rollout + weights + reduce (+ plant) of one instance
-int enqueue_single(brmppi_ctx* ctx, hipStream_t st, const SolveDesc* d_desc, const brmppi_problem& p,
-                   const ScratchLayout& L, const LaunchShape& sh, size_t lds) {
-  int rc;
-  if (variant_pre(sh.variant)) {
-    if ((rc = enqueue_noise(ctx, st, d_desc, p, L))) return rc;
-  }
-  return enqueue_rollout_reduce(ctx, st, d_desc, p, L, sh, lds);
-}
-
 int ensure_scratch(brmppi_ctx* ctx, size_t bytes) {
   if (ctx->scratch.bytes >= bytes) return 0;
   if (ctx->scratch.ptr) ++ctx->scratch_grows;
@@ -637,6 +630,45 @@ int ensure_scratch(brmppi_ctx* ctx, size_t bytes) {
 // ---------------------------------------------------------------------------
 // plain solve
 // ---------------------------------------------------------------------------
+// Costs of up to this size are written to pinned host memory by the rollout
+// itself: the transfer runs while the samples do.
+constexpr size_t kDirectCostBytes = size_t(1) << 20;
+// Larger results come in pieces of this size through two halves of the pinned
+// buffer: the device fills one while the host empties the other.
+// (3001 applied sequences of 37 steps, 1.4 MB: 191 us for the update and its
+// download; by a pitched copy to the caller's pageable memory 900 us)
+constexpr size_t kPieceBytes = size_t(256) << 10;
+
+// n_rows rows of `row` floats, `pitch` apart at src on the device, to dense rows at dst
+int download_rows(brmppi_ctx* ctx, hipStream_t s, float* dst, size_t row, const char* src, size_t pitch, size_t n_rows,
+                  const char* piece) {
+  constexpr size_t kPiece = kPieceBytes / sizeof(float);
+  const size_t total = (n_rows - 1) * pitch + row;
+  const size_t n_pieces = (total + kPiece - 1) / kPiece;
+  auto half = [&](size_t k) { return const_cast<char*>(piece) + (k % 2) * kPieceBytes; };
+  auto fetch = [&](size_t k) -> int {
+    const size_t a = k * kPiece, n = std::min(kPiece, total - a);
+    HIPCHK(hipMemcpyAsync(half(k), src + a * sizeof(float), n * sizeof(float), hipMemcpyDeviceToHost, s));
+    HIPCHK(hipEventRecord(ctx->loop_ev[k % 2], s));
+    return 0;
+  };
+  if (int rc = fetch(0)) return rc;
+  for (size_t k = 0; k < n_pieces; ++k) {
+    if (k + 1 < n_pieces)
+      if (int rc = fetch(k + 1)) return rc;
+    HIPCHK(hipEventSynchronize(ctx->loop_ev[k % 2]));
+    const float* got = reinterpret_cast<const float*>(half(k));
+    const size_t a = k * kPiece, b = std::min(total, a + kPiece);
+    for (size_t at = a; at < b;) {
+      const size_t r = at / pitch, c = at - r * pitch;   // c past the row: its padding
+      const size_t end = std::min(b, r * pitch + (c < row ? row : pitch));
+      if (c < row) std::memcpy(dst + r * row + c, got + (at - a), (end - at) * sizeof(float));
+      at = end;
+    }
+  }
+  return 0;
+}
+
 // fixed != nullptr: the scratch is that block of fixed_bytes (the device's
 // static scratch), and the call allocates nothing: no arena block, no pinned
 // staging growth, no HIP events (sizes beyond either are ENOMEM)
@@ -654,8 +686,14 @@ int solve_locked(brmppi_ctx* ctx, const brmppi_problem* p, const brmppi_outputs*
   const InputBlock IB = input_block(p->T, p->u_nom != nullptr, L.n_wchunk);
   const size_t in_off = L.bytes;
   const size_t need = in_off + round_up(IB.bytes, 256);
-  const size_t out_floats = 4 + 3 * (size_t)p->T;
-  const size_t pin_need = round_up(IB.bytes, 256) + out_floats * sizeof(float);
+  // pinned: [input block | stats, sequence | costs | two pieces of the sequences];
+  // the kernels read the first and write the next two themselves
+  const size_t out_off = round_up(IB.bytes, 256);
+  const size_t J_off = out_off + round_up((4 + 3 * (size_t)p->T) * sizeof(float), 256);
+  const bool J_direct = out->J_out && lds > 0 && p->S * sizeof(float) <= kDirectCostBytes;
+  const size_t piece_off = J_off + (J_direct ? round_up(p->S * sizeof(float), 256) : 0);
+  const bool rows_out = out->useq_out || (out->J_out && !J_direct);
+  const size_t pin_need = piece_off + (rows_out ? 2 * kPieceBytes : 0);
   char* base;
   if (fixed) {
     if (need > fixed_bytes)
@@ -672,29 +710,35 @@ int solve_locked(brmppi_ctx* ctx, const brmppi_problem* p, const brmppi_outputs*
   hipStream_t s = ctx->streams[0];
   char* pin = ctx->pin.ptr;
   SolveDesc* h_desc = reinterpret_cast<SolveDesc*>(pin);
-  float* pin_out = reinterpret_cast<float*>(pin + round_up(IB.bytes, 256));
+  float* pin_out = reinterpret_cast<float*>(pin + out_off);
+  float* pin_J = reinterpret_cast<float*>(pin + J_off);
 
   fill_desc(*h_desc, *p, c, L, base, 0, reinterpret_cast<const float*>(base + in_off + IB.unom),
-            reinterpret_cast<uint32_t*>(base + in_off + IB.counter), reinterpret_cast<float*>(base + L.off_out),
-            lds > 0, out->useq_out != nullptr);
+            reinterpret_cast<uint32_t*>(base + in_off + IB.counter), pin_out, lds > 0, out->useq_out != nullptr);
+  if (J_direct) h_desc->J = pin_J;
   std::memset(pin + IB.counter, 0, IB.unom - IB.counter);
   if (p->u_nom) std::memcpy(pin + IB.unom, p->u_nom, sizeof(float) * 3 * p->T);
-  HIPCHK(hipMemcpyAsync(d_desc, h_desc, IB.bytes, hipMemcpyHostToDevice, s));
+  const Upload up = upload(pin, base + in_off, IB.bytes);
   ctx->no_events = fixed != nullptr;
-  rc = enqueue_single(ctx, s, d_desc, *p, L, sh, lds);
+  if (variant_pre(sh.variant)) {
+    rc = enqueue_noise(ctx, s, *h_desc, 1, 0, up);
+  } else {
+    const hipError_t e = launch_upload(up, s);
+    rc = e == hipSuccess ? 0 : fail(BRMPPI_EDEVICE, std::string("upload: ") + hipGetErrorString(e));
+  }
+  if (!rc) rc = enqueue_rollout_reduce(ctx, s, d_desc, *p, L, sh, lds);
   ctx->no_events = false;
   if (rc) {
     (void)hipStreamSynchronize(s);   // nothing of this call may still run on the scratch
     return rc;
   }
-  HIPCHK(hipMemcpyAsync(pin_out, base + L.off_out, out_floats * sizeof(float), hipMemcpyDeviceToHost, s));
   HIPCHK(hipStreamSynchronize(s));
   collect_timing(ctx);
-  if (out->J_out) HIPCHK(hipMemcpy(out->J_out, base + L.off_J, sizeof(float) * p->S, hipMemcpyDeviceToHost));
-  if (out->useq_out) {
-    HIPCHK(hipMemcpy2D(out->useq_out, sizeof(float) * p->S, base + L.off_ustar, sizeof(float) * L.S_pad,
-                       sizeof(float) * p->S, 3 * (size_t)p->T, hipMemcpyDeviceToHost));
-  }
+  if (J_direct) std::memcpy(out->J_out, pin_J, sizeof(float) * p->S);
+  else if (out->J_out && (rc = download_rows(ctx, s, out->J_out, p->S, base + L.off_J, L.S_pad, 1, pin + piece_off))) return rc;
+  if (out->useq_out && (rc = download_rows(ctx, s, out->useq_out, p->S, base + L.off_ustar, L.S_pad, 3 * (size_t)p->T,
+                                           pin + piece_off)))
+    return rc;
   const int status = (int)pin_out[3];
   std::memcpy(out->u_out, pin_out + 4, sizeof(float) * 3 * p->T);
   if (status == BRMPPI_OK) c.warm_T = p->T;   // the shifted result is resident
@@ -723,7 +767,7 @@ struct BatchPlan {
   // block layout: header [descs | tiles | ritems | nominals | counters]
   // (one upload), outputs (one download), then every instance's scratch
   size_t off_descs = 0, off_tiles = 0, off_ritems = 0, off_counters = 0, header_bytes = 0;
-  size_t off_outs = 0, out_floats = 0, total = 0;
+  size_t out_floats = 0, total = 0;
   uint32_t block = 256;              // of the rollout launch
 };
 
@@ -761,7 +805,6 @@ void plan_layout(brmppi_ctx* ctx, const brmppi_problem* const* ps, uint32_t n, B
   bp.off_counters = o;                        // uploaded as zeros
   o = round_up(o + sizeof(uint32_t) * n, 256);
   bp.header_bytes = o;
-  bp.off_outs = o;
   bp.out_pos.resize(n);
   size_t nf = 0;
   for (uint32_t i = 0; i < n; ++i) {
@@ -769,7 +812,6 @@ void plan_layout(brmppi_ctx* ctx, const brmppi_problem* const* ps, uint32_t n, B
     nf += 4 + 3 * (size_t)ps[i]->T;
   }
   bp.out_floats = nf;
-  o = round_up(o + sizeof(float) * nf, 256);
   bp.scratch_off.resize(n);
   for (uint32_t i = 0; i < n; ++i) {
     bp.scratch_off[i] = o;
@@ -785,9 +827,8 @@ void plan_descs(brmppi_ctx* ctx, const brmppi_problem* const* ps, uint32_t n, ch
     const brmppi_problem& p = *ps[i];
     const float* unom_dev = p.u_nom ? reinterpret_cast<const float*>(base + bp.unom_off[i]) : nullptr;
     uint32_t* counter = reinterpret_cast<uint32_t*>(base + bp.off_counters) + i;
-    float* out = reinterpret_cast<float*>(base + bp.off_outs) + bp.out_pos[i];
     fill_desc(bp.descs[i], p, ctx->ctrl[p.controller], bp.layouts[i], base + bp.scratch_off[i], 0, unom_dev,
-              counter, out);
+              counter, nullptr);   // the outputs' place follows when it is staged
   }
 }
 
@@ -891,18 +932,25 @@ int enqueue_batch(brmppi_ctx* ctx, hipStream_t st, char* base, const BatchPlan& 
   return 0;
 }
 
-// write the header of a batch into pinned memory (uploaded to `base` in one copy)
+// write the header of a batch into pinned memory (uploaded to the batch's block
+// by one launch); the outputs follow it there, written by the kernels
 void stage_batch(const BatchPlan& bp, const brmppi_problem* const* ps, char* pin) {
   std::memcpy(pin + bp.off_descs, bp.descs.data(), sizeof(SolveDesc) * bp.descs.size());
   std::memcpy(pin + bp.off_tiles, bp.tiles.data(), sizeof(Tile) * bp.tiles.size());
   std::memcpy(pin + bp.off_ritems, bp.ritems.data(), sizeof(Item) * bp.ritems.size());
+  float* outs = reinterpret_cast<float*>(pin + bp.header_bytes);
+  for (size_t i = 0; i < bp.descs.size(); ++i) {
+    SolveDesc& d = reinterpret_cast<SolveDesc*>(pin + bp.off_descs)[i];
+    d.stats = outs + bp.out_pos[i];
+    d.u_new = d.stats + 4;
+  }
   for (size_t i = 0; i < bp.descs.size(); ++i)
     if (ps[i]->u_nom) std::memcpy(pin + bp.unom_off[i], ps[i]->u_nom, sizeof(float) * 3 * ps[i]->T);
   std::memset(pin + bp.off_counters, 0, bp.header_bytes - bp.off_counters);
 }
 
-// enqueue upload, kernels (or a graph of them) and the single download of a batch
-// whose block starts at `base`; `pin` holds header_bytes + out_floats floats
+// enqueue the upload and the kernels (or a graph of them) of a batch whose block
+// starts at `base`; `pin` holds header_bytes + out_floats floats
 int run_batch(brmppi_ctx* ctx, hipStream_t s, char* base, const BatchPlan& bp, BatchCounters* ctr, char* pin,
               bool use_graph);
 
@@ -916,7 +964,7 @@ void drop_graph(brmppi_ctx* ctx) {
 
 int run_batch(brmppi_ctx* ctx, hipStream_t s, char* base, const BatchPlan& bp, BatchCounters* ctr, char* pin,
               bool use_graph) {
-  HIPCHK(hipMemcpyAsync(base, pin, bp.header_bytes, hipMemcpyHostToDevice, s));
+  HIPCHK(launch_upload(upload(pin, base, bp.header_bytes), s));
   int rc;
   if (!use_graph) {
     if ((rc = enqueue_batch(ctx, s, base, bp, ctr, true))) return rc;
@@ -941,8 +989,6 @@ int run_batch(brmppi_ctx* ctx, hipStream_t s, char* base, const BatchPlan& bp, B
     }
     HIPCHK(hipGraphLaunch(ctx->graph_exec, s));
   }
-  HIPCHK(hipMemcpyAsync(pin + bp.header_bytes, base + bp.off_outs, bp.out_floats * sizeof(float),
-                        hipMemcpyDeviceToHost, s));
   return 0;
 }
 
@@ -1085,7 +1131,6 @@ int closed_loop_locked(brmppi_ctx* ctx, const brmppi_problem* p0, uint32_t n_up,
   } else if (x_out) {
     HIPCHK(hipMemcpyAsync(pin_x0, c.plant, sizeof(double) * 8, hipMemcpyDeviceToHost, s));
   }
-  HIPCHK(hipMemcpyAsync(base + in_off, pin, head_bytes, hipMemcpyHostToDevice, s));
   const uint32_t n_chunks = (n_up + C - 1) / C;
   // copy the logs of chunk j (complete) from its staging half to the caller
   auto take_logs = [&](uint32_t j) {
@@ -1116,20 +1161,18 @@ int closed_loop_locked(brmppi_ctx* ctx, const brmppi_problem* p0, uint32_t n_up,
       // took 2.6 us of it)
       if (logs) d->log = reinterpret_cast<double*>(hd + desc_bytes * C) + kLogRecord * i;
     }
-    HIPCHK(hipMemcpyAsync(hd, hp, desc_bytes * cnt, hipMemcpyHostToDevice, s));
-    const SolveDesc* first = reinterpret_cast<const SolveDesc*>(hd);
+    // the chunk's descriptors, with the first chunk the head before them
+    const size_t head = j == 0 ? half_rel : 0;
+    const Upload up = upload(hp - head, hd - head, head + desc_bytes * cnt);
     if (pre) {
-      rc = timed(ctx, s, 4, [&] { return launch_noise(first, desc_bytes, cnt, p.S, p.T, L.n_normals, s); });
-      if (rc) return rc;
+      const SolveDesc& first = *reinterpret_cast<const SolveDesc*>(hp);
+      if ((rc = enqueue_noise(ctx, s, first, cnt, noise_bytes / sizeof(float), up))) return rc;
+    } else {
+      HIPCHK(launch_upload(up, s));
     }
-    for (uint32_t i = 0; i < cnt; ++i) {
-      const SolveDesc* dd = reinterpret_cast<const SolveDesc*>(hd + desc_bytes * i);
-      if (!pre) {
-        if ((rc = enqueue_single(ctx, s, dd, p, L, sh, lds))) return rc;   // includes the plant step
-      } else {
-        if ((rc = enqueue_rollout_reduce(ctx, s, dd, p, L, sh, lds))) return rc;
-      }
-    }
+    for (uint32_t i = 0; i < cnt; ++i)   // each with its plant step
+      if ((rc = enqueue_rollout_reduce(ctx, s, reinterpret_cast<const SolveDesc*>(hd + desc_bytes * i), p, L, sh, lds)))
+        return rc;
     if (logs)
       HIPCHK(hipMemcpyAsync(hp + desc_bytes * C, hd + desc_bytes * C, half_bytes - desc_bytes * C,
                             hipMemcpyDeviceToHost, s));
@@ -1176,10 +1219,8 @@ int HipServed::launch(B& b) {
   if ((rc = ctx->slot_pin[b.slot].ensure(bp.header_bytes + bp.out_floats * sizeof(float)))) return rc;
   char* pin = ctx->slot_pin[b.slot].ptr;
   stage_batch(bp, ps.data(), pin);
-  HIPCHK(hipMemcpyAsync(base, pin, bp.header_bytes, hipMemcpyHostToDevice, s));
+  HIPCHK(launch_upload(upload(pin, base, bp.header_bytes), s));
   if ((rc = enqueue_batch(ctx, s, base, bp, ctx->counters + 1 + b.slot, false))) return rc;
-  HIPCHK(hipMemcpyAsync(pin + bp.header_bytes, base + bp.off_outs, bp.out_floats * sizeof(float),
-                        hipMemcpyDeviceToHost, s));
   st.out_pos = bp.out_pos;
   st.out_floats = bp.out_floats;
   st.out_off = bp.header_bytes;
@@ -1698,7 +1739,7 @@ int brmppi_autotune(brmppi_ctx* ctx) {
           const uint32_t nr = L.n_wchunk * L.n_rgroup;
           auto run = [&]() -> hipError_t {
             hipError_t e = hipSuccess;
-            if (variant_pre(variant)) e = launch_noise(d_desc, 0, 1, S, T, K, s);
+            if (variant_pre(variant)) e = launch_noise(NoiseArgs{h.noise, 0, 0, L.S_pad, K, 0}, 1, T, Upload{}, s);
             if (e == hipSuccess)
               e = launch_rollout(bucket, variant, d_desc, grid, block, lds, s);
             if (e == hipSuccess && !lds) e = launch_reduce(d_desc, nullptr, nr, nullptr, nr, s);

@@ -125,3 +125,21 @@ def test_one_group_and_two(ctx, S):
     assert np.array_equal(B.brmppi_closed_loop(ctx.h, B.ProblemBuffers(p, controller=0), 3, want_u=False)[0], x)
     ctx.set_path(0, p.path, p.ds)
     assert np.array_equal(B.brmppi_closed_loop(ctx.h, B.ProblemBuffers(p, controller=0), 3, want_x=False)[1], u)
+
+
+@pytest.mark.parametrize("S,T", [(67, 120), (70001, 2), (300001, 1)])
+def test_downloads_in_pieces(ctx, S, T):
+    """Costs and applied sequences that reach the caller in several pieces: ends
+    of pieces in a row's padding, rows longer than a piece, costs past the size
+    that the rollout writes to the host itself.  Against the FP64 oracle at the
+    stated bars (costs 1e-4 relative, inputs 1e-4 of their range)."""
+    from oracle import oracle as O
+    p = problem("rest", 0, W.FLAG_GUIDANCE_OFF).copy(S=S, T=T, u_nom=np.zeros((T, 3), np.float32))
+    ctx.set_path(0, p.path, p.ds)
+    want = O.solve(p, nthreads=min(8, os.cpu_count() or 1), want_useq=True)
+    got = B.brmppi_solve_ex(ctx.h, B.ProblemBuffers(p, controller=0), want_J=True, want_useq=True)
+    only = B.brmppi_solve_ex(ctx.h, B.ProblemBuffers(p, controller=0), want_J=True)
+    tol = 1e-4 * np.array([4.0, 1.8, p.params["nu_bar"]])
+    assert np.max(np.abs(got["J"] - want["J"]) / np.abs(want["J"])) <= J_RTOL
+    assert np.all(np.abs(got["useq"].reshape(T, 3, S).transpose(2, 0, 1) - want["useq"]) <= tol)
+    assert np.array_equal(only["J"], got["J"])
