@@ -311,8 +311,9 @@ int brmppi_autotune(brmppi_ctx* ctx);
 /* Force a rollout launch shape for every plain and batched launch: block size
  * 64..256 (multiple of 64) and variant 0 = one lane per sample, noise drawn in
  * the kernel; 1 = one lane, noise from the parallel kernel; 2 / 3 / 4 = two /
- * four / eight lanes per sample, noise from the parallel kernel (a batched
- * launch takes the block size and its own forms; a plain solve whose normals
+ * four / eight lanes per sample, noise from the parallel kernel (eight lanes and
+ * block 256 up to 8192 samples: drawn ahead of the steps by the rollout's own
+ * launch; a batched launch takes the block size and its own forms; a plain solve whose normals
  * would take more than 2 GiB or half the arena draws them in the kernel).  block
  * 0 restores the tuned/default choice.  EINVAL for a block outside 64..256 or
  * not a multiple of 64, or a variant above 4. */
@@ -321,7 +322,8 @@ int brmppi_set_launch(brmppi_ctx* ctx, uint32_t block, uint32_t variant);
  * blocking calls) or BRMPPI_CTX_PROFILE_ROLLOUT (rollout and noise only), from
  * HIP events on the launching stream (ms totals and launch counts):
  * out[0..1] rollout, out[2..3] reduce (weights + average + shift + plant),
- * out[4..5] noise.  A profiling context launches batches directly instead of
+ * out[4..5] noise (drawn by the rollout's own launch: counted, with no time of
+ * its own).  A profiling context launches batches directly instead of
  * replaying their graph. */
 int brmppi_profile_read(brmppi_ctx* ctx, double out[6]);
 int brmppi_profile_reset(brmppi_ctx* ctx);

@@ -22,6 +22,7 @@ constexpr size_t kFusedLdsMax = 64 * 1024;   // dynamic LDS bound of the fused r
 constexpr uint32_t kCtrStride = 32;          // completion counters one 128-B line apart
 constexpr int kPathWin = 1024;    // waypoints staged in LDS per tile
 constexpr int kPathBack = 64;     // of which before the start progress
+constexpr size_t kCuLds = 160 * 1024;
 constexpr int kMaxBlock = 256;    // rollout block size bound (launch_bounds)
 constexpr int kNoisePrefetch = 2;   // steps of normals loaded ahead of their use
 
@@ -49,7 +50,7 @@ struct alignas(16) SolveDesc {
   double* log;                  // closed loop: the update's log record (kLogRecord doubles: the plant
                                 // state after it, the three floats of the averaged first input), or NULL
   const float4* path;           // controller path (absolute coordinates)
-  const float* u_nom_in;        // 3T nominal sequence read by the rollout
+  const float* u_nom_in;        // 3T nominal sequence read by the rollout (NULL: follows the descriptor)
   float* u_nom_out;             // 3T warm-start slot of the controller (shift target)
   float* u_star;                // [3T][S_pad] applied inputs
   float* J;                     // [S_pad]
@@ -66,6 +67,16 @@ struct alignas(16) SolveDesc {
   float* noise;                 // [T][n_normals][S_pad] precomputed normals (variants 1-4)
   brmppi_obstacle obs[BRMPPI_MAX_OBS];
 };
+
+// An update's inputs as the argument of its launch: the descriptor and, where its
+// u_nom_in is NULL, the nominal sequence.
+constexpr uint32_t kInlineSteps = 216;   // with the descriptor, within the 4 KB of arguments
+struct SolveArgs {
+  SolveDesc d;
+  float unom[3 * kInlineSteps];
+  uint32_t run, pad[3];         // steps drawn at a time (set by the launcher)
+};
+static_assert(sizeof(SolveArgs) <= 4096, "a launch's arguments");
 
 struct Tile { uint32_t inst, s0; };
 struct Item { uint32_t inst, idx; };
@@ -89,6 +100,11 @@ int variant_in_kernel(int bucket);
 // descs->fused must be set and the tile size a multiple of kUnit)
 hipError_t launch_rollout(int bucket, int variant, const SolveDesc* desc, uint32_t grid, uint32_t block,
                           size_t lds_bytes, hipStream_t stream);
+// eight lanes per sample, the normals drawn by the same launch
+// (k_rollout_drawn, fused epilogue); one block of kDrawnTile samples per CU, T <= kInlineSteps
+constexpr int kDrawnVariant = 7;
+constexpr uint32_t kDrawnTile = 32;
+hipError_t launch_rollout_drawn(int bucket, SolveArgs& args, uint32_t grid, size_t lds_bytes, hipStream_t stream);
 // the rollouts of a batch's tiles (each of block / variant_lanes(variant_in_kernel(bucket))
 // samples of its instance); grid at most n_tiles
 hipError_t launch_rollout_batch(const SolveDesc* descs, const Tile* tiles, uint32_t n_tiles, BatchCounters* ctr,

@@ -730,6 +730,17 @@ constexpr int philox_blocks() {
   return GUIDED ? (5 + NOB + 3) / 4 : 1;
 }
 
+// Where a rollout's normals come from: drawn by its own lanes, read from the
+// buffer of the noise kernel, or read from LDS, where the block draws those of a
+// run of steps at a time (k_rollout_drawn)
+enum NoiseFrom : int { kOwnDraw = 0, kBuffer = 1, kRuns = 2 };
+
+// floats of a sample and step in a run (16 bytes of padding, as below)
+template <int NOB, bool GUIDED>
+constexpr int run_stride() {
+  return 4 * philox_blocks<NOB, GUIDED>() + 4;
+}
+
 // Normals drawn in the kernel for samples shared by G lanes: lane g draws the
 // blocks g, g + G, ..., and the lanes read what they need from the sample's
 // place in LDS (in floats; 16 bytes of padding spread the samples over the banks)
@@ -744,12 +755,14 @@ constexpr int coop_stride() {
 // holds the same inputs, state and cost.
 // s_u / s_J (fused epilogue): the tile's applied inputs [3T][lds_stride] and
 // costs in LDS, at column t_local.
-template <int NOB, bool GUIDED, int G, bool PRE, int ROWS>
+// kRuns: the steps before run_end are drawn; next_run(run_end) draws the next
+// ones and gives their end.
+template <int NOB, bool GUIDED, int G, int NOISE, int ROWS, typename NextRun>
 __device__ __forceinline__ void rollout_sample(const SolveDesc& d, uint32_t s, bool store, int g, const float* x0,
                                                const ObsL* __restrict__ sobs, const float4* __restrict__ spath,
                                                const float4* __restrict__ s_un, int w0, int nw, int k0, float phi0,
                                                float* s_u, uint32_t lds_stride, uint32_t t_local, float* s_J,
-                                               float* s_nrm) {
+                                               float* s_nrm, uint32_t run_end, NextRun next_run) {
   static_assert(G == 1 || G == 2 || G == 4 || G == 8, "lanes per sample");
   constexpr int NSL = GUIDED ? (NOB + G - 1) / G : 1;   // obstacle slots of this lane
   constexpr int NV = 8 / G;                            // virtual lanes of this lane
@@ -757,7 +770,9 @@ __device__ __forceinline__ void rollout_sample(const SolveDesc& d, uint32_t s, b
   constexpr int NH = (G == 1) ? 2 : 1;                 // hitch rows computed by this lane
   constexpr int NBMAX = philox_blocks<NOB, GUIDED>();    // Philox blocks of a step
   // normals drawn in the kernel and shared by the sample's lanes through LDS
-  constexpr bool kCoop = !PRE && G > 1;
+  constexpr bool PRE = NOISE == kBuffer;
+  constexpr bool kCoop = NOISE == kOwnDraw && G > 1;
+  constexpr bool kFromRun = NOISE == kRuns;
   const brmppi_params& P = d.prm;
   const uint32_t T = d.T;
   const int n_obs = (int)d.n_obs;
@@ -866,7 +881,7 @@ __device__ __forceinline__ void rollout_sample(const SolveDesc& d, uint32_t s, b
   // arithmetic per load.
   static_assert(!PRE || kNoisePrefetch == 2, "two queue slots");
   constexpr int PF = PRE ? 2 : 1;
-  float nx_in[PF][3], nx_h[PF][NH], nx_o[PF][NSL];   // (kCoop: the next step's, read from LDS)
+  float nx_in[PF][3], nx_h[PF][NH], nx_o[PF][NSL];   // (from LDS: the next step's)
   uint32_t off_in[3], off_h[NH], off_o[NSL];
   const uint32_t step_bytes = d.n_normals * S_pad * (uint32_t)sizeof(float);
   const uint32_t last_bytes = step_bytes * (T - 1);
@@ -910,9 +925,10 @@ __device__ __forceinline__ void rollout_sample(const SolveDesc& d, uint32_t s, b
   // operations execute in order: the fences only keep the compiler from
   // reordering them.  A normal past the drawn blocks (rows past the last
   // obstacle) is read from the last drawn one.
-  float* const nrm = kCoop ? s_nrm + t_local * coop_stride<NOB, G>() : nullptr;
+  // kFromRun: the same from the sample's place in the run of steps in LDS.
+  const float* nrm = s_nrm + t_local * (kCoop ? coop_stride<NOB, G>() : run_stride<NOB, GUIDED>());
   uint32_t nrm_o[NSL];
-  if constexpr (kCoop) {
+  if constexpr (kCoop || kFromRun) {
 #pragma unroll
     for (int j = 0; j < NSL; ++j) nrm_o[j] = min((uint32_t)(5 + gi + G * j), (uint32_t)(4 * nb - 1));
   }
@@ -926,19 +942,26 @@ __device__ __forceinline__ void rollout_sample(const SolveDesc& d, uint32_t s, b
           float e[4];
           philox4x32_10(s, tau, (uint32_t)(g + G * i), d.instance, d.seed_lo, d.seed_hi, r);
           box_muller4(r, e);
-          lds_put(reinterpret_cast<float4*>(nrm) + g + G * i, make_float4(e[0], e[1], e[2], e[3]));
+          lds_put(reinterpret_cast<float4*>(s_nrm + t_local * coop_stride<NOB, G>()) + g + G * i,
+                  make_float4(e[0], e[1], e[2], e[3]));
         }
       }
       asm volatile("" ::: "memory");
-      const Vec3 in = lds3(reinterpret_cast<const float4*>(nrm));
+    }
+    if constexpr (kCoop || kFromRun) {
+      const float* at = nrm;
+      const Vec3 in = lds3(reinterpret_cast<const float4*>(at));
       nx_in[0][0] = in.x;
       nx_in[0][1] = in.y;
       nx_in[0][2] = in.z;
+      if constexpr (GUIDED) {
 #pragma unroll
-      for (int k = 0; k < NH; ++k) nx_h[0][k] = lds(nrm + min(3 + hk0 + k, 4 * nb - 1));
+        for (int k = 0; k < NH; ++k) nx_h[0][k] = lds(at + min(3 + hk0 + k, 4 * nb - 1));
 #pragma unroll
-      for (int j = 0; j < NSL; ++j) nx_o[0][j] = lds(nrm + nrm_o[j]);
+        for (int j = 0; j < NSL; ++j) nx_o[0][j] = lds(at + nrm_o[j]);
+      }
     }
+    if constexpr (kFromRun) nrm += kDrawnTile * run_stride<NOB, GUIDED>();
   };
   coop_draw(0);
   Vec3 un = lds3(s_un);                        // nominal inputs, read a step ahead
@@ -954,7 +977,7 @@ __device__ __forceinline__ void rollout_sample(const SolveDesc& d, uint32_t s, b
     // --- noise: normals 0..2 perturb the inputs, 3 and 4 the hitch rows'
     // auxiliary inputs, 5 + o obstacle o's ---
     float uj, uw, unu, nz_h[NH], nz_o[NSL];
-    if constexpr (PRE || kCoop) {
+    if constexpr (PRE || kCoop || kFromRun) {
       uj = fmaf(sj, nx_in[q][0], un.x);
       uw = fmaf(sw, nx_in[q][1], un.y);
       unu = fmaf(sn, nx_in[q][2], un.z);
@@ -987,7 +1010,7 @@ __device__ __forceinline__ void rollout_sample(const SolveDesc& d, uint32_t s, b
         for (int j = 0; j < NSL; ++j) nz_o[j] = fmaf(ke, eps[5 + j], kc);   // G == 1: slot j is obstacle j
       }
     }
-    if constexpr (kCoop) coop_draw(tau + 1);   // (the draw of step T is unused)
+    if constexpr (kCoop) coop_draw(tau + 1);   // (step T's are unused)
     un = lds3(s_un + (tau + 1));   // (past the last step: the staged array's extra entry, unused)
     RefPoint rf{};
     if constexpr (!kBatchCost) rf = reference(f, k0, n_path, spath, w0, nw, gpath, ox, oy);
@@ -1005,7 +1028,7 @@ __device__ __forceinline__ void rollout_sample(const SolveDesc& d, uint32_t s, b
     // normals' products here (the compiler would otherwise sink them to their
     // uses in the rows, past the refill) and the scheduling barrier keeps the
     // refill below them.
-    if constexpr (PRE) {
+    if constexpr (PRE || kFromRun) {
       asm volatile("" : "+v"(uj), "+v"(uw), "+v"(unu));
       if constexpr (GUIDED) {
 #pragma unroll
@@ -1014,7 +1037,8 @@ __device__ __forceinline__ void rollout_sample(const SolveDesc& d, uint32_t s, b
         for (int j = 0; j < NSL; ++j) asm volatile("" : "+v"(nz_o[j]));
       }
       __builtin_amdgcn_sched_barrier(0);
-      load_normals(q);
+      if constexpr (PRE) load_normals(q);
+      else coop_draw(tau + 1);
     }
 
     float U0 = 0.0f;
@@ -1159,6 +1183,18 @@ __device__ __forceinline__ void rollout_sample(const SolveDesc& d, uint32_t s, b
       ug += 3 * (size_t)S_pad;
     }
     if (in_lds) {
+      // the reads made ahead are awaited before the writes, not with them
+      asm volatile("" : "+v"(un.x), "+v"(un.y), "+v"(un.z));
+      if constexpr (kFromRun) {
+#pragma unroll
+        for (int k = 0; k < 3; ++k) asm volatile("" : "+v"(nx_in[0][k]));
+        if constexpr (GUIDED) {
+#pragma unroll
+          for (int k = 0; k < NH; ++k) asm volatile("" : "+v"(nx_h[0][k]));
+#pragma unroll
+          for (int j = 0; j < NSL; ++j) asm volatile("" : "+v"(nx_o[0][j]));
+        }
+      }
       // every lane of the sample writes the same values to its column; the
       // column of a sample past S is never weighted
       lds_put(su, uj);
@@ -1186,19 +1222,27 @@ __device__ __forceinline__ void rollout_sample(const SolveDesc& d, uint32_t s, b
     return rc;
   };
   uint32_t tau = 0;
-  if constexpr (PRE) {
+  if constexpr (PRE || kFromRun) {
     // whole pairs, then an odd last step: every pass of the loop issues both
     // slots' refills, so a step's wait for its own slot leaves the other
     // slot's loads in flight; G is even, so only the pair's second step can
-    // complete a run of G kept steps
+    // complete a run of G kept steps (and a run of drawn steps is even too)
     // (tested at the bottom: with the test at the top the compiler keeps two
     // copies of the state and moves one into the other in every pass)
     const uint32_t T2 = T & ~1u;
     if (T2 != 0) {
       do {
         step(tau, std::integral_constant<int, 0>{});
-        step(tau + 1, std::integral_constant<int, 1>{});
+        step(tau + 1, std::integral_constant<int, PF - 1>{});
         tau += 2;
+        if constexpr (kFromRun) {
+          // the next run (the step read ahead past the end of one is unused)
+          if (tau == run_end && tau != T) {
+            run_end = next_run(tau);
+            nrm = s_nrm + t_local * run_stride<NOB, GUIDED>();
+            coop_draw(tau);
+          }
+        }
         if constexpr (kBatchCost) {
           if ((tau & (G - 1)) == 0) {
             const float rc = kept_cost(tau - G);
@@ -1536,21 +1580,22 @@ __device__ __forceinline__ float block_min(float v, float* s_red) {
   for (uint32_t w = 1; w < blockDim.x / 64; ++w) r = fminf(r, lds(s_red + w));
   return r;
 }
-// two sums with one pair of barriers (s_red: 2 x 4 floats), each in the same
+// two sums with one pair of barriers (s_red: two floats per wave), each in the same
 // order as a single block sum
 __device__ __forceinline__ void block_sum2(float& a, float& b, float* s_red) {
+  const uint32_t nw = blockDim.x / 64;
   a = wave_sum(a);
   b = wave_sum(b);
   __syncthreads();
   if ((threadIdx.x & 63) == 0) {
     lds_put(s_red + (threadIdx.x >> 6), a);
-    lds_put(s_red + 4 + (threadIdx.x >> 6), b);
+    lds_put(s_red + nw + (threadIdx.x >> 6), b);
   }
   __syncthreads();
-  float ra = lds(s_red), rb = lds(s_red + 4);
-  for (uint32_t w = 1; w < blockDim.x / 64; ++w) {
+  float ra = lds(s_red), rb = lds(s_red + nw);
+  for (uint32_t w = 1; w < nw; ++w) {
     ra += lds(s_red + w);
-    rb += lds(s_red + 4 + w);
+    rb += lds(s_red + nw + w);
   }
   a = ra;
   b = rb;
@@ -1565,10 +1610,13 @@ __device__ __forceinline__ void put_result(const SolveDesc& d, uint32_t r, uint3
   if (r >= 3) gst(d.u_nom_out + r - 3, U);
   if (r + 3 >= R) gst(d.u_nom_out + r, U);
 }
+__device__ __forceinline__ const float* nominal_in(const SolveDesc& d) {
+  return d.u_nom_in ? d.u_nom_in : reinterpret_cast<const float*>(&d + 1);
+}
 // every cost non-finite: return the nominal sequence, keep the warm start
 __device__ __forceinline__ void put_nominal(const SolveDesc& d, uint32_t R, bool plant, double* s_plant) {
   for (uint32_t r = threadIdx.x; r < R; r += blockDim.x) {
-    const float U = gld(d.u_nom_in + r);
+    const float U = gld(nominal_in(d) + r);
     gst(d.u_new + r, U);
     if (plant && r < 3) lds_put(s_plant + 14 + r, (double)U);
   }
@@ -1862,10 +1910,8 @@ struct TileStart {
   float phi0;
 };
 
-// Stages a tile's instance into LDS: the path window, the nominal inputs and the
-// obstacle rows.  The caller's barrier completes it.
-__device__ __forceinline__ void stage_tile(const SolveDesc& d, float4* s_path, float4* s_unom, ObsL* s_obs,
-                                           TileStart& st) {
+// Where a tile's instance starts, from its descriptor
+__device__ __forceinline__ void tile_start(const SolveDesc& d, TileStart& st) {
   float (&x0)[8] = st.x0;
   if (d.x0_resident) {
 #pragma unroll
@@ -1874,7 +1920,6 @@ __device__ __forceinline__ void stage_tile(const SolveDesc& d, float4* s_path, f
 #pragma unroll
     for (int k = 0; k < 8; ++k) x0[k] = d.x0[k];
   }
-  const float ox = x0[0], oy = x0[1];
   // progress origin: f0 = psi0/ds = k0 + phi0
   const double f0 = (double)x0[7] / (double)d.ds;
   double fk = floor(f0);
@@ -1890,7 +1935,15 @@ __device__ __forceinline__ void stage_tile(const SolveDesc& d, float4* s_path, f
   if (nw > kPathWin) nw = kPathWin;
   st.w0 = w0;
   st.nw = nw;
+}
 
+// Stages a tile's instance into LDS by the block's first bd threads (at least
+// 64): the path window, the nominal inputs and the obstacle rows.  The caller's
+// barrier completes it.
+__device__ __forceinline__ void stage_tile(const SolveDesc& d, float4* s_path, float4* s_unom, ObsL* s_obs,
+                                           const TileStart& st, int bd) {
+  const float ox = st.x0[0], oy = st.x0[1];
+  const int w0 = st.w0, nw = st.nw;
   // stage the obstacle rows (row r: obstacle r % n_objects around footprint
   // disc r / n_objects) and the path window
   if (threadIdx.x < d.n_obs) {
@@ -1929,9 +1982,10 @@ __device__ __forceinline__ void stage_tile(const SolveDesc& d, float4* s_path, f
   // the path window (headings in revolutions) and the nominal inputs, their
   // first loads all issued before the first store (the window's 4 per thread
   // at 256 threads): one memory latency, not one per value a thread stages
-  const int Ti = (int)d.T, bd = (int)blockDim.x, tx = (int)threadIdx.x;
+  const int Ti = (int)d.T, tx = (int)threadIdx.x;
+  const float* un_in = nominal_in(d);
   auto load_un = [&](int tau) __attribute__((always_inline)) {
-    const float* p = d.u_nom_in + 3 * min(tau, Ti - 1);
+    const float* p = un_in + 3 * min(tau, Ti - 1);
     return make_float4(gld(p), gld(p + 1), gld(p + 2), 0.0f);
   };
   const float4 un0 = load_un(tx);
@@ -1949,22 +2003,26 @@ __device__ __forceinline__ void stage_tile(const SolveDesc& d, float4* s_path, f
   for (int tau = tx + bd; tau < Ti; tau += bd) s_unom[tau] = load_un(tau);
 }
 
-// The rollouts of a staged tile of blockDim.x / G samples from s0 on.  Every lane
+// The rollouts of a staged tile from sample s0 on, G threads each.  Every lane
 // runs (lanes past S repeat the last sample and do not store), so the
 // group-wide DPP broadcasts always read active lanes.
-template <int NOB, bool GUIDED, int G, bool PRE>
+struct NoRun {
+  __device__ __forceinline__ uint32_t operator()(uint32_t) const { return 0; }
+};
+template <int NOB, bool GUIDED, int G, int NOISE, typename NextRun = NoRun>
 __device__ __forceinline__ void tile_rollout(const SolveDesc& d, uint32_t s0, const TileStart& st,
                                              const float4* s_path, const float4* s_unom, const ObsL* s_obs,
-                                             float* s_u, uint32_t lds_stride, float* s_J, float* s_nrm) {
+                                             float* s_u, uint32_t lds_stride, float* s_J, float* s_nrm,
+                                             uint32_t run_end = 0, NextRun next_run = NextRun{}) {
   const uint32_t t_local = threadIdx.x / G;
   const uint32_t s_raw = s0 + t_local;
   const int g = (int)(threadIdx.x % G);
   const bool valid = s_raw < d.S;
   const uint32_t s = valid ? s_raw : d.S - 1;
   auto rollout = [&](auto ROWS) __attribute__((always_inline)) {
-    rollout_sample<NOB, GUIDED, G, PRE, decltype(ROWS)::value>(d, s, valid && g == 0, g, st.x0, s_obs, s_path, s_unom,
+    rollout_sample<NOB, GUIDED, G, NOISE, decltype(ROWS)::value>(d, s, valid && g == 0, g, st.x0, s_obs, s_path, s_unom,
                                                               st.w0, st.nw, st.k0, st.phi0, s_u, lds_stride, t_local,
-                                                              s_J, s_nrm);
+                                                              s_J, s_nrm, run_end, next_run);
   };
   if constexpr (GUIDED) {
     if (d.row_kind == kRowsDisc) rollout(std::integral_constant<int, kRowsDisc>{});
@@ -1996,7 +2054,8 @@ void k_rollout(const SolveDesc* __restrict__ desc) {
   const uint32_t s0 = blockIdx.x * per_tile;
   const SolveDesc& d = *desc;
   TileStart st;
-  stage_tile(d, s_path, s_unom, s_obs, st);
+  tile_start(d, st);
+  stage_tile(d, s_path, s_unom, s_obs, st, (int)blockDim.x);
   // fused epilogue: LDS for the tile's applied inputs, costs (+inf where no
   // sample stores), weights, units
   const bool fused = d.fused != 0;
@@ -2012,9 +2071,105 @@ void k_rollout(const SolveDesc* __restrict__ desc) {
     for (uint32_t i = threadIdx.x; i < per_tile; i += blockDim.x) s_J[i] = INFINITY;
   }
   __syncthreads();
-  tile_rollout<NOB, GUIDED, G, PRE>(d, s0, st, s_path, s_unom, s_obs, s_u, lds_stride, s_J,
-                                    reinterpret_cast<float*>(s_nrm));
+  tile_rollout<NOB, GUIDED, G, PRE ? kBuffer : kOwnDraw>(d, s0, st, s_path, s_unom, s_obs, s_u, lds_stride, s_J,
+                                                         reinterpret_cast<float*>(s_nrm));
   if (!fused) return;
+  __syncthreads();
+  tile_epilogue(d, s0, per_tile, s_u, lds_stride, s_J, s_gam, s_mu, s_sig, s_up, s_red, s_trig, &s_flag);
+}
+
+// Rollout of one instance of up to one block per CU: eight lanes per sample on
+// the block's first four waves, one on each SIMD.  The normals of a run of steps
+// (as many as LDS holds: the horizon in one to three runs) are drawn by all eight
+// waves before the first four take the steps: two waves on a SIMD draw in half
+// the time of one, which issues an instruction every 4 cycles where most take 2 of
+// the pipe.  (Four waves that draw while the others take the steps cost the
+// steps more than the draws take apart from them: 49.2 us against 47.2, 8192
+// samples, 50 steps, 8 obstacles.)  The inputs are the launch's arguments, so that
+// an update is one launch.  Measured against the noise kernel's launch and then
+// the rollout's: that update 62.7 -> 57.2 us, 512 samples of 20 steps 40.9 -> 37.8,
+// 5000 of 120 steps without guidance 61.2 -> 54.2, with 8 obstacles 124.0 -> 119.6,
+// 4096 of 60 steps and 32 rows 140 on both sides (its normals take three runs).
+// What bounds it is the chain of steps, 0.6 us each, at one wave a SIMD.
+template <int NOB, bool GUIDED>
+__global__ __launch_bounds__(2 * kMaxBlock) __attribute__((amdgpu_waves_per_eu(2, 2)))
+void k_rollout_drawn(const SolveArgs) {
+  __shared__ float4 s_path[kPathWin];
+  __shared__ float4 s_unom[kInlineSteps + 1];
+  __shared__ ObsL s_obs[BRMPPI_MAX_OBS];
+  __shared__ uint32_t s_flag;
+  __shared__ float s_red[2 * (2 * kMaxBlock / 64)];
+  __shared__ double s_trig[kPlantLds];
+  extern __shared__ float s_dyn[];            // the run's normals, then the fused epilogue's
+  constexpr int G = 8, kStride = run_stride<NOB, GUIDED>();
+  constexpr uint32_t kAhead = 32;             // a multiple of kMaxBlock / kDrawnTile
+  const uint32_t per_tile = kDrawnTile, lds_stride = per_tile + 1;
+  const uint32_t s0 = blockIdx.x * per_tile;
+  // the argument itself, not a copy of it
+  const SolveArgs& a = *(const SolveArgs*)__builtin_amdgcn_kernarg_segment_ptr();
+  const SolveDesc& d = a.d;
+  const uint32_t T = d.T, run = a.run;
+  float* s_nrm = s_dyn;
+  float* s_u = s_dyn + run * (per_tile * kStride);
+  float* s_J = s_u + fused_lds_region(per_tile, T, d.n_wchunk);
+  float* s_gam = s_J + per_tile;
+  float* s_mu = s_gam + per_tile;
+  float* s_sig = s_mu + kGroupUnits;
+  float4* s_up = reinterpret_cast<float4*>(s_sig + kGroupUnits);
+  if (threadIdx.x < per_tile) s_J[threadIdx.x] = INFINITY;
+  // the first four waves stage the tile, its loads in flight while the others
+  // begin to draw
+  const bool rolls = __builtin_amdgcn_readfirstlane(threadIdx.x) < kMaxBlock;
+  TileStart st;
+  if (rolls) {
+    tile_start(d, st);
+    stage_tile(d, s_path, s_unom, s_obs, st, kMaxBlock);
+  }
+  // a run's blocks of four normals, 32 samples each: (step, block) q.  The last
+  // four waves take the first `ahead` of them (8 at a time), then all eight go on.
+  const uint32_t nb = GUIDED ? (5 + d.n_obs + 3) / 4 : 1u, inv_nb = 65536u / nb + 1u;
+  auto draw = [&](uint32_t tau0, uint32_t ahead) __attribute__((always_inline)) -> uint32_t {
+    const uint32_t end = min(tau0 + run, T), n = (end - tau0) * nb;
+    const uint32_t j = threadIdx.x % per_tile, s = min(s0 + j, d.S - 1);
+    constexpr uint32_t kHalf = kMaxBlock / kDrawnTile;
+    uint32_t q = threadIdx.x / per_tile;
+    q = rolls ? ahead + kHalf + q : q - kHalf;
+    // two at a time: their chains of dependent instructions overlap (past the
+    // last one, that one again)
+    while (q < n) {
+      const uint32_t q1 = q + (q < ahead ? kHalf : 2 * kHalf);
+      float e[2][4];
+      uint32_t at[2];
+#pragma unroll
+      for (int k = 0; k < 2; ++k) {
+        const uint32_t qk = min(k ? q1 : q, n - 1);
+        const uint32_t i = (qk * inv_nb) >> 16, b = qk - i * nb;   // qk / nb, exact: qk < 10 * 216
+        uint32_t r[4];
+        philox4x32_10(s, tau0 + i, b, d.instance, d.seed_lo, d.seed_hi, r);
+        box_muller4(r, e[k]);
+        at[k] = (i * per_tile + j) * kStride + 4 * b;
+      }
+#pragma unroll
+      for (int k = 0; k < 2; ++k)
+        lds_put(reinterpret_cast<float4*>(s_nrm + at[k]), make_float4(e[k][0], e[k][1], e[k][2], e[k][3]));
+      q = q1 + (q1 < ahead ? kHalf : 2 * kHalf);
+    }
+    __syncthreads();
+    return end;
+  };
+  uint32_t end = draw(0, kAhead);
+  if (rolls) {
+    tile_rollout<NOB, GUIDED, G, kRuns>(d, s0, st, s_path, s_unom, s_obs, s_u, lds_stride, s_J, s_nrm, end,
+                                        [&](uint32_t tau) __attribute__((always_inline)) {
+                                          __syncthreads();   // the run's normals have been read
+                                          return draw(tau, 0);
+                                        });
+  } else {
+    while (end != T) {
+      __syncthreads();
+      end = draw(end, 0);
+    }
+  }
   __syncthreads();
   tile_epilogue(d, s0, per_tile, s_u, lds_stride, s_J, s_gam, s_mu, s_sig, s_up, s_red, s_trig, &s_flag);
 }
@@ -2048,10 +2203,11 @@ void k_rollout_batch(const SolveDesc* __restrict__ descs, const Tile* __restrict
     const Tile tl = tiles[tix];
     const SolveDesc& d = descs[__builtin_amdgcn_readfirstlane(tl.inst)];
     TileStart st;
-    stage_tile(d, s_path, s_unom, s_obs, st);
+    tile_start(d, st);
+    stage_tile(d, s_path, s_unom, s_obs, st, (int)blockDim.x);
     __syncthreads();
     auto run = [&](auto NOB, auto GUIDED, auto G) __attribute__((always_inline)) {
-      tile_rollout<decltype(NOB)::value, decltype(GUIDED)::value, decltype(G)::value, false>(
+      tile_rollout<decltype(NOB)::value, decltype(GUIDED)::value, decltype(G)::value, kOwnDraw>(
           d, tl.s0, st, s_path, s_unom, s_obs, nullptr, 0, nullptr, s_nrm);
     };
     using std::integral_constant;
@@ -2312,10 +2468,12 @@ __global__ void k_fill_u32(uint32_t* __restrict__ p, uint32_t value, size_t n) {
 // rollout variants: 0 = one lane per sample, in-kernel noise; 1 = one lane,
 // precomputed noise; 2 / 3 / 4 = two / four / eight lanes per sample,
 // precomputed noise; 5 / 6 = two / four lanes per sample, in-kernel noise (the
-// form without a noise buffer of the buckets of 16 / 32 rows; not settable)
+// form without a noise buffer of the buckets of 16 / 32 rows; not settable);
+// 7 = eight lanes, normals from the block's drawing waves (takes the place of 4
+// up to a block per CU; not settable)
 int variant_lanes(int variant) {
-  constexpr int lanes[7] = {1, 1, 2, 4, 8, 2, 4};
-  return variant >= 0 && variant < 7 ? lanes[variant] : 1;
+  constexpr int lanes[8] = {1, 1, 2, 4, 8, 2, 4, 8};
+  return variant >= 0 && variant < 8 ? lanes[variant] : 1;
 }
 bool variant_pre(int variant) { return variant >= 1 && variant <= kMaxVariant; }
 // The in-kernel-noise form of a bucket: at most eight obstacle rows per lane.
@@ -2359,6 +2517,39 @@ hipError_t launch_rollout(int bucket, int variant, const SolveDesc* desc, uint32
     case 8: return launch_variant<8, true>(variant, desc, grid, block, lds, stream);
     case 16: return launch_variant<16, true>(variant, desc, grid, block, lds, stream);
     case 32: return launch_variant<32, true>(variant, desc, grid, block, lds, stream);
+    default: return hipErrorInvalidValue;
+  }
+}
+
+template <int NOB, bool GD>
+static hipError_t launch_drawn_t(const SolveArgs& args, uint32_t grid, size_t lds, hipStream_t stream) {
+  hipLaunchKernelGGL((k_rollout_drawn<NOB, GD>), dim3(grid), dim3(2 * kMaxBlock), lds, stream, args);
+  return hipGetLastError();
+}
+
+// steps of a run: the horizon in equal runs of an even length, each within what the block's other
+// uses leave of the CU's LDS
+static uint32_t drawn_run(int bucket, uint32_t T, size_t lds, size_t* run_lds) {
+  constexpr size_t kStatic = 24 * 1024;   // path window, nominal inputs, obstacle rows
+  const size_t step = sizeof(float) * kDrawnTile * (4 * (size_t)(bucket == 0 ? 1 : (5 + bucket + 3) / 4) + 4);
+  const size_t room = kCuLds - kStatic - lds;
+  const uint32_t most = (uint32_t)(room / step) & ~1u, runs = (T + most - 1) / most, run = ((T + runs - 1) / runs + 1) & ~1u;
+  *run_lds = run * step;
+  return run;
+}
+
+hipError_t launch_rollout_drawn(int bucket, SolveArgs& args, uint32_t grid, size_t lds, hipStream_t stream) {
+  if (args.d.T > kInlineSteps || args.d.S > grid * kDrawnTile || lds > kFusedLdsMax || !args.d.fused)
+    return hipErrorInvalidValue;
+  size_t run_lds = 0;
+  args.run = drawn_run(bucket, args.d.T, lds, &run_lds);
+  lds += run_lds;
+  switch (bucket) {
+    case 0: return launch_drawn_t<0, false>(args, grid, lds, stream);
+    case 2: return launch_drawn_t<2, true>(args, grid, lds, stream);
+    case 8: return launch_drawn_t<8, true>(args, grid, lds, stream);
+    case 16: return launch_drawn_t<16, true>(args, grid, lds, stream);
+    case 32: return launch_drawn_t<32, true>(args, grid, lds, stream);
     default: return hipErrorInvalidValue;
   }
 }

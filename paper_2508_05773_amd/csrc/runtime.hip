@@ -322,6 +322,7 @@ struct brmppi_ctx {
   LaunchShape forced{0, 0};     // block 0 = not forced
   Block counters_blk;           // BatchCounters per stream + spare
   BatchCounters* counters = nullptr;
+  uint32_t* drawn_ctr = nullptr;   // completion counters of k_rollout_drawn (zero again when it ends)
 
   // blocking-path scratch (cached; re-allocated only when a call needs more)
   Block scratch;
@@ -517,17 +518,6 @@ void fill_desc(SolveDesc& d, const brmppi_problem& p, const Controller& c, const
   d.row_kind = footprint_is_rear_axle(d.prm) ? kind : (uint32_t)kRowsDisc;
 }
 
-// launch shape of a plain (single-instance) rollout
-LaunchShape plain_shape(brmppi_ctx* ctx, const brmppi_problem& p) {
-  const int bucket = bucket_for(obstacle_rows(ctx, p), p.flags);
-  LaunchShape s = ctx->forced.block ? ctx->forced : ctx->shape[bucket_index(bucket)][s_class(p.S)];
-  if (s.block == 0) s = default_shape(bucket, p.S, (p.flags & BRMPPI_COLLISION_PENALTY) != 0);
-  const size_t noise = (size_t)normals_per_step(ctx, p) * p.T * round_up(p.S, 256) * sizeof(float);
-  if (variant_pre(s.variant) && noise > std::min(kMaxNoiseBytes, ctx->arena.size() / 2))
-    s.variant = variant_in_kernel(bucket);
-  return s;
-}
-
 // dynamic LDS of the fused epilogue for a plain launch, 0 when the tiles are
 // not whole units or do not fit (k_reduce then reduces from HBM)
 size_t fused_lds(const brmppi_problem& p, const LaunchShape& sh) {
@@ -535,6 +525,29 @@ size_t fused_lds(const brmppi_problem& p, const LaunchShape& sh) {
   if (!fused_tile_ok(per_tile)) return 0;
   const size_t b = fused_lds_bytes(per_tile, p.T, (p.S + kWChunk - 1) / kWChunk);
   return b <= kFusedLdsMax ? b : 0;
+}
+
+// Whether k_rollout_drawn takes the place of the noise kernel and the rollout of
+// eight lanes: up to a block per CU (a second one on a CU would wait for the
+// first's LDS), tiles that reduce themselves, a horizon whose nominal sequence
+// fits the launch's arguments.  It is 3 to 7 us faster there, a launch and the wait
+// between the two.
+constexpr uint32_t kDrawnBlocks = 256;   // eight groups at most
+bool drawn_fits(const brmppi_ctx* ctx, const LaunchShape& s, uint32_t S, uint32_t T, size_t lds) {
+  return s.variant == 4 && s.block == 256 && S <= kDrawnTile * std::min<uint32_t>(ctx->n_cu, kDrawnBlocks) &&
+         T <= kInlineSteps && lds > 0;
+}
+
+// launch shape of a plain (single-instance) rollout
+LaunchShape plain_shape(brmppi_ctx* ctx, const brmppi_problem& p) {
+  const int bucket = bucket_for(obstacle_rows(ctx, p), p.flags);
+  LaunchShape s = ctx->forced.block ? ctx->forced : ctx->shape[bucket_index(bucket)][s_class(p.S)];
+  if (s.block == 0) s = default_shape(bucket, p.S, (p.flags & BRMPPI_COLLISION_PENALTY) != 0);
+  if (drawn_fits(ctx, s, p.S, p.T, fused_lds(p, s))) s.variant = kDrawnVariant;
+  const size_t noise = (size_t)normals_per_step(ctx, p) * p.T * round_up(p.S, 256) * sizeof(float);
+  if (variant_pre(s.variant) && noise > std::min(kMaxNoiseBytes, ctx->arena.size() / 2))
+    s.variant = variant_in_kernel(bucket);
+  return s;
 }
 
 ScratchLayout plain_layout(const brmppi_ctx* ctx, const brmppi_problem& p, const LaunchShape& sh) {
@@ -598,6 +611,20 @@ int enqueue_noise(brmppi_ctx* ctx, hipStream_t st, const SolveDesc& h, uint32_t 
   if (!h.noise) return fail(BRMPPI_EINVAL, "internal: noise buffer missing");
   const NoiseArgs a{h.noise, stride, (uint64_t)h.seed_hi << 32 | h.seed_lo, h.S_pad, h.n_normals, h.instance};
   return timed(ctx, st, 4, [&] { return launch_noise(a, count, h.T, up, st); });
+}
+
+// An update by k_rollout_drawn: its inputs as the launch's arguments, the nominal
+// sequence among them when the caller gives one.
+int enqueue_drawn(brmppi_ctx* ctx, hipStream_t st, SolveArgs& a, const float* u_nom, size_t lds) {
+  if (u_nom) {
+    a.d.u_nom_in = nullptr;
+    std::memcpy(a.unom, u_nom, sizeof(float) * 3 * a.d.T);
+  }
+  const uint32_t grid = (a.d.S + kDrawnTile - 1) / kDrawnTile;
+  const int rc = timed(ctx, st, 0, [&] { return launch_rollout_drawn((int)a.d.bucket, a, grid, lds, st); });
+  // normals drawn apart from the rollout's lanes, in no time of their own
+  if (!rc && !ctx->no_events && (ctx->flags & (BRMPPI_CTX_PROFILE | BRMPPI_CTX_PROFILE_ROLLOUT))) ctx->prof.n[4] += 1.0;
+  return rc;
 }
 
 Upload upload(const char* src, char* dst, size_t bytes) { return Upload{src, dst, (bytes + 15) / 16}; }
@@ -683,7 +710,8 @@ int solve_locked(brmppi_ctx* ctx, const brmppi_problem* p, const brmppi_outputs*
   const ScratchLayout L = plain_layout(ctx, *p, sh);
   // device: [scratch | input block]
   const size_t lds = fused_lds(*p, sh);
-  const InputBlock IB = input_block(p->T, p->u_nom != nullptr, L.n_wchunk);
+  const bool drawn = sh.variant == kDrawnVariant;   // the inputs are the launch's arguments
+  const InputBlock IB = drawn ? InputBlock{} : input_block(p->T, p->u_nom != nullptr, L.n_wchunk);
   const size_t in_off = L.bytes;
   const size_t need = in_off + round_up(IB.bytes, 256);
   // pinned: [input block | stats, sequence | costs | two pieces of the sequences];
@@ -713,20 +741,27 @@ int solve_locked(brmppi_ctx* ctx, const brmppi_problem* p, const brmppi_outputs*
   float* pin_out = reinterpret_cast<float*>(pin + out_off);
   float* pin_J = reinterpret_cast<float*>(pin + J_off);
 
-  fill_desc(*h_desc, *p, c, L, base, 0, reinterpret_cast<const float*>(base + in_off + IB.unom),
-            reinterpret_cast<uint32_t*>(base + in_off + IB.counter), pin_out, lds > 0, out->useq_out != nullptr);
-  if (J_direct) h_desc->J = pin_J;
-  std::memset(pin + IB.counter, 0, IB.unom - IB.counter);
-  if (p->u_nom) std::memcpy(pin + IB.unom, p->u_nom, sizeof(float) * 3 * p->T);
-  const Upload up = upload(pin, base + in_off, IB.bytes);
   ctx->no_events = fixed != nullptr;
-  if (variant_pre(sh.variant)) {
-    rc = enqueue_noise(ctx, s, *h_desc, 1, 0, up);
+  if (drawn) {
+    SolveArgs a;
+    fill_desc(a.d, *p, c, L, base, 0, nullptr, ctx->drawn_ctr, pin_out, true, out->useq_out != nullptr);
+    if (J_direct) a.d.J = pin_J;
+    rc = enqueue_drawn(ctx, s, a, p->u_nom, lds);
   } else {
-    const hipError_t e = launch_upload(up, s);
-    rc = e == hipSuccess ? 0 : fail(BRMPPI_EDEVICE, std::string("upload: ") + hipGetErrorString(e));
+    fill_desc(*h_desc, *p, c, L, base, 0, reinterpret_cast<const float*>(base + in_off + IB.unom),
+              reinterpret_cast<uint32_t*>(base + in_off + IB.counter), pin_out, lds > 0, out->useq_out != nullptr);
+    if (J_direct) h_desc->J = pin_J;
+    std::memset(pin + IB.counter, 0, IB.unom - IB.counter);
+    if (p->u_nom) std::memcpy(pin + IB.unom, p->u_nom, sizeof(float) * 3 * p->T);
+    const Upload up = upload(pin, base + in_off, IB.bytes);
+    if (variant_pre(sh.variant)) {
+      rc = enqueue_noise(ctx, s, *h_desc, 1, 0, up);
+    } else {
+      const hipError_t e = launch_upload(up, s);
+      rc = e == hipSuccess ? 0 : fail(BRMPPI_EDEVICE, std::string("upload: ") + hipGetErrorString(e));
+    }
+    if (!rc) rc = enqueue_rollout_reduce(ctx, s, d_desc, *p, L, sh, lds);
   }
-  if (!rc) rc = enqueue_rollout_reduce(ctx, s, d_desc, *p, L, sh, lds);
   ctx->no_events = false;
   if (rc) {
     (void)hipStreamSynchronize(s);   // nothing of this call may still run on the scratch
@@ -1089,6 +1124,7 @@ int closed_loop_locked(brmppi_ctx* ctx, const brmppi_problem* p0, uint32_t n_up,
   // normals on a second stream while a chunk runs was measured slower: the
   // noise waves delay the rollout's, each of which is on the critical path of
   // its update.)
+  const bool drawn = sh.variant == kDrawnVariant;   // the inputs are each launch's arguments
   const bool pre = variant_pre(sh.variant);
   const size_t noise_bytes = pre ? round_up((size_t)L.n_normals * p.T * L.S_pad * sizeof(float), 256) : 0;
   uint32_t C = kLoopChunk;
@@ -1151,7 +1187,15 @@ int closed_loop_locked(brmppi_ctx* ctx, const brmppi_problem* p0, uint32_t n_up,
     const uint32_t k0 = j * C, cnt = std::min(C, n_up - k0);
     char* hp = half_pin(h);
     char* hd = half_dev(h);
-    for (uint32_t i = 0; i < cnt; ++i) {
+    if (drawn) {
+      for (uint32_t i = 0; i < cnt; ++i) {
+        SolveArgs a;
+        fill_desc(a.d, p, c, L, base, k0 + i, nullptr, ctx->drawn_ctr, d_out, true, false);
+        if (logs) a.d.log = reinterpret_cast<double*>(hd + desc_bytes * C) + kLogRecord * i;
+        if ((rc = enqueue_drawn(ctx, s, a, k0 + i == 0 ? p.u_nom : nullptr, lds))) return rc;
+      }
+    }
+    for (uint32_t i = 0; i < cnt && !drawn; ++i) {
       const uint32_t k = k0 + i;
       SolveDesc* d = reinterpret_cast<SolveDesc*>(hp + desc_bytes * i);
       // only the first update reads the caller's sequence; later ones the shifted result
@@ -1164,13 +1208,15 @@ int closed_loop_locked(brmppi_ctx* ctx, const brmppi_problem* p0, uint32_t n_up,
     // the chunk's descriptors, with the first chunk the head before them
     const size_t head = j == 0 ? half_rel : 0;
     const Upload up = upload(hp - head, hd - head, head + desc_bytes * cnt);
-    if (pre) {
+    if (drawn) {
+      // nothing to upload
+    } else if (pre) {
       const SolveDesc& first = *reinterpret_cast<const SolveDesc*>(hp);
       if ((rc = enqueue_noise(ctx, s, first, cnt, noise_bytes / sizeof(float), up))) return rc;
     } else {
       HIPCHK(launch_upload(up, s));
     }
-    for (uint32_t i = 0; i < cnt; ++i)   // each with its plant step
+    for (uint32_t i = 0; i < cnt && !drawn; ++i)   // each with its plant step
       if ((rc = enqueue_rollout_reduce(ctx, s, reinterpret_cast<const SolveDesc*>(hd + desc_bytes * i), p, L, sh, lds)))
         return rc;
     if (logs)
@@ -1358,9 +1404,11 @@ int brmppi_create(const brmppi_config* cfg, brmppi_ctx** out) {
   for (uint32_t k = 0; k < cfg->n_streams; ++k)
     if (int rc = ctx->slot_pin[k].ensure(kPinnedInit)) return rc;
   for (auto& e : ctx->loop_ev) HIPCHK(hipEventCreateWithFlags(&e, hipEventDisableTiming));
-  ctx->counters_blk = ctx->arena.alloc(sizeof(BatchCounters) * 5);
+  const size_t ctr_bytes = round_up(sizeof(BatchCounters) * 5, 256) + counter_bytes(kDrawnBlocks * kDrawnTile / kWChunk);
+  ctx->counters_blk = ctx->arena.alloc(ctr_bytes);
   if (!ctx->counters_blk.ptr) return fail(BRMPPI_ENOMEM, "arena too small");
   ctx->counters = reinterpret_cast<BatchCounters*>(ctx->counters_blk.ptr);
+  ctx->drawn_ctr = reinterpret_cast<uint32_t*>(ctx->counters_blk.ptr + round_up(sizeof(BatchCounters) * 5, 256));
   {
     // one staging-sized copy each way before the counters are cleared: the
     // runtime hands copies above a few KB to a DMA engine whose first use in a
@@ -1371,8 +1419,7 @@ int brmppi_create(const brmppi_config* cfg, brmppi_ctx** out) {
     hipError_t e = hipMemcpyAsync(cfg->arena, ctx->pin.ptr, cb, hipMemcpyHostToDevice, ctx->streams[0]);
     if (e == hipSuccess) e = hipMemcpyAsync(ctx->pin.ptr, cfg->arena, cb, hipMemcpyDeviceToHost, ctx->streams[0]);
     if (e == hipSuccess)
-      e = launch_fill_u32(reinterpret_cast<uint32_t*>(ctx->counters), 0u, sizeof(BatchCounters) * 5 / 4,
-                          ctx->streams[0]);
+      e = launch_fill_u32(reinterpret_cast<uint32_t*>(ctx->counters), 0u, ctr_bytes / 4, ctx->streams[0]);
     if (e == hipSuccess) e = hipStreamSynchronize(ctx->streams[0]);
     if (e != hipSuccess) return fail(BRMPPI_EDEVICE, std::string("context init: ") + hipGetErrorString(e));
   }
@@ -1737,8 +1784,12 @@ int brmppi_autotune(brmppi_ctx* ctx) {
           h.ustar_global = lds ? 0u : 1u;
           HIPCHK(hipMemcpy(d_desc, &h, sizeof(h), hipMemcpyHostToDevice));
           const uint32_t nr = L.n_wchunk * L.n_rgroup;
+          SolveArgs args;
+          args.d = h;
+          const bool drawn = drawn_fits(ctx, LaunchShape{block, variant}, S, T, lds);
           auto run = [&]() -> hipError_t {
             hipError_t e = hipSuccess;
+            if (drawn) return launch_rollout_drawn(bucket, args, grid, lds, s);
             if (variant_pre(variant)) e = launch_noise(NoiseArgs{h.noise, 0, 0, L.S_pad, K, 0}, 1, T, Upload{}, s);
             if (e == hipSuccess)
               e = launch_rollout(bucket, variant, d_desc, grid, block, lds, s);

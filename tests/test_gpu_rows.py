@@ -143,3 +143,25 @@ def test_downloads_in_pieces(ctx, S, T):
     assert np.max(np.abs(got["J"] - want["J"]) / np.abs(want["J"])) <= J_RTOL
     assert np.all(np.abs(got["useq"].reshape(T, 3, S).transpose(2, 0, 1) - want["useq"]) <= tol)
     assert np.array_equal(only["J"], got["J"])
+
+
+@pytest.mark.parametrize("n_obs", [0, 2, 8, 16, 32])
+def test_normals_drawn_in_runs(ctx, n_obs):
+    """Eight lanes per sample with the normals drawn by the rollout's launch, as
+    many steps at a time as LDS holds: one step, an odd last step, one to several
+    runs, the longest horizons that it takes and the first that it leaves to the
+    noise kernel, a partial tile, the largest sample count and the first above
+    it.  Bit for bit the four-lane form with the noise kernel."""
+    for S, T in ((1, 1), (33, 2), (65, 11), (100, 24), (100, 25), (100, 49), (100, 50), (64, 155), (64, 156), (64, 217), (8191, 3), (8193, 3)):
+        p = problem("moving", n_obs).copy(S=S, T=T, u_nom=np.full((T, 3), 0.1, np.float32))
+        ctx.set_path(0, p.path, p.ds)
+        print(f"  n_obs={n_obs} S={S} T={T}", flush=True)
+        got = []
+        for shape in ((256, 4), (256, 3)):
+            B.brmppi_set_launch(ctx.h, *shape)
+            try:
+                got.append(B.brmppi_solve_ex(ctx.h, B.ProblemBuffers(p, controller=0), want_J=True))
+            finally:
+                B.brmppi_set_launch(ctx.h, 0, 0)
+        assert np.array_equal(got[0]["J"], got[1]["J"])
+        assert np.array_equal(got[0]["U_new"], got[1]["U_new"])
