@@ -263,10 +263,11 @@ struct RowTerms {
   float L, P, Q;
 };
 
-// guarded barrier: copysign(max(|hhat|, h_eps), hhat) with 0 -> +h_eps
+// guarded barrier: copysign(max(|hhat|, h_eps), hhat) with 0 -> +h_eps (hhat is
+// a sum whose zero is an exact cancellation, +0).  The NaN-propagating maximum: a
+// NaN stays one, and its sample's cost is then non-finite.
 __device__ __forceinline__ float barrier_rcp(float hhat, float h_eps) {
-  const float g = sel(hhat < 0.0f, -h_eps, h_eps);
-  return rcp(sel(fabsf(hhat) < h_eps, g, hhat));
+  return rcp(copysignf(__builtin_elementwise_maximum(fabsf(hhat), h_eps), hhat));
 }
 
 // Row sums of the 2x2 normal equations of the eliminated projection,
