@@ -783,7 +783,16 @@ __device__ __forceinline__ void rollout_sample(const SolveDesc& d, uint32_t s, b
   const bool hitch = !(d.flags & BRMPPI_HITCH_OFF);
   const bool penalty = (d.flags & BRMPPI_COLLISION_PENALTY) != 0;
   const int nb = GUIDED ? (5 + n_obs + 3) / 4 : 1;
-  const float ox = x0[0], oy = x0[1];
+  float ox = x0[0], oy = x0[1];
+  if constexpr (NOISE == kOwnDraw) {
+    // uniform in the block: to scalar registers in the forms whose vector registers
+    // spill (64 instances 707 -> 685 us)
+    ox = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(ox)));
+    oy = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(oy)));
+    k0 = __builtin_amdgcn_readfirstlane(k0);
+    w0 = __builtin_amdgcn_readfirstlane(w0);
+    nw = __builtin_amdgcn_readfirstlane(nw);
+  }
   const float4* __restrict__ gpath = d.path;
   const int n_path = (int)d.n_path;
   const int hk0 = (G == 1) ? 0 : (g & 1);    // first hitch row of this lane
