@@ -8,6 +8,8 @@
 //               (eqs. (13)-(15)) accumulated; writes the applied inputs
 //               [3T][S] and the cost of every sample.  One or several lanes
 //               per sample; noise drawn in the kernel or read from k_noise.
+//               k_rollout_drawn: up to 8192 samples, the update's only launch;
+//               k_rollout_batch: the tiles of a batch from one queue.
 //   k_reduce  : weights exp(-(J - m)/lambda) (Sec. III-B) and the weighted
 //               average of the applied inputs (eq. (5)) from HBM, in units of
 //               32 samples and groups of 32 units merged by log-sum-exp; the
@@ -239,10 +241,10 @@ __device__ __forceinline__ RefPoint reference(float f, int k0, int n_path, const
 // carries the full state; obstacle o's barrier row is computed by group lane
 // o % G, and the rows' projection terms are summed over the group by DPP
 // butterflies in a canonical tree of eight virtual lanes (below), so that
-// every lane ends with the same sums, bit for bit, as a one-lane sample.  With PRE the
-// normals come from the noise buffer filled by k_noise (same Philox and
-// Box-Muller code) instead of being drawn in the rollout.  Results are
-// therefore bitwise identical for every (G, PRE) and block size.
+// every lane ends with the same sums, bit for bit, as a one-lane sample.  The normals
+// are drawn in the rollout or come from the noise buffer filled by k_noise or from
+// a run of steps drawn into LDS (the same Philox and Box-Muller code).  Results are
+// therefore bitwise identical for every G, source of normals and block size.
 //
 // What bounds the step is the number of instructions, of any kind: a wave
 // issues at most one every 4 cycles (transcendentals 8), and with one wave per
@@ -252,9 +254,9 @@ __device__ __forceinline__ RefPoint reference(float f, int k0, int n_path, const
 // gradient-by-gradient expansion of eq. (17): about 290 instructions a step in
 // the eight-lane form with one row per lane, where the expansion took 430.
 // Measured with it, before -> now: closed-loop update of 8192 samples, 50
-// steps, 8 ellipses 63.7 -> 53.1 us; solve of 65536 samples, 100 steps, 32
-// ellipses 1038 -> 658 us; of 5000 samples, 120 steps, 7 super-ellipses 168 ->
-// 129 us.
+// steps, 8 ellipses 63.7 -> 53.1 us (46.2 since); solve of 65536 samples, 100 steps, 32
+// ellipses 1038 -> 658 us (610 since); of 5000 samples, 120 steps, 7 super-ellipses 168 ->
+// 129 us (117 since).
 
 // One row of eq. (9), divided by its guarded barrier value hh and with the
 // inputs' scale factors left out: u^alpha = -(L + P U0 + Q U1) - alpha with
@@ -1829,9 +1831,6 @@ __device__ __forceinline__ void group_merge(const SolveDesc& d, uint32_t gu0, ui
   }
 }
 
-// Fused reduction of one tile (its samples' costs and applied inputs are in
-// LDS): unit weights, unit partials to HBM; the last tile of each group merges
-// the group, the last group the instance (U_new, shift, plant step).
 // Waves per SIMD the register allocation must leave room for.  Up to 16
 // obstacle slots every launch shape fits two waves (the one-lane forms with a
 // few spilled values, which still pays: at one wave per SIMD nothing hides the
@@ -1843,6 +1842,9 @@ constexpr int rollout_waves_per_simd() {
   return (NOB <= 16 || G >= 4) ? 2 : 1;
 }
 
+// Fused reduction of one tile (its samples' costs and applied inputs are in
+// LDS): unit weights, unit partials to HBM; the last tile of each group merges
+// the group, the last group the instance (U_new, shift, plant step).
 // Inlined into the kernel: as a function call, every lane saved and restored
 // its callee-saved registers around it (tens of bytes of scratch per lane).
 __device__ __forceinline__ void tile_epilogue(const SolveDesc& d, uint32_t s0, uint32_t per_tile, float* s_u, uint32_t lds_stride,
@@ -2198,8 +2200,8 @@ void k_rollout_drawn(const SolveArgs) {
 // instruction on vector registers, 4 per FP64, comparison or scalar-operand
 // one, 8 per transcendental), 80 % of the launch.  Measured, launch per bucket
 // -> this: 64 instances (1024 to 16384 samples, 20 to 80 steps, up to 16
-// obstacles) 765 -> 745 us a call, 48 served requests (up to 32768 samples, 100
-// steps, 32 obstacles) 2813 -> 2125 us.
+// obstacles) 765 -> 745 us a call (687 since), 48 served requests (up to 32768
+// samples, 100 steps, 32 obstacles) 2813 -> 2125 us (2032 since).
 __global__ __launch_bounds__(kMaxBlock) __attribute__((amdgpu_waves_per_eu(2, 8)))
 void k_rollout_batch(const SolveDesc* __restrict__ descs, const Tile* __restrict__ tiles, uint32_t n_tiles,
                      BatchCounters* __restrict__ ctr) {

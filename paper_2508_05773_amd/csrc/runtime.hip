@@ -266,7 +266,8 @@ struct HipServed {
 
 // rollout launch shape: block size and variant (0 = one lane per sample,
 // in-kernel noise; 1 = one lane, precomputed noise; 2 / 3 / 4 = two / four /
-// eight lanes per sample, precomputed noise).  No shape changes any result bit.
+// eight lanes per sample, precomputed noise; 5 .. 7 chosen here, not settable: see
+// variant_in_kernel and drawn_fits).  No shape changes any result bit.
 struct LaunchShape {
   uint32_t block = 0;    // 0: not set
   int variant = 0;
@@ -724,8 +725,12 @@ int solve_locked(brmppi_ctx* ctx, const brmppi_problem* p, const brmppi_outputs*
   const size_t pin_need = piece_off + (rows_out ? 2 * kPieceBytes : 0);
   char* base;
   if (fixed) {
-    if (need > fixed_bytes)
-      return fail(BRMPPI_ENOMEM, "the update needs " + std::to_string(need) + " bytes of scratch, more than the " +
+    // the limit is the one the interface states, normals included, also where the
+    // rollout draws its own
+    const size_t asked = !drawn ? need : scratch_layout(p->S, p->T, normals_per_step(ctx, *p)).bytes +
+                                             round_up(input_block(p->T, p->u_nom != nullptr, L.n_wchunk).bytes, 256);
+    if (asked > fixed_bytes)
+      return fail(BRMPPI_ENOMEM, "the update needs " + std::to_string(asked) + " bytes of scratch, more than the " +
                                      std::to_string(fixed_bytes) + " of the static scratch");
     if (pin_need > ctx->pin.bytes) return fail(BRMPPI_ENOMEM, "inputs larger than the pinned staging buffer");
     base = fixed;
@@ -800,7 +805,7 @@ struct BatchPlan {
   std::vector<size_t> unom_off;      // offset of each caller nominal sequence (header), or 0
   std::vector<size_t> out_pos;       // float offset of each [stats(4) | u_new(3T)] in the outputs
   // block layout: header [descs | tiles | ritems | nominals | counters]
-  // (one upload), outputs (one download), then every instance's scratch
+  // (one upload), then every instance's scratch; the outputs go to pinned memory
   size_t off_descs = 0, off_tiles = 0, off_ritems = 0, off_counters = 0, header_bytes = 0;
   size_t out_floats = 0, total = 0;
   uint32_t block = 256;              // of the rollout launch

@@ -165,3 +165,13 @@ def test_normals_drawn_in_runs(ctx, n_obs):
                 B.brmppi_set_launch(ctx.h, 0, 0)
         assert np.array_equal(got[0]["J"], got[1]["J"])
         assert np.array_equal(got[0]["U_new"], got[1]["U_new"])
+
+
+def test_noalloc_limit_counts_the_normals(ctx):
+    """The scratch limit of the allocation-free solve is the stated one, normals
+    included, whichever launch draws them."""
+    for T, rc_want in ((30, B.OK), (100, B.ENOMEM)):
+        p = problem("rest", 32).copy(S=8192, T=T, u_nom=np.zeros((T, 3), np.float32))
+        ctx.set_path(0, p.path, p.ds)
+        rc = B.brmppi_solve_noalloc(ctx.h, B.ProblemBuffers(p, controller=0), allow=(B.OK, B.ENOMEM))[2]
+        assert rc == rc_want, T
