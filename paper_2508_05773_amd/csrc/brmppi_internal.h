@@ -105,6 +105,32 @@ hipError_t launch_rollout(int bucket, int variant, const SolveDesc* desc, uint32
 constexpr int kDrawnVariant = 7;
 constexpr uint32_t kDrawnTile = 32;
 hipError_t launch_rollout_drawn(int bucket, SolveArgs& args, uint32_t grid, size_t lds_bytes, hipStream_t stream);
+// Its dynamic LDS: the normals of a run of steps (a slot of kDrawnTile samples a
+// step), the path window, the fused epilogue's `fused` bytes.  A step reads the next
+// one's normals, the last of a run so from the slot past it, whose values are not
+// used: that slot lies in the path window, which is longer than any and not written
+// while the steps run.  The horizon goes in equal runs of an even length, each within
+// what the block's other uses leave of the CU's LDS.
+constexpr uint32_t drawn_slot(int bucket) {   // bytes
+  return 4 * kDrawnTile * (4 * (bucket == 0 ? 1u : (5u + (uint32_t)bucket + 3) / 4) + 4);
+}
+constexpr size_t kDrawnPath = 16 * (size_t)kPathWin;
+constexpr size_t kDrawnStatic = 8 * 1024;   // nominal inputs, obstacle rows, the epilogue's scalars
+static_assert(drawn_slot(BRMPPI_MAX_OBS) <= kDrawnPath, "the slot past a run lies in the path window");
+struct DrawnLds {
+  uint32_t run;                 // steps drawn at a time
+  size_t path, epilogue, bytes; // offsets of the path window and the epilogue; the whole
+};
+inline DrawnLds drawn_lds(int bucket, uint32_t T, size_t fused) {
+  const size_t room = kCuLds - kDrawnStatic - kDrawnPath - fused;
+  const uint32_t most = (uint32_t)(room / drawn_slot(bucket)) & ~1u, runs = (T + most - 1) / most;
+  DrawnLds l;
+  l.run = ((T + runs - 1) / runs + 1) & ~1u;
+  l.path = (size_t)l.run * drawn_slot(bucket);
+  l.epilogue = l.path + kDrawnPath;
+  l.bytes = l.epilogue + fused;
+  return l;
+}
 // the rollouts of a batch's tiles (each of block / variant_lanes(variant_in_kernel(bucket))
 // samples of its instance); grid at most n_tiles
 hipError_t launch_rollout_batch(const SolveDesc* descs, const Tile* tiles, uint32_t n_tiles, BatchCounters* ctr,

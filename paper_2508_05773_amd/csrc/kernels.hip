@@ -1251,7 +1251,8 @@ __device__ __forceinline__ void rollout_sample(const SolveDesc& d, uint32_t s, b
         step(tau + 1, std::integral_constant<int, PF - 1>{});
         tau += 2;
         if constexpr (kFromRun) {
-          // the next run (the step read ahead past the end of one is unused)
+          // the next run (what was read ahead past the end of one, from the path
+          // window, is unused)
           if (tau == run_end && tau != T) {
             run_end = next_run(tau);
             nrm = s_nrm + t_local * run_stride<NOB, GUIDED>();
@@ -2109,13 +2110,14 @@ void k_rollout(const SolveDesc* __restrict__ desc) {
 template <int NOB, bool GUIDED>
 __global__ __launch_bounds__(2 * kMaxBlock) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void k_rollout_drawn(const SolveArgs) {
-  __shared__ float4 s_path[kPathWin];
   __shared__ float4 s_unom[kInlineSteps + 1];
   __shared__ ObsL s_obs[BRMPPI_MAX_OBS];
   __shared__ uint32_t s_flag;
   __shared__ float s_red[2 * (2 * kMaxBlock / 64)];
   __shared__ double s_trig[kPlantLds];
-  extern __shared__ float s_dyn[];            // the run's normals, then the fused epilogue's
+  extern __shared__ float4 s_drawn[];         // as drawn_lds lays it out
+  static_assert(sizeof(s_unom) + sizeof(s_obs) + sizeof(s_flag) + sizeof(s_red) + sizeof(s_trig) + 64 <= kDrawnStatic,
+                "with padding");
   constexpr int G = 8, kStride = run_stride<NOB, GUIDED>();
   constexpr uint32_t kAhead = 32;             // a multiple of kMaxBlock / kDrawnTile
   const uint32_t per_tile = kDrawnTile, lds_stride = per_tile + 1;
@@ -2124,8 +2126,10 @@ void k_rollout_drawn(const SolveArgs) {
   const SolveArgs& a = *(const SolveArgs*)__builtin_amdgcn_kernarg_segment_ptr();
   const SolveDesc& d = a.d;
   const uint32_t T = d.T, run = a.run;
-  float* s_nrm = s_dyn;
-  float* s_u = s_dyn + run * (per_tile * kStride);
+  float* s_nrm = reinterpret_cast<float*>(s_drawn);
+  static_assert(4 * kDrawnTile * kStride == drawn_slot(NOB), "a slot of the run");
+  float4* s_path = reinterpret_cast<float4*>(s_nrm + run * (per_tile * kStride));
+  float* s_u = reinterpret_cast<float*>(s_path + kPathWin);
   float* s_J = s_u + fused_lds_region(per_tile, T, d.n_wchunk);
   float* s_gam = s_J + per_tile;
   float* s_mu = s_gam + per_tile;
@@ -2542,23 +2546,12 @@ static hipError_t launch_drawn_t(const SolveArgs& args, uint32_t grid, size_t ld
   return hipGetLastError();
 }
 
-// steps of a run: the horizon in equal runs of an even length, each within what the block's other
-// uses leave of the CU's LDS
-static uint32_t drawn_run(int bucket, uint32_t T, size_t lds, size_t* run_lds) {
-  constexpr size_t kStatic = 24 * 1024;   // path window, nominal inputs, obstacle rows
-  const size_t step = sizeof(float) * kDrawnTile * (4 * (size_t)(bucket == 0 ? 1 : (5 + bucket + 3) / 4) + 4);
-  const size_t room = kCuLds - kStatic - lds;
-  const uint32_t most = (uint32_t)(room / step) & ~1u, runs = (T + most - 1) / most, run = ((T + runs - 1) / runs + 1) & ~1u;
-  *run_lds = run * step;
-  return run;
-}
-
 hipError_t launch_rollout_drawn(int bucket, SolveArgs& args, uint32_t grid, size_t lds, hipStream_t stream) {
   if (args.d.T > kInlineSteps || args.d.S > grid * kDrawnTile || lds > kFusedLdsMax || !args.d.fused)
     return hipErrorInvalidValue;
-  size_t run_lds = 0;
-  args.run = drawn_run(bucket, args.d.T, lds, &run_lds);
-  lds += run_lds;
+  const DrawnLds l = drawn_lds(bucket, args.d.T, lds);
+  args.run = l.run;
+  lds = l.bytes;
   switch (bucket) {
     case 0: return launch_drawn_t<0, false>(args, grid, lds, stream);
     case 2: return launch_drawn_t<2, true>(args, grid, lds, stream);
