@@ -15,7 +15,7 @@ CSRC = os.path.join(HERE, "csrc")
 INCLUDE = os.path.join(ROOT, "include")
 LIB = os.path.join(HERE, "libbrmppi.so")
 SOURCES = ["kernels.hip", "runtime.hip"]
-HEADERS = ["brmppi_internal.h", "served_core.h"]
+HEADERS = ["brmppi_internal.h", "launch_plan.h", "served_core.h"]
 
 ARCH = os.environ.get("BRMPPI_ARCH", "gfx950")
 

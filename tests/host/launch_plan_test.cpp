@@ -1,11 +1,12 @@
 // CPU test of the rules by which the host prepares a launch
-// (paper_2508_05773_amd/csrc/brmppi_internal.h), over all the sizes that they
+// (paper_2508_05773_amd/csrc/launch_plan.h, brmppi_internal.h), over all the sizes that they
 // accept.  Built and run by tests/test_launch_plan_host.py under AddressSanitizer +
 // UndefinedBehaviorSanitizer.
 #include <cstdio>
 #include <cstdlib>
+#include <vector>
 
-#include "brmppi_internal.h"
+#include "launch_plan.h"
 
 using namespace brm;
 
@@ -47,8 +48,43 @@ static void drawn_reads_in_range() {
   }
 }
 
+// a one-disc parameter set
+static brmppi_params rear_axle() {
+  brmppi_params P{};
+  P.n_disc_tractor = 1;
+  return P;
+}
+
+// The update that the launch shapes are timed on: every row that the kernels stage
+// (obstacle r % n_objects around disc r / n_objects) is one that its descriptor has.
+static void tune_update_rows() {
+  const brmppi_params P = rear_axle();
+  std::vector<char> mem(1 << 18);
+  for (int bucket : {0, 2, 8, 16, 32}) {
+    const TuneUpdate t(bucket, 64, 4, P);
+    const ScratchLayout L = scratch_layout(64, 4, bucket ? 5 + bucket : 3);
+    CHECK(L.bytes <= mem.size());
+    Resident c;
+    uint32_t counter[2 * kCtrStride] = {};
+    float out[4 + 12], unom[12] = {};
+    c.unom = unom;
+    c.ds = 0.1f;
+    SolveDesc d;
+    fill_desc(d, t.p, c, L, mem.data(), 0, nullptr, counter, out, true, false);
+    CHECK(d.n_obs == (uint32_t)bucket && d.n_objects == (uint32_t)bucket);
+    CHECK(d.bucket == (uint32_t)bucket && d.row_kind == kRowsStatic);
+    CHECK(d.u_nom_in == unom && d.noise && d.gctr == counter + kCtrStride);
+    for (uint32_t r = 0; r < d.n_obs; ++r) {
+      CHECK(r / d.n_objects < n_discs(d.prm));
+      const brmppi_obstacle& o = d.obs[r % d.n_objects];
+      CHECK(o.mx > 0 && o.my > 0 && (o.e == 2.0f || o.e == 4.0f));
+    }
+  }
+}
+
 int main() {
   drawn_reads_in_range();
+  tune_update_rows();
   std::printf("launch plan: all checks passed\n");
   return 0;
 }

@@ -1,4 +1,4 @@
-"""The host's launch rules (csrc/brmppi_internal.h), built for the CPU and checked
+"""The host's launch rules (csrc/launch_plan.h, csrc/brmppi_internal.h), built for the CPU and checked
 over all the sizes that they accept (tests/host/launch_plan_test.cpp lists the
 checks), under AddressSanitizer + UndefinedBehaviorSanitizer."""
 import os
