@@ -88,14 +88,26 @@ struct alignas(16) BatchCounters {
 };
 
 // Launchers (kernels.hip).  All enqueue on `stream` and return hipError_t.
-// Rollout variant: 0 = one lane per sample with in-kernel noise, 1 = one lane
-// with precomputed noise, 2 / 3 / 4 = two / four / eight lanes per sample
-// with precomputed noise (k_noise must run first).  All variants give bitwise
-// identical results.
-constexpr int kMaxVariant = 4;   // 0: G1 fused noise, 1: G1, 2: G2, 3: G4, 4: G8 (precomputed noise)
-int variant_lanes(int variant);
-bool variant_pre(int variant);
-int variant_in_kernel(int bucket);
+// k_noise must run before a variant with precomputed noise.  All variants give
+// bitwise identical results.
+// rollout variants: 0 = one lane per sample, in-kernel noise; 1 = one lane,
+// precomputed noise; 2 / 3 / 4 = two / four / eight lanes per sample,
+// precomputed noise; 5 / 6 = two / four lanes per sample, in-kernel noise (the
+// form without a noise buffer of the buckets of 16 / 32 rows; not settable);
+// 7 = eight lanes, normals from the block's drawing waves (takes the place of 4
+// up to a block per CU; not settable)
+constexpr int kMaxVariant = 4;   // the last that a caller can set
+inline int variant_lanes(int variant) {
+  constexpr int lanes[8] = {1, 1, 2, 4, 8, 2, 4, 8};
+  return variant >= 0 && variant < 8 ? lanes[variant] : 1;
+}
+inline bool variant_pre(int variant) { return variant >= 1 && variant <= kMaxVariant; }
+// The in-kernel-noise form of a bucket: at most eight obstacle rows per lane.
+// One lane with 16 or 32 rows does not fit the 256 registers that let two
+// waves share a SIMD, and what it spills or loses in occupancy costs more
+// than the state that two or four lanes hold redundantly.
+inline int variant_in_kernel(int bucket) { return bucket == 32 ? 6 : (bucket == 16 ? 5 : 0); }
+
 // lds_bytes > 0: the single instance's tiles reduce themselves (fused epilogue;
 // descs->fused must be set and the tile size a multiple of kUnit)
 hipError_t launch_rollout(int bucket, int variant, const SolveDesc* desc, uint32_t grid, uint32_t block,

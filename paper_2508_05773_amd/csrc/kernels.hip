@@ -2484,23 +2484,6 @@ __global__ void k_fill_u32(uint32_t* __restrict__ p, uint32_t value, size_t n) {
 // ---------------------------------------------------------------------------
 // launchers
 // ---------------------------------------------------------------------------
-// rollout variants: 0 = one lane per sample, in-kernel noise; 1 = one lane,
-// precomputed noise; 2 / 3 / 4 = two / four / eight lanes per sample,
-// precomputed noise; 5 / 6 = two / four lanes per sample, in-kernel noise (the
-// form without a noise buffer of the buckets of 16 / 32 rows; not settable);
-// 7 = eight lanes, normals from the block's drawing waves (takes the place of 4
-// up to a block per CU; not settable)
-int variant_lanes(int variant) {
-  constexpr int lanes[8] = {1, 1, 2, 4, 8, 2, 4, 8};
-  return variant >= 0 && variant < 8 ? lanes[variant] : 1;
-}
-bool variant_pre(int variant) { return variant >= 1 && variant <= kMaxVariant; }
-// The in-kernel-noise form of a bucket: at most eight obstacle rows per lane.
-// One lane with 16 or 32 rows does not fit the 256 registers that let two
-// waves share a SIMD, and what it spills or loses in occupancy costs more
-// than the state that two or four lanes hold redundantly.
-int variant_in_kernel(int bucket) { return bucket == 32 ? 6 : (bucket == 16 ? 5 : 0); }
-
 template <int NOB, bool GD, int G, bool PRE>
 static hipError_t launch_rollout_t(const SolveDesc* desc, uint32_t grid, uint32_t block, size_t lds,
                                    hipStream_t stream) {

@@ -9,6 +9,71 @@
 
 namespace brm {
 
+// rollout launch shape: block size and variant (0 = one lane per sample,
+// in-kernel noise; 1 = one lane, precomputed noise; 2 / 3 / 4 = two / four /
+// eight lanes per sample, precomputed noise; 5 .. 7 chosen here, not settable: see
+// variant_in_kernel and drawn_fits).  No shape changes any result bit.
+struct LaunchShape {
+  uint32_t block = 0;    // 0: not set
+  int variant = 0;
+};
+
+// The shape of a plain solve that is neither tuned nor forced.  Blocks of 256:
+// the dispatcher spreads a block's waves over its CU's SIMDs, and two blocks of
+// two waves can land on the same two (65536 samples, 32 rows, one lane: 610 us
+// at 128 threads, 330 at 256).  Lanes: as many as put one wave on each of the
+// 1024 SIMDs (65536 lanes), since a wave issues at most one instruction every
+// 4 cycles whatever else its SIMD holds; beyond that a lane keeps at most
+// eight rows, because the one- and two-lane forms with more rows run out of
+// registers.  Measured (us a solve, T = 40; 2/8/16/32 rows; two, four, eight
+// lanes): 12000 samples 59 59 72 / 74 67 76 / 95 77 88 / 132 98 100; 20011
+// samples 64 75 95 / 82 86 99 / 102 101 113 / 140 127 131; 32768 samples 69 80
+// 117 / 85 90 117 / 108 106 136 / 150 136 163; 65536 samples with one lane and
+// precomputed normals 84 / 165 / 643 / 293, with four lanes 120 / 136 / 175 / 251.
+// Without guidance the lanes share the stage costs, which the collision penalty
+// makes the largest part: 20011 samples, two / four / eight lanes 47 / 47 / 50,
+// with the penalty over 24 obstacles 70 / 63 / 62; 65536 with one / four 62 / 76 and
+// 108 / 107.
+// Normals in HBM or drawn by the rollout (variant_in_kernel).  With eight rows the
+// one-lane form with precomputed normals spills, most of all with moving obstacles
+// or discs (65536 samples, T = 110: eight at rest 466, moving 1277, four around two
+// discs 1481; drawn 292, 320, 591; four lanes 339, 368, 511): four lanes up to three
+// quarters of a wave per SIMD (49152 samples, T = 60: 146, drawn 174; 57344: 177 and
+// 174), drawn beyond.  Elsewhere the buffer pays until its traffic outweighs the
+// draws: without guidance at 128 MB, where normals and applied inputs leave the
+// last-level cache together (40000 samples, T = 200, 96 MB: 133 and 130 drawn;
+// 32768, T = 400, 157 MB: 268 and 218; 131072, T = 110, 173 MB: 203 and 141); with the
+// penalty, whose rows four lanes share, only with more than a wave per SIMD
+// (131072 samples, T = 40, 63 MB: 24 obstacles 173 and 128; 65536, T = 110, 87 MB: 214
+// and 219); with 16 rows around the rear axle from 512 MB and many waves on (65536
+// samples, T = 110, 605 MB: 467 and 352; 131072, T = 40, 440 MB: 331 and 344; 40000,
+// T = 200, 672 MB: 560 and 582; around four discs 65536, T = 110: 734 and 708, 100000,
+// T = 200: 2128 and 2401).
+inline LaunchShape default_shape(int bucket, uint32_t S, size_t noise_bytes, bool penalty, bool rear_axle) {
+  LaunchShape s;
+  s.block = 256;
+  bool drawn = false;      // normals drawn by the rollout
+  if (S <= 8192) {
+    s.variant = 4;
+  } else if (bucket == 0 && penalty) {
+    s.variant = S <= 24576 ? 4 : 3;
+    drawn = S > 65536 && noise_bytes > size_t(48) << 20;
+  } else if (bucket == 32) {
+    s.variant = S <= 24576 ? 4 : 3;
+  } else if (bucket == 16) {
+    s.variant = 3;
+    drawn = rear_axle && S > 49152 && noise_bytes > size_t(512) << 20;
+  } else if (bucket == 8) {
+    s.variant = S > 16384 && S <= 32768 ? 2 : 3;
+    drawn = S > 49152;
+  } else {
+    s.variant = S <= 16384 ? 3 : (S <= 32768 ? 2 : 1);
+    drawn = bucket == 0 && noise_bytes > size_t(128) << 20;
+  }
+  if (drawn) s.variant = variant_in_kernel(bucket);
+  return s;
+}
+
 // what stays on the device for a controller between its updates
 struct Resident {
   float* unom = nullptr;      // nominal sequence, 3T floats

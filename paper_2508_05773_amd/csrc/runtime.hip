@@ -214,41 +214,6 @@ struct HipServed {
   void trace_pop() { roctxRangePop(); }
 };
 
-// rollout launch shape: block size and variant (0 = one lane per sample,
-// in-kernel noise; 1 = one lane, precomputed noise; 2 / 3 / 4 = two / four /
-// eight lanes per sample, precomputed noise; 5 .. 7 chosen here, not settable: see
-// variant_in_kernel and drawn_fits).  No shape changes any result bit.
-struct LaunchShape {
-  uint32_t block = 0;    // 0: not set
-  int variant = 0;
-};
-
-// The shape of a plain solve that is neither tuned nor forced.  Blocks of 256:
-// the dispatcher spreads a block's waves over its CU's SIMDs, and two blocks of
-// two waves can land on the same two (65536 samples, 32 rows, one lane: 610 us
-// at 128 threads, 330 at 256).  Lanes: as many as put one wave on each of the
-// 1024 SIMDs (65536 lanes), since a wave issues at most one instruction every
-// 4 cycles whatever else its SIMD holds; beyond that a lane keeps at most
-// eight rows, because the one- and two-lane forms with more rows run out of
-// registers.  Measured (us a solve, T = 40; 2/8/16/32 rows; two, four, eight
-// lanes): 12000 samples 64 63 75 / 87 75 81 / 119 88 91 / 165 115 106; 20011
-// samples 69 79 98 / 92 95 103 / 124 111 116 / 173 146 141; 32768 samples 74 85
-// 121 / 95 98 122 / 128 113 138 / 179 152 172; 65536 samples with one lane and
-// precomputed normals 89 / 128 / 650 / 333, with four lanes 124 / 152 / 186 / 280.
-// Without guidance the lanes share the stage costs, which the collision penalty
-// makes the largest part: 20011 samples, two / four / eight lanes 51 / 52 / 54,
-// with the penalty 67 / 58 / 58; 65536 with one / four 69 / 83 and 93 / 95.
-LaunchShape default_shape(int bucket, uint32_t S, bool penalty) {
-  LaunchShape s;
-  s.block = 256;
-  if (S <= 8192) s.variant = 4;
-  else if (bucket == 0 && penalty) s.variant = S <= 24576 ? 4 : 3;
-  else if (bucket == 32) s.variant = S <= 24576 ? 4 : 3;
-  else if (bucket == 16) s.variant = 3;
-  else s.variant = S <= 16384 ? 3 : (S <= 32768 ? 2 : 1);
-  return s;
-}
-
 constexpr int kBuckets[5] = {0, 2, 8, 16, 32};
 int bucket_index(int bucket) {
   for (int i = 0; i < 5; ++i)
@@ -431,9 +396,10 @@ bool drawn_fits(const brmppi_ctx* ctx, const LaunchShape& s, uint32_t S, uint32_
 LaunchShape plain_shape(brmppi_ctx* ctx, const brmppi_problem& p) {
   const int bucket = bucket_for(obstacle_rows(ctx, p), p.flags);
   LaunchShape s = ctx->forced.block ? ctx->forced : ctx->shape[bucket_index(bucket)][s_class(p.S)];
-  if (s.block == 0) s = default_shape(bucket, p.S, (p.flags & BRMPPI_COLLISION_PENALTY) != 0);
-  if (drawn_fits(ctx, s, p.S, p.T, fused_lds(p, s))) s.variant = kDrawnVariant;
   const size_t noise = (size_t)normals_per_step(ctx, p) * p.T * round_up(p.S, 256) * sizeof(float);
+  if (s.block == 0)
+    s = default_shape(bucket, p.S, noise, (p.flags & BRMPPI_COLLISION_PENALTY) != 0, footprint_is_rear_axle(params_of(ctx, p)));
+  if (drawn_fits(ctx, s, p.S, p.T, fused_lds(p, s))) s.variant = kDrawnVariant;
   if (variant_pre(s.variant) && noise > std::min(kMaxNoiseBytes, ctx->arena.size() / 2))
     s.variant = variant_in_kernel(bucket);
   return s;

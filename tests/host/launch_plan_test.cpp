@@ -82,9 +82,32 @@ static void tune_update_rows() {
   }
 }
 
+// The default shape over its whole range: one that the bucket's kernels have, and
+// not the one-lane form with precomputed normals where it spills (8 to 32 rows).
+static void default_shapes() {
+  for (int bucket : {0, 2, 8, 16, 32}) {
+    const uint32_t K = bucket ? 5u + (uint32_t)bucket : 3u;
+    for (uint32_t S = 1; S <= BRMPPI_MAX_S; S = S < 64 ? S + 1 : S + S / 9) {
+      for (uint32_t T : {1u, 20u, 48u, 110u, 216u, 512u}) {
+        for (int k = 0; k < 4; ++k) {
+          const size_t noise = (size_t)K * T * round_up(S, 256) * sizeof(float);
+          const LaunchShape s = default_shape(bucket, S, noise, k & 1, k & 2);
+          CHECK(s.block == 256);
+          CHECK(variant_pre(s.variant) || s.variant == variant_in_kernel(bucket));
+          CHECK(bucket < 8 || s.variant != 1);
+          if (S <= 8192) CHECK(s.variant == 4);
+          // as few waves as to leave SIMDs idle: several lanes a sample
+          if (S <= 16384 && variant_pre(s.variant)) CHECK(variant_lanes(s.variant) >= 4);
+        }
+      }
+    }
+  }
+}
+
 int main() {
   drawn_reads_in_range();
   tune_update_rows();
+  default_shapes();
   std::printf("launch plan: all checks passed\n");
   return 0;
 }
