@@ -405,11 +405,12 @@ LaunchShape plain_shape(brmppi_ctx* ctx, const brmppi_problem& p) {
   return s;
 }
 
-ScratchLayout plain_layout(const brmppi_ctx* ctx, const brmppi_problem& p, const LaunchShape& sh) {
+// (without normals: see Normals)
+ScratchLayout plain_layout(const brmppi_ctx* ctx, const brmppi_problem& p) {
   const brmppi_problem* pp = &p;
   uint32_t rows = kRowsPerPass;
   reduce_rows(&pp, 1, ctx->n_cu, &rows);
-  return scratch_layout(p.S, p.T, variant_pre(sh.variant) ? normals_per_step(ctx, p) : 0u, rows);
+  return scratch_layout(p.S, p.T, 0u, rows);
 }
 
 hipEvent_t take_event(brmppi_ctx* ctx) {
@@ -509,6 +510,39 @@ int ensure_scratch(brmppi_ctx* ctx, size_t bytes) {
   return 0;
 }
 
+// The precomputed normals of a call: behind the first `used` bytes of the kept
+// scratch where they fit, else in a block of the arena that the call gives back, so
+// that they never take what a later batch or request could use.  take() fails where
+// there is no room: the call then draws its normals in the rollout.
+class Normals {
+ public:
+  explicit Normals(brmppi_ctx* ctx) : ctx_(ctx) {}
+  ~Normals() {
+    // a call that failed may have left work on its stream that still uses the block,
+    // which another stream's batch could be given
+    if (blk_.ptr && !idle_) (void)hipStreamSynchronize(ctx_->streams[0]);
+    ctx_->arena.release(blk_);
+  }
+  Normals(const Normals&) = delete;
+  Normals& operator=(const Normals&) = delete;
+  char* take(size_t used, size_t bytes) {
+    used = round_up(used, 256);
+    if (ctx_->scratch.bytes >= used + bytes) return ctx_->scratch.ptr + used;
+    blk_ = ctx_->arena.alloc(bytes);
+    return blk_.ptr;
+  }
+  void idle() { idle_ = true; }   // the call's stream has been waited for
+
+ private:
+  brmppi_ctx* ctx_;
+  Block blk_;
+  bool idle_ = false;
+};
+
+size_t normals_bytes(const brmppi_ctx* ctx, const brmppi_problem& p) {
+  return (size_t)normals_per_step(ctx, p) * p.T * round_up(p.S, 256) * sizeof(float);
+}
+
 // ---------------------------------------------------------------------------
 // plain solve
 // ---------------------------------------------------------------------------
@@ -561,14 +595,36 @@ int solve_locked(brmppi_ctx* ctx, const brmppi_problem* p, const brmppi_outputs*
   if (rc) return rc;
   if (!out || !out->u_out) return fail(BRMPPI_EINVAL, "u_out is NULL");
   Controller& c = ctx->ctrl[p->controller];
-  const LaunchShape sh = plain_shape(ctx, *p);
-  const ScratchLayout L = plain_layout(ctx, *p, sh);
+  LaunchShape sh = plain_shape(ctx, *p);
+  const ScratchLayout L = plain_layout(ctx, *p);
   // device: [scratch | input block]
-  const size_t lds = fused_lds(*p, sh);
   const bool drawn = sh.variant == kDrawnVariant;   // the inputs are the launch's arguments
   const InputBlock IB = drawn ? InputBlock{} : input_block(p->T, p->u_nom != nullptr, L.n_wchunk);
   const size_t in_off = L.bytes;
   const size_t need = in_off + round_up(IB.bytes, 256);
+  char* base;
+  float* noise = nullptr;
+  Normals normals(ctx);
+  if (fixed) {
+    // the limit is the one the interface states, normals included, also where the
+    // rollout draws its own
+    const size_t asked = !drawn ? need + (variant_pre(sh.variant) ? normals_bytes(ctx, *p) : 0)
+                                : L.bytes + normals_bytes(ctx, *p) +
+                                      round_up(input_block(p->T, p->u_nom != nullptr, L.n_wchunk).bytes, 256);
+    if (asked > fixed_bytes)
+      return fail(BRMPPI_ENOMEM, "the update needs " + std::to_string(asked) + " bytes of scratch, more than the " +
+                                     std::to_string(fixed_bytes) + " of the static scratch");
+    base = fixed;
+    if (variant_pre(sh.variant)) noise = reinterpret_cast<float*>(fixed + need);
+  } else {
+    if ((rc = ensure_scratch(ctx, need))) return rc;
+    base = ctx->scratch.ptr;
+    if (variant_pre(sh.variant)) {
+      noise = reinterpret_cast<float*>(normals.take(need, normals_bytes(ctx, *p)));
+      if (!noise) sh.variant = variant_in_kernel(bucket_for(obstacle_rows(ctx, *p), p->flags));
+    }
+  }
+  const size_t lds = fused_lds(*p, sh);
   // pinned: [input block | stats, sequence | costs | two pieces of the sequences];
   // the kernels read the first and write the next two themselves
   const size_t out_off = round_up(IB.bytes, 256);
@@ -577,21 +633,10 @@ int solve_locked(brmppi_ctx* ctx, const brmppi_problem* p, const brmppi_outputs*
   const size_t piece_off = J_off + (J_direct ? round_up(p->S * sizeof(float), 256) : 0);
   const bool rows_out = out->useq_out || (out->J_out && !J_direct);
   const size_t pin_need = piece_off + (rows_out ? 2 * kPieceBytes : 0);
-  char* base;
   if (fixed) {
-    // the limit is the one the interface states, normals included, also where the
-    // rollout draws its own
-    const size_t asked = !drawn ? need : scratch_layout(p->S, p->T, normals_per_step(ctx, *p)).bytes +
-                                             round_up(input_block(p->T, p->u_nom != nullptr, L.n_wchunk).bytes, 256);
-    if (asked > fixed_bytes)
-      return fail(BRMPPI_ENOMEM, "the update needs " + std::to_string(asked) + " bytes of scratch, more than the " +
-                                     std::to_string(fixed_bytes) + " of the static scratch");
     if (pin_need > ctx->pin.bytes) return fail(BRMPPI_ENOMEM, "inputs larger than the pinned staging buffer");
-    base = fixed;
-  } else {
-    if ((rc = ensure_scratch(ctx, need))) return rc;
-    if ((rc = ctx->pin.ensure(pin_need))) return rc;
-    base = ctx->scratch.ptr;
+  } else if ((rc = ctx->pin.ensure(pin_need))) {
+    return rc;
   }
   SolveDesc* d_desc = reinterpret_cast<SolveDesc*>(base + in_off);
   hipStream_t s = ctx->streams[0];
@@ -609,6 +654,7 @@ int solve_locked(brmppi_ctx* ctx, const brmppi_problem* p, const brmppi_outputs*
   } else {
     fill_desc(*h_desc, *p, c, L, base, 0, reinterpret_cast<const float*>(base + in_off + IB.unom),
               reinterpret_cast<uint32_t*>(base + in_off + IB.counter), pin_out, lds > 0, out->useq_out != nullptr);
+    h_desc->noise = noise;
     if (J_direct) h_desc->J = pin_J;
     std::memset(pin + IB.counter, 0, IB.unom - IB.counter);
     if (p->u_nom) std::memcpy(pin + IB.unom, p->u_nom, sizeof(float) * 3 * p->T);
@@ -627,6 +673,7 @@ int solve_locked(brmppi_ctx* ctx, const brmppi_problem* p, const brmppi_outputs*
     return rc;
   }
   HIPCHK(hipStreamSynchronize(s));
+  normals.idle();
   collect_timing(ctx);
   if (J_direct) std::memcpy(out->J_out, pin_J, sizeof(float) * p->S);
   else if (out->J_out && (rc = download_rows(ctx, s, out->J_out, p->S, base + L.off_J, L.S_pad, 1, pin + piece_off))) return rc;
@@ -970,9 +1017,8 @@ int closed_loop_locked(brmppi_ctx* ctx, const brmppi_problem* p0, uint32_t n_up,
   int rc = validate(ctx, &p);
   c.plant_set = plant_was_set;
   if (rc) return rc;
-  const LaunchShape sh = plain_shape(ctx, p);
-  const ScratchLayout L = plain_layout(ctx, p, sh);
-  const size_t lds = fused_lds(p, sh);
+  LaunchShape sh = plain_shape(ctx, p);
+  const ScratchLayout L = plain_layout(ctx, p);
   // The updates run in chunks of C: one descriptor upload per chunk and, when
   // the launch shape reads precomputed normals, one noise launch per chunk
   // (slot i of a chunk-sized noise region for its i-th update).  Descriptors
@@ -984,8 +1030,8 @@ int closed_loop_locked(brmppi_ctx* ctx, const brmppi_problem* p0, uint32_t n_up,
   // noise waves delay the rollout's, each of which is on the critical path of
   // its update.)
   const bool drawn = sh.variant == kDrawnVariant;   // the inputs are each launch's arguments
-  const bool pre = variant_pre(sh.variant);
-  const size_t noise_bytes = pre ? round_up((size_t)L.n_normals * p.T * L.S_pad * sizeof(float), 256) : 0;
+  const size_t noise_bytes = round_up(normals_bytes(ctx, p), 256);
+  bool pre = variant_pre(sh.variant);
   uint32_t C = kLoopChunk;
   if (pre) {
     const size_t cap = std::min(kClosedLoopNoiseBytes, ctx->arena.size() / 2);
@@ -995,7 +1041,7 @@ int closed_loop_locked(brmppi_ctx* ctx, const brmppi_problem* p0, uint32_t n_up,
   const size_t desc_bytes = round_up(sizeof(SolveDesc), 256);
   const size_t unom_bytes = p.u_nom ? sizeof(float) * 3 * p.T : 0;
   const size_t half_bytes = desc_bytes * C + round_up(sizeof(double) * kLogRecord * C, 256);
-  // device: [scratch | counters (zero) | nominal | half 0 | half 1 | normals of C updates]
+  // device: [scratch | counters (zero) | nominal | half 0 | half 1], and the normals of C updates
   // pinned: [counters | nominal | half 0 | half 1 | start state]; a half holds
   // the chunk's descriptors, then its plant states and applied inputs
   const size_t ctr_rel = 0;
@@ -1004,10 +1050,23 @@ int closed_loop_locked(brmppi_ctx* ctx, const brmppi_problem* p0, uint32_t n_up,
   const size_t half_rel = round_up(head_bytes, 256);
   const size_t x0_rel = half_rel + 2 * half_bytes;
   const size_t in_off = L.bytes;
-  const size_t noise_off = in_off + x0_rel;
-  const size_t need = noise_off + (pre ? C * noise_bytes : 0);
+  const size_t need = in_off + x0_rel;
   if ((rc = ensure_scratch(ctx, need))) return rc;
   if ((rc = ctx->pin.ensure(x0_rel + 256))) return rc;
+  Normals normals(ctx);
+  char* noise = nullptr;
+  // the chunk's normals: of fewer updates where there is no room for all (the halves
+  // keep their size), at the least of one
+  if (pre) {
+    const uint32_t most = C;
+    while (!(noise = normals.take(need, C * noise_bytes)) && C > 1) C /= 2;
+    if (!noise) {
+      pre = false;
+      C = most;
+      sh.variant = variant_in_kernel(bucket_for(obstacle_rows(ctx, p), p.flags));
+    }
+  }
+  const size_t lds = fused_lds(p, sh);
   char* base = ctx->scratch.ptr;
   char* pin = ctx->pin.ptr;
   hipStream_t s = ctx->streams[0];
@@ -1059,7 +1118,7 @@ int closed_loop_locked(brmppi_ctx* ctx, const brmppi_problem* p0, uint32_t n_up,
       SolveDesc* d = reinterpret_cast<SolveDesc*>(hp + desc_bytes * i);
       // only the first update reads the caller's sequence; later ones the shifted result
       fill_desc(*d, p, c, L, base, k, (k == 0 && p.u_nom) ? d_unom : nullptr, d_ctr, d_out, lds > 0, false);
-      if (pre) d->noise = reinterpret_cast<float*>(base + noise_off + i * noise_bytes);
+      if (pre) d->noise = reinterpret_cast<float*>(noise + i * noise_bytes);
       // the update's last block writes the log (two device copies an update
       // took 2.6 us of it)
       if (logs) d->log = reinterpret_cast<double*>(hd + desc_bytes * C) + kLogRecord * i;
@@ -1079,11 +1138,12 @@ int closed_loop_locked(brmppi_ctx* ctx, const brmppi_problem* p0, uint32_t n_up,
       if ((rc = enqueue_rollout_reduce(ctx, s, reinterpret_cast<const SolveDesc*>(hd + desc_bytes * i), p, L, sh, lds)))
         return rc;
     if (logs)
-      HIPCHK(hipMemcpyAsync(hp + desc_bytes * C, hd + desc_bytes * C, half_bytes - desc_bytes * C,
+      HIPCHK(hipMemcpyAsync(hp + desc_bytes * C, hd + desc_bytes * C, sizeof(double) * kLogRecord * cnt,
                             hipMemcpyDeviceToHost, s));
     HIPCHK(hipEventRecord(ctx->loop_ev[h], s));
   }
   HIPCHK(hipStreamSynchronize(s));
+  normals.idle();
   collect_timing(ctx);
   if (logs) {
     for (uint32_t j = n_chunks >= 2 ? n_chunks - 2 : 0; j < n_chunks; ++j) take_logs(j);
