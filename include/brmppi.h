@@ -257,9 +257,11 @@ int brmppi_solve_ex(brmppi_ctx* ctx, const brmppi_problem* p, const brmppi_outpu
  * contents (the counters a call needs at zero are uploaded with its inputs);
  * calls of one process on one GPU are serialised, and a call returns only
  * after its device work is done.  Errors: as brmppi_solve; ENOMEM when the
- * update needs more scratch than the array holds (about S*T*(3 + 5 + n_obs)*4
- * bytes) or its inputs more than the staging buffer; ESTATE when the array's
- * address could not be taken at create. */
+ * update needs more scratch than the array holds (about S*T*3*4 bytes, and up to
+ * 32768 samples, 8192 without guidance, S*T*(5 + n_obs)*4 or S*T*3*4 for its normals,
+ * unless these exceed half the arena; a tuned or forced shape that draws them in the
+ * rollout counts none) or its inputs more than the staging buffer; ESTATE when the
+ * array's address could not be taken at create. */
 int brmppi_solve_noalloc(brmppi_ctx* ctx, const brmppi_problem* p, float* u_out, brmppi_stats* st);
 
 /* ---- batched solve (blocking) ------------------------------------------- */

@@ -392,15 +392,36 @@ bool drawn_fits(const brmppi_ctx* ctx, const LaunchShape& s, uint32_t S, uint32_
          T <= kInlineSteps && lds > 0;
 }
 
+size_t normals_bytes(const brmppi_ctx* ctx, const brmppi_problem& p) {
+  return (size_t)normals_per_step(ctx, p) * p.T * round_up(p.S, 256) * sizeof(float);
+}
+size_t normals_limit(const brmppi_ctx* ctx) { return std::min(kMaxNoiseBytes, ctx->arena.size() / 2); }
+
+// the shape that the caller forced or tuned, if any (block 0: none)
+LaunchShape set_shape(const brmppi_ctx* ctx, const brmppi_problem& p) {
+  if (ctx->forced.block) return ctx->forced;
+  return ctx->shape[bucket_index(bucket_for(obstacle_rows(ctx, p), p.flags))][s_class(p.S)];
+}
+
+// Bytes of normals in the scratch that brmppi_solve_noalloc is stated to need: the
+// same whichever launch draws them, so that a new default shape does not move the
+// limit.
+size_t stated_normals(const brmppi_ctx* ctx, const brmppi_problem& p) {
+  const LaunchShape s = set_shape(ctx, p);
+  const bool counted = s.block ? variant_pre(s.variant) : p.S <= ((p.flags & BRMPPI_GUIDANCE_OFF) ? 8192u : 32768u);
+  const size_t n = normals_bytes(ctx, p);
+  return counted && n <= normals_limit(ctx) ? n : 0;
+}
+
 // launch shape of a plain (single-instance) rollout
 LaunchShape plain_shape(brmppi_ctx* ctx, const brmppi_problem& p) {
   const int bucket = bucket_for(obstacle_rows(ctx, p), p.flags);
-  LaunchShape s = ctx->forced.block ? ctx->forced : ctx->shape[bucket_index(bucket)][s_class(p.S)];
-  const size_t noise = (size_t)normals_per_step(ctx, p) * p.T * round_up(p.S, 256) * sizeof(float);
+  LaunchShape s = set_shape(ctx, p);
+  const size_t noise = normals_bytes(ctx, p);
   if (s.block == 0)
     s = default_shape(bucket, p.S, noise, (p.flags & BRMPPI_COLLISION_PENALTY) != 0, footprint_is_rear_axle(params_of(ctx, p)));
   if (drawn_fits(ctx, s, p.S, p.T, fused_lds(p, s))) s.variant = kDrawnVariant;
-  if (variant_pre(s.variant) && noise > std::min(kMaxNoiseBytes, ctx->arena.size() / 2))
+  if (variant_pre(s.variant) && noise > normals_limit(ctx))
     s.variant = variant_in_kernel(bucket);
   return s;
 }
@@ -539,10 +560,6 @@ class Normals {
   bool idle_ = false;
 };
 
-size_t normals_bytes(const brmppi_ctx* ctx, const brmppi_problem& p) {
-  return (size_t)normals_per_step(ctx, p) * p.T * round_up(p.S, 256) * sizeof(float);
-}
-
 // ---------------------------------------------------------------------------
 // plain solve
 // ---------------------------------------------------------------------------
@@ -606,16 +623,16 @@ int solve_locked(brmppi_ctx* ctx, const brmppi_problem* p, const brmppi_outputs*
   float* noise = nullptr;
   Normals normals(ctx);
   if (fixed) {
-    // the limit is the one the interface states, normals included, also where the
-    // rollout draws its own
-    const size_t asked = !drawn ? need + (variant_pre(sh.variant) ? normals_bytes(ctx, *p) : 0)
-                                : L.bytes + normals_bytes(ctx, *p) +
-                                      round_up(input_block(p->T, p->u_nom != nullptr, L.n_wchunk).bytes, 256);
+    const size_t asked = L.bytes + round_up(input_block(p->T, p->u_nom != nullptr, L.n_wchunk).bytes, 256) +
+                         stated_normals(ctx, *p);
     if (asked > fixed_bytes)
       return fail(BRMPPI_ENOMEM, "the update needs " + std::to_string(asked) + " bytes of scratch, more than the " +
                                      std::to_string(fixed_bytes) + " of the static scratch");
     base = fixed;
-    if (variant_pre(sh.variant)) noise = reinterpret_cast<float*>(fixed + need);
+    if (variant_pre(sh.variant)) {
+      if (need + normals_bytes(ctx, *p) <= fixed_bytes) noise = reinterpret_cast<float*>(fixed + need);
+      else sh.variant = variant_in_kernel(bucket_for(obstacle_rows(ctx, *p), p->flags));
+    }
   } else {
     if ((rc = ensure_scratch(ctx, need))) return rc;
     base = ctx->scratch.ptr;

@@ -86,3 +86,28 @@ def test_closed_loop_in_a_small_arena(S, T, n_obs, flags, arena):
             print(f"  S={S} T={T} n_obs={n_obs} arena={a >> 20} MiB", flush=True)
             got.append(B.brmppi_closed_loop(c.h, B.ProblemBuffers(p, controller=0), 19))
     assert np.array_equal(got[0][0], got[1][0]) and np.array_equal(got[0][1], got[1][1])
+
+
+@pytest.mark.parametrize("S,T,n_obs,flags,arena,ok", [
+    (65536, 50, 8, 0, 512 << 20, True),                       # 41 MB, normals not counted
+    (40000, 40, 8, 0, 512 << 20, True),
+    (32768, 100, 0, W.FLAG_GUIDANCE_OFF, 512 << 20, True),
+    (65536, 100, 0, W.FLAG_GUIDANCE_OFF, 512 << 20, False),   # 79 MB
+    (8192, 100, 32, 0, 200 << 20, True),                      # normals above half the arena: not counted
+    (20000, 100, 8, 0, 512 << 20, False),                     # 105 MB of normals
+    (8192, 300, 0, W.FLAG_GUIDANCE_OFF, 512 << 20, True),     # 30 MB and as much of normals
+    (8192, 400, 0, W.FLAG_GUIDANCE_OFF, 512 << 20, False),
+])
+def test_noalloc_limit(S, T, n_obs, flags, arena, ok):
+    """the allocation-free solve takes what its stated limit allows, with or without
+    room for the normals in its array, and gives the plain solve's bits"""
+    p = problem(S, T, n_obs, flags)
+    with context(arena) as c:
+        c.set_path(0, p.path, p.ds)
+        pb = B.ProblemBuffers(p, controller=0)
+        print(f"  S={S} T={T} n_obs={n_obs} flags={flags}", flush=True)
+        u, _, rc = B.brmppi_solve_noalloc(c.h, pb, allow=(B.OK, B.ENOMEM))
+        assert rc == (B.OK if ok else B.ENOMEM)
+        if ok:
+            u = u.copy()
+            assert np.array_equal(u, B.brmppi_solve(c.h, pb)[0])
