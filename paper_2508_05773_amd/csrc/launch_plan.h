@@ -99,8 +99,9 @@ inline size_t counter_bytes(uint32_t n_groups) {
   return round_up(sizeof(uint32_t) * kCtrStride * (1 + (size_t)n_groups), 256);
 }
 
+// units: with the partials of tiles that reduce themselves
 inline ScratchLayout scratch_layout(uint32_t S, uint32_t T, uint32_t noise_normals = 0,
-                                    uint32_t rows_item = kRowsPerPass) {
+                                    uint32_t rows_item = kRowsPerPass, bool units = true) {
   ScratchLayout L;
   L.n_normals = noise_normals;
   L.S_pad = (uint32_t)round_up(S, 256);
@@ -118,15 +119,31 @@ inline ScratchLayout scratch_layout(uint32_t S, uint32_t T, uint32_t noise_norma
   L.off_rpart = o;
   o = round_up(o + (size_t)L.n_wchunk * 3 * T * sizeof(float), 256);
   L.off_upart = o;
-  o = round_up(o + (size_t)L.n_units * sizeof(float4), 256);
+  o = round_up(o + (units ? (size_t)L.n_units * sizeof(float4) : 0), 256);
   L.off_urow = o;
-  o = round_up(o + (size_t)L.n_units * 3 * T * sizeof(float), 256);
+  o = round_up(o + (units ? (size_t)L.n_units * 3 * T * sizeof(float) : 0), 256);
   L.off_out = o;
   o = round_up(o + (size_t)(4 + 3 * T) * sizeof(float), 256);
   L.off_noise = o;
   o = round_up(o + (size_t)noise_normals * T * L.S_pad * sizeof(float), 256);
   L.bytes = o;
   return L;
+}
+
+// an instance of a batch: reduced by k_reduce, no unit partials
+inline ScratchLayout batch_scratch(uint32_t S, uint32_t T, uint32_t rows_item) {
+  return scratch_layout(S, T, 0, rows_item, false);
+}
+
+// Device bytes that one request is counted with in a served batch: scratch,
+// descriptor, tiles, work items and alignment slack.  What a batch takes stays below
+// this at any launch shape: its smallest tiles, of 16 samples (block 64, four lanes),
+// need less than the unit partials that it does not have.
+inline size_t request_footprint(uint32_t S, uint32_t T) {
+  const ScratchLayout L = scratch_layout(S, T);
+  const size_t tiles = (S + 63) / 64;
+  const size_t items = L.n_wchunk + (size_t)L.n_wchunk * L.n_rgroup;
+  return L.bytes + sizeof(SolveDesc) + (tiles + items) * 8 + sizeof(float) * (4 + 6 * (size_t)T) + 8 * 256;
 }
 
 // base: the instance's scratch; unom_dev: device copy of p.u_nom when the

@@ -741,7 +741,7 @@ void plan_layout(brmppi_ctx* ctx, const brmppi_problem* const* ps, uint32_t n, B
   std::vector<uint32_t> rows_item(n);
   reduce_rows(ps, n, ctx->n_cu, rows_item.data());
   for (uint32_t i = 0; i < n; ++i) {
-    bp.layouts[i] = scratch_layout(ps[i]->S, ps[i]->T, 0, rows_item[i]);
+    bp.layouts[i] = batch_scratch(ps[i]->S, ps[i]->T, rows_item[i]);
     const uint32_t per = batch_tile(ctx, *ps[i], bp.block);
     n_tiles += (ps[i]->S + per - 1) / per;
     n_r += (size_t)bp.layouts[i].n_wchunk * bp.layouts[i].n_rgroup;
@@ -1174,15 +1174,6 @@ int closed_loop_locked(brmppi_ctx* ctx, const brmppi_problem* p0, uint32_t n_up,
 // ---------------------------------------------------------------------------
 // served form
 // ---------------------------------------------------------------------------
-// device bytes one request adds to a served batch: scratch, descriptor, its
-// tiles (at the smallest block size and four lanes per sample) and work items, plus alignment slack
-size_t request_footprint(const brmppi_problem& p) {
-  const ScratchLayout L = scratch_layout(p.S, p.T);
-  const size_t tiles = (p.S + 15) / 16;
-  const size_t items = L.n_wchunk + (size_t)L.n_wchunk * L.n_rgroup;
-  return L.bytes + sizeof(SolveDesc) + (tiles + items) * 8 + sizeof(float) * (4 + 6 * (size_t)p.T) + 8 * 256;
-}
-
 // launch one batch of admitted requests on stream slot b.slot (ctx->mu held)
 template <class B>
 int HipServed::launch(B& b) {
@@ -1555,7 +1546,7 @@ int brmppi_submit(brmppi_ctx* ctx, const brmppi_problem* p, uint64_t* ticket) {
     rc = validate(ctx, &q);
     if (rc) return rc;
   }
-  const size_t fp = request_footprint(*p);
+  const size_t fp = request_footprint(p->S, p->T);
   if (fp > ctx->arena.size()) return fail(BRMPPI_ENOMEM, "request can never fit in the arena");
   std::unique_ptr<Request> r(new Request());
   copy_problem(*r, *p, params_of(ctx, *p));

@@ -104,10 +104,31 @@ static void default_shapes() {
   }
 }
 
+// A served request is counted with the bytes of 64-sample tiles, and a batch of it takes no
+// more of the arena at any tile size.
+static void request_footprints() {
+  CHECK(request_footprint(1000, 30) == 390536);   // with tiles of 64 samples
+  CHECK(request_footprint(32768, 100) == 40758064);
+  for (uint32_t S = 1; S <= BRMPPI_MAX_S; S = S < 64 ? S + 1 : S + S / 9) {
+    for (uint32_t T = 1; T <= BRMPPI_MAX_T; T += 1 + T / 5) {
+      for (uint32_t tile : {16u, 32u, 64u, 256u}) {
+        const ScratchLayout L = batch_scratch(S, T, kRowsPerPass);
+        size_t o = round_up(sizeof(SolveDesc), 256);                 // the parts of a batch, each aligned
+        o = round_up(o + sizeof(Tile) * ((S + tile - 1) / tile), 256);
+        o = round_up(o + sizeof(Item) * (size_t)L.n_wchunk * L.n_rgroup, 256);
+        o = round_up(o + sizeof(float) * 3 * T, 256);
+        o = round_up(o + sizeof(uint32_t), 256);
+        CHECK(o + L.bytes <= request_footprint(S, T));
+      }
+    }
+  }
+}
+
 int main() {
   drawn_reads_in_range();
   tune_update_rows();
   default_shapes();
+  request_footprints();
   std::printf("launch plan: all checks passed\n");
   return 0;
 }
