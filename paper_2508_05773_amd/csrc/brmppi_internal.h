@@ -21,6 +21,7 @@ constexpr int kRedBlocksPerCU = 2;   // reduce blocks a CU holds at once (its LD
 constexpr size_t kFusedLdsMax = 64 * 1024;   // dynamic LDS bound of the fused rollout
 constexpr uint32_t kCtrStride = 32;          // completion counters one 128-B line apart
 constexpr int kPathWin = 1024;    // waypoints staged in LDS per tile
+constexpr int kPathLds = kPathWin + 2;   // and the frame that they are in
 constexpr int kPathBack = 64;     // of which before the start progress
 constexpr size_t kCuLds = 160 * 1024;
 constexpr int kMaxBlock = 256;    // rollout block size bound (launch_bounds)
@@ -126,7 +127,7 @@ hipError_t launch_rollout_drawn(int bucket, SolveArgs& args, uint32_t grid, size
 constexpr uint32_t drawn_slot(int bucket) {   // bytes
   return 4 * kDrawnTile * (4 * (bucket == 0 ? 1u : (5u + (uint32_t)bucket + 3) / 4) + 4);
 }
-constexpr size_t kDrawnPath = 16 * (size_t)kPathWin;
+constexpr size_t kDrawnPath = 16 * (size_t)kPathLds;
 constexpr size_t kDrawnStatic = 8 * 1024;   // nominal inputs, obstacle rows, the epilogue's scalars
 static_assert(drawn_slot(BRMPPI_MAX_OBS) <= kDrawnPath, "the slot past a run lies in the path window");
 struct DrawnLds {

@@ -1,0 +1,49 @@
+"""GPU: the resolution of headings, at quarter turns and away from them.
+
+At rest, with the heading terms alone in the cost, a sample of one step costs
+2 (Q1 e1^2 + Q2 e2^2), e1 and e2 the start headings' distances from the path's.
+Headings are held in revolutions from the quarter turn nearest the start heading, so
+an angle of up to an eighth of a turn has half a unit in the last place of 2^-28
+revolutions, 2.3e-8 rad, and start and path are rounded twice each: 9.4e-8 rad of
+1e-3 is a relative 1.9e-4 of the cost.
+"""
+import numpy as np
+import pytest
+
+from paper_2508_05773_amd import brmppi as B
+from paper_2508_05773_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+HEADINGS = [0.0, 0.3, 0.78, 1.5709, 1.62, 1.7, 2.0, 3.1417, 3.15, 3.2, 3.3, -1.5709, -1.7, -3.15, -3.3, 4.8, 6.4, 20.0]
+
+
+def wrap(x):
+    return x - 2 * np.pi * np.round(x / (2 * np.pi))
+
+
+@pytest.mark.parametrize("S,shape", [(64, (0, 0)), (65, (256, 0)), (9000, (0, 0))])
+@pytest.mark.parametrize("turn", [0.0, 6.283185307179586])
+def test_heading_costs(S, shape, turn):
+    """(turn: the path's headings a whole turn further than the start's)"""
+    with B.Context(arena_bytes=64 << 20, n_streams=1, max_controllers=1) as c:
+        B.brmppi_set_launch(c.h, *shape)
+        for th in HEADINGS:
+            p = W.random_small(7, S=64, T=1, n_obs=0)
+            path = p.path.copy()
+            path[:, 2] = np.float32(th + turn)
+            path[:, 3] = np.float32(th + turn + 0.01)
+            x0 = p.x0.copy()
+            x0[2:4] = 0.0
+            x0[4] = np.float32(path[0, 2] - np.float32(turn)) + np.float32(1e-3)
+            x0[5] = np.float32(path[0, 3] - np.float32(turn)) - np.float32(1e-3)
+            q = dict(p.params, Qc=0.0, Ql=0.0, Qth1=3.0, Qth2=2.0, R_j=0.0, R_w=0.0, mu=0.0)
+            p = p.copy(S=S, path=path, x0=x0, params=q, flags=W.FLAG_GUIDANCE_OFF)
+            e1 = wrap(np.float64(x0[4]) - np.float64(path[0, 2]))
+            e2 = wrap(np.float64(x0[5]) - np.float64(path[0, 3]))
+            want = 2.0 * (3.0 * e1**2 + 2.0 * e2**2)
+            c.set_path(0, p.path, p.ds)
+            J = B.brmppi_solve_ex(c.h, B.ProblemBuffers(p, controller=0), want_J=True)["J"]
+            err = np.max(np.abs(J - want) / want)
+            print(f"  S={S} heading {th} + {turn:.2f}: {err:.1e}", flush=True)
+            assert err <= 2e-4, th
