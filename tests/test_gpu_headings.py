@@ -47,3 +47,36 @@ def test_heading_costs(S, shape, turn):
             err = np.max(np.abs(J - want) / want)
             print(f"  S={S} heading {th} + {turn:.2f}: {err:.1e}", flush=True)
             assert err <= 2e-4, th
+
+
+@pytest.mark.parametrize("shape", [(256, 0), (0, 0)])
+def test_terminal_heading(shape):
+    """The sine and cosine of the terminal cost's reference heading are the library's.
+    At rest on the first waypoint, one step of progress away from the second, 10 m off:
+    the contour error there is 10 m times a sine and cosine product, and a sample's
+    cost its square.  With correctly rounded functions its root mean square error over
+    400 headings is 3.2e-8 of the distance, with the hardware's (3.0 to 3.4e-8 rms)
+    4.2 to 4.8e-8: the bar lies between."""
+    rng = np.random.default_rng(3)
+    q = None
+    err = []
+    with B.Context(arena_bytes=64 << 20, n_streams=1, max_controllers=1) as c:
+        B.brmppi_set_launch(c.h, *shape)
+        for _ in range(400):
+            p = W.random_small(7, S=64, T=1, n_obs=0)
+            th, way = np.float32(rng.uniform(-3.1, 3.1)), rng.uniform(-np.pi, np.pi)
+            xy = np.float32([10 * np.cos(way), 10 * np.sin(way)])
+            path = np.zeros((3, 4), np.float32)
+            path[:, :2] = np.arange(3, dtype=np.float32)[:, None] * xy
+            path[:, 2:] = th
+            x0 = np.zeros(8, np.float32)
+            x0[4:6] = np.float32(th + rng.uniform(-0.7, 0.7))
+            q = q or dict(p.params, Ts=0.5, sigma_nu=0.0, Qc=1.0, Ql=0.0, Qth1=0.0, Qth2=0.0, R_j=0.0, R_w=0.0, mu=0.0)
+            p = p.copy(path=path, ds=0.5, x0=x0, params=q, u_nom=np.float32([[0.0, 0.0, 1.0]]), flags=W.FLAG_GUIDANCE_OFF)
+            c.set_path(0, p.path, p.ds)
+            J = B.brmppi_solve_ex(c.h, B.ProblemBuffers(p, controller=0), want_J=True)["J"].astype(np.float64)
+            h, e = np.float64(th), -xy.astype(np.float64)
+            err.append((np.sqrt(J[0]) - abs(np.sin(h) * e[0] - np.cos(h) * e[1])) / 10)
+    rms = np.sqrt(np.mean(np.square(err)))
+    print(f"  rms {rms:.2e} of the distance", flush=True)
+    assert rms <= 3.9e-8
