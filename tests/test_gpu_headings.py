@@ -1,4 +1,5 @@
-"""GPU: the resolution of headings, at quarter turns and away from them.
+"""GPU: the resolution of headings, at quarter turns and away from them, and of
+progress.
 
 At rest, with the heading terms alone in the cost, a sample of one step costs
 2 (Q1 e1^2 + Q2 e2^2), e1 and e2 the start headings' distances from the path's.
@@ -80,3 +81,28 @@ def test_terminal_heading(shape):
     rms = np.sqrt(np.mean(np.square(err)))
     print(f"  rms {rms:.2e} of the distance", flush=True)
     assert rms <= 3.9e-8
+
+
+@pytest.mark.parametrize("S,shape", [(64, (0, 0)), (65, (256, 0)), (9000, (0, 0))])
+def test_progress(S, shape):
+    """At rest on a straight path with progress of 1/16 m a step, exact in FP32 over 512
+    steps, the lag errors are the progress itself.  Its waypoint index is rounded twice
+    (1/ds and the product), the point and the error once each, the square once: 4.5
+    units of 2^-24, twice that in the square, 5.4e-7 of the cost."""
+    T = 512
+    p = W.random_small(7, S=64, T=1, n_obs=0)
+    path = np.zeros((400, 4), np.float32)
+    path[:, 0] = np.float32(0.3) * np.arange(400, dtype=np.float32)
+    u = np.zeros((T, 3), np.float32)
+    u[:, 2] = 1.0
+    q = dict(p.params, Ts=0.0625, sigma_j=0.0, sigma_w=0.0, sigma_nu=0.0, Qc=0.0, Ql=1.0, Qth1=0.0, Qth2=0.0, R_j=0.0, R_w=0.0,
+             mu=0.0)
+    p = p.copy(S=S, T=T, path=path, ds=float(np.float32(0.3)), x0=np.zeros(8, np.float32), params=q, u_nom=u, flags=W.FLAG_GUIDANCE_OFF)
+    f = np.arange(T + 1) * 0.0625 / np.float64(np.float32(0.3))
+    want = np.sum(np.interp(f, np.arange(400), path[:, 0].astype(np.float64)) ** 2)
+    with B.Context(arena_bytes=256 << 20, n_streams=1, max_controllers=1) as c:
+        B.brmppi_set_launch(c.h, *shape)
+        c.set_path(0, p.path, p.ds)
+        J = B.brmppi_solve_ex(c.h, B.ProblemBuffers(p, controller=0), want_J=True)["J"].astype(np.float64)
+    print(f"  S={S}: {np.max(np.abs(J - want)) / want:.1e}", flush=True)
+    assert np.max(np.abs(J - want)) <= 5.4e-7 * want
