@@ -71,13 +71,13 @@ struct alignas(16) SolveDesc {
 
 // An update's inputs as the argument of its launch: the descriptor and, where its
 // u_nom_in is NULL, the nominal sequence.
-constexpr uint32_t kInlineSteps = 216;   // with the descriptor, within the 4 KB of arguments
+constexpr uint32_t kInlineSteps = 162;   // the longest horizon whose fused epilogue fits at 32 samples a tile
 struct SolveArgs {
   SolveDesc d;
   float unom[3 * kInlineSteps];
   uint32_t run, pad[3];         // steps drawn at a time (set by the launcher)
 };
-static_assert(sizeof(SolveArgs) <= 4096, "a launch's arguments");
+static_assert(sizeof(SolveArgs) <= 4096, "4 KB are a launch's arguments");
 
 struct Tile { uint32_t inst, s0; };
 struct Item { uint32_t inst, idx; };
@@ -131,14 +131,15 @@ constexpr size_t kDrawnPath = 16 * (size_t)kPathLds;
 constexpr size_t kDrawnStatic = 8 * 1024;   // nominal inputs, obstacle rows, the epilogue's scalars
 static_assert(drawn_slot(BRMPPI_MAX_OBS) <= kDrawnPath, "the slot past a run lies in the path window");
 struct DrawnLds {
-  uint32_t run;                 // steps drawn at a time
+  uint32_t run, runs;           // steps drawn at a time, and how often
   size_t path, epilogue, bytes; // offsets of the path window and the epilogue; the whole
 };
 inline DrawnLds drawn_lds(int bucket, uint32_t T, size_t fused) {
   const size_t room = kCuLds - kDrawnStatic - kDrawnPath - fused;
-  const uint32_t most = (uint32_t)(room / drawn_slot(bucket)) & ~1u, runs = (T + most - 1) / most;
+  const uint32_t most = (uint32_t)(room / drawn_slot(bucket)) & ~1u;
   DrawnLds l;
-  l.run = ((T + runs - 1) / runs + 1) & ~1u;
+  l.runs = (T + most - 1) / most;
+  l.run = ((T + l.runs - 1) / l.runs + 1) & ~1u;
   l.path = (size_t)l.run * drawn_slot(bucket);
   l.epilogue = l.path + kDrawnPath;
   l.bytes = l.epilogue + fused;
@@ -151,7 +152,7 @@ hipError_t launch_rollout_batch(const SolveDesc* descs, const Tile* tiles, uint3
 // dynamic LDS of the fused epilogue for a tile of `per_tile` samples: the
 // tile's applied inputs [3T][per_tile + 1] (later reused for the n_groups
 // merge scales), costs, weights, unit minima and scales, unit partials
-__host__ __device__ inline size_t fused_lds_region(uint32_t per_tile, uint32_t T, uint32_t n_groups) {
+__host__ __device__ constexpr size_t fused_lds_region(uint32_t per_tile, uint32_t T, uint32_t n_groups) {
   const size_t a = (size_t)3 * T * (per_tile + 1);
   return ((a > n_groups ? a : n_groups) + 3) / 4 * 4;
 }
@@ -161,10 +162,12 @@ __host__ __device__ inline size_t fused_lds_region(uint32_t per_tile, uint32_t T
 __host__ __device__ inline bool fused_tile_ok(uint32_t per_tile) {
   return per_tile > 0 && per_tile % kUnit == 0 && kWChunk % per_tile == 0;
 }
-__host__ __device__ inline size_t fused_lds_bytes(uint32_t per_tile, uint32_t T, uint32_t n_groups) {
+__host__ __device__ constexpr size_t fused_lds_bytes(uint32_t per_tile, uint32_t T, uint32_t n_groups) {
   return sizeof(float) * (fused_lds_region(per_tile, T, n_groups) + 2 * (size_t)per_tile + 2 * kGroupUnits) +
          16 * kGroupUnits;
 }
+static_assert(fused_lds_bytes(kDrawnTile, kInlineSteps, 8) <= kFusedLdsMax &&
+              fused_lds_bytes(kDrawnTile, kInlineSteps + 1, 8) > kFusedLdsMax, "the horizon of k_rollout_drawn");
 // inputs a launch copies from pinned host memory to the device (n 16-byte units)
 struct Upload {
   const void* src;

@@ -2219,7 +2219,7 @@ void k_rollout_drawn(const SolveArgs) {
 #pragma unroll
       for (int k = 0; k < 2; ++k) {
         const uint32_t qk = min(k ? q1 : q, n - 1);
-        const uint32_t i = (qk * inv_nb) >> 16, b = qk - i * nb;   // qk / nb, exact: qk < 10 * 216
+        const uint32_t i = (qk * inv_nb) >> 16, b = qk - i * nb;   // qk / nb, exact: qk < 10 * 162
         uint32_t r[4];
         philox4x32_10(s, tau0 + i, b, d.instance, d.seed_lo, d.seed_hi, r);
         box_muller4(r, e[k]);

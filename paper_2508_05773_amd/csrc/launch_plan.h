@@ -2,6 +2,7 @@
 // of its scratch and the descriptor that the kernels read.  No device call.
 #pragma once
 
+#include <algorithm>
 #include <cstring>
 
 #include "brmppi_internal.h"
@@ -72,6 +73,22 @@ inline LaunchShape default_shape(int bucket, uint32_t S, size_t noise_bytes, boo
   }
   if (drawn) s.variant = variant_in_kernel(bucket);
   return s;
+}
+
+// Whether k_rollout_drawn takes the place of the noise kernel and the rollout of
+// eight lanes (fused: the bytes of its epilogue, 0 for none): up to a block per CU (a
+// second one on a CU would wait for the first's LDS), tiles that reduce themselves, a
+// horizon whose epilogue fits.  It saves a launch and the wait between the two, 2 to 6 us
+// at up to 2048 samples and 4 to 14 at 8192 (drawn / two launches: 256 samples, 24 steps,
+// 8 rows 40 / 43 us; 8192, 50 steps, 8 rows 57 / 63; 8192, 130 steps, 16 rows 121 / 132),
+// and each run beyond the first costs it a pair of barriers and a draw that nothing
+// hides, 2 to 3 us: with few samples, whose noise kernel is short, many runs lose (256
+// samples, 32 rows: 40 steps, two runs 63 / 64; 60, three 82 / 79; 162, 14 181 / 160; 2048
+// samples: 100 steps, seven 123 / 123; 162, 14 183 / 172; 8192 samples: 14 185 / 192).
+constexpr uint32_t kDrawnBlocks = 256;   // eight groups at most
+inline bool drawn_fits(int n_cu, int bucket, const LaunchShape& s, uint32_t S, uint32_t T, size_t fused) {
+  return s.variant == 4 && s.block == 256 && S <= kDrawnTile * std::min<uint32_t>((uint32_t)n_cu, kDrawnBlocks) &&
+         T <= kInlineSteps && fused > 0 && drawn_lds(bucket, T, fused).runs <= 2 + S / 256;
 }
 
 // what stays on the device for a controller between its updates

@@ -381,17 +381,6 @@ size_t fused_lds(const brmppi_problem& p, const LaunchShape& sh) {
   return b <= kFusedLdsMax ? b : 0;
 }
 
-// Whether k_rollout_drawn takes the place of the noise kernel and the rollout of
-// eight lanes: up to a block per CU (a second one on a CU would wait for the
-// first's LDS), tiles that reduce themselves, a horizon whose nominal sequence
-// fits the launch's arguments.  It is 3 to 7 us faster there, a launch and the wait
-// between the two.
-constexpr uint32_t kDrawnBlocks = 256;   // eight groups at most
-bool drawn_fits(const brmppi_ctx* ctx, const LaunchShape& s, uint32_t S, uint32_t T, size_t lds) {
-  return s.variant == 4 && s.block == 256 && S <= kDrawnTile * std::min<uint32_t>(ctx->n_cu, kDrawnBlocks) &&
-         T <= kInlineSteps && lds > 0;
-}
-
 size_t normals_bytes(const brmppi_ctx* ctx, const brmppi_problem& p) {
   return (size_t)normals_per_step(ctx, p) * p.T * round_up(p.S, 256) * sizeof(float);
 }
@@ -420,7 +409,7 @@ LaunchShape plain_shape(brmppi_ctx* ctx, const brmppi_problem& p) {
   const size_t noise = normals_bytes(ctx, p);
   if (s.block == 0)
     s = default_shape(bucket, p.S, noise, (p.flags & BRMPPI_COLLISION_PENALTY) != 0, footprint_is_rear_axle(params_of(ctx, p)));
-  if (drawn_fits(ctx, s, p.S, p.T, fused_lds(p, s))) s.variant = kDrawnVariant;
+  if (drawn_fits(ctx->n_cu, bucket, s, p.S, p.T, fused_lds(p, s))) s.variant = kDrawnVariant;
   if (variant_pre(s.variant) && noise > normals_limit(ctx))
     s.variant = variant_in_kernel(bucket);
   return s;
@@ -1677,7 +1666,7 @@ int brmppi_autotune(brmppi_ctx* ctx) {
           const uint32_t nr = L.n_wchunk * L.n_rgroup;
           SolveArgs args;
           args.d = h;
-          const bool drawn = drawn_fits(ctx, LaunchShape{block, variant}, S, T, lds);
+          const bool drawn = drawn_fits(ctx->n_cu, bucket, LaunchShape{block, variant}, S, T, lds);
           auto run = [&]() -> hipError_t {
             hipError_t e = hipSuccess;
             if (drawn) return launch_rollout_drawn(bucket, args, grid, lds, s);

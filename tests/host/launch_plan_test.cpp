@@ -104,6 +104,27 @@ static void default_shapes() {
   }
 }
 
+// k_rollout_drawn is taken only where its launch is valid, and not with more runs than
+// its samples pay for.
+static void drawn_rule() {
+  for (int bucket : {0, 2, 8, 16, 32}) {
+    for (uint32_t S = 1; S <= 9000; S += 1 + S / 7) {
+      for (uint32_t T = 1; T <= BRMPPI_MAX_T; ++T) {
+        size_t fused = fused_lds_bytes(kDrawnTile, T, (S + kWChunk - 1) / kWChunk);
+        if (fused > kFusedLdsMax) fused = 0;
+        const bool fits = drawn_fits(256, bucket, LaunchShape{256, 4}, S, T, fused);
+        if (fits) CHECK(S <= 8192 && T <= kInlineSteps && drawn_lds(bucket, T, fused).runs <= 2 + S / 256);
+        if (S <= 8192 && T <= 20) CHECK(fits);
+        if (S > 8192 || T > kInlineSteps) CHECK(!fits);
+        CHECK(!drawn_fits(256, bucket, LaunchShape{256, 3}, S, T, fused) && !drawn_fits(256, bucket, LaunchShape{64, 4}, S, T, fused));
+        if (S > 4096) CHECK(!drawn_fits(128, bucket, LaunchShape{256, 4}, S, T, fused));
+      }
+    }
+  }
+  CHECK(drawn_fits(256, 32, LaunchShape{256, 4}, 8192, 162, fused_lds_bytes(kDrawnTile, 162, 8)));
+  CHECK(!drawn_fits(256, 32, LaunchShape{256, 4}, 256, 162, fused_lds_bytes(kDrawnTile, 162, 1)));
+}
+
 // A served request is counted with the bytes of 64-sample tiles, and a batch of it takes no
 // more of the arena at any tile size.
 static void request_footprints() {
@@ -128,6 +149,7 @@ int main() {
   drawn_reads_in_range();
   tune_update_rows();
   default_shapes();
+  drawn_rule();
   request_footprints();
   std::printf("launch plan: all checks passed\n");
   return 0;

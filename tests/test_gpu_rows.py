@@ -175,3 +175,25 @@ def test_noalloc_limit_counts_the_normals(ctx):
         ctx.set_path(0, p.path, p.ds)
         rc = B.brmppi_solve_noalloc(ctx.h, B.ProblemBuffers(p, controller=0), allow=(B.OK, B.ENOMEM))[2]
         assert rc == rc_want, T
+
+
+@pytest.mark.parametrize("S,T,n_obs,drawn", [
+    (3000, 12, 7, True), (8191, 3, 7, True), (8193, 12, 7, False),       # up to a block per CU
+    (8192, 162, 32, True), (8192, 163, 32, False), (600, 162, 0, True), (600, 163, 0, False),   # the epilogue's LDS
+    (256, 40, 32, True), (256, 60, 32, True), (256, 81, 32, False), (255, 60, 32, False), (256, 162, 32, False),   # runs
+])
+def test_which_launch_draws(S, T, n_obs, drawn):
+    """The default form at the edges of what the rollout's own launch draws (its noise
+    is counted without a time; the noise kernel's has one), and the four-lane form's
+    bits in either."""
+    p = problem("moving", n_obs).copy(S=S, T=T, u_nom=np.full((T, 3), 0.1, np.float32))
+    with B.Context(arena_bytes=512 << 20, n_streams=1, max_controllers=4, flags_extra=B.CTX_PROFILE_ROLLOUT) as c:
+        c.set_path(0, p.path, p.ds)
+        print(f"  n_obs={n_obs} S={S} T={T}", flush=True)
+        got = B.brmppi_solve_ex(c.h, B.ProblemBuffers(p, controller=0), want_J=True)
+        prof = B.brmppi_profile_read(c.h)
+        assert prof["rollout"]["count"] == 1 and prof["noise"]["count"] == 1
+        assert (prof["noise"]["ms"] == 0.0) == drawn
+        B.brmppi_set_launch(c.h, 256, 3)
+        want = B.brmppi_solve_ex(c.h, B.ProblemBuffers(p, controller=0), want_J=True)
+    assert np.array_equal(got["J"], want["J"]) and np.array_equal(got["U_new"], want["U_new"])
