@@ -111,3 +111,22 @@ def test_noalloc_limit(S, T, n_obs, flags, arena, ok):
         if ok:
             u = u.copy()
             assert np.array_equal(u, B.brmppi_solve(c.h, pb)[0])
+
+
+@pytest.mark.parametrize("n_obs", [0, 2, 3, 8, 9, 16, 17, 32])
+@pytest.mark.parametrize("T", [20, 60, 90])
+def test_drawn_for_lack_of_room(n_obs, T):
+    """8300 samples (a partial tile in every form) whose normals exceed half the arena:
+    the rollout draws them itself, on one lane up to eight rows, two up to 16, four up
+    to 32, with tiles that reduce themselves (T = 20; 60 on four lanes) and without.
+    The bits of the buffered form; the launch counts tell the two apart."""
+    p = problem(8300, T, n_obs)
+    normals = 4 * (5 + n_obs) * T * 8448
+    sequences = 4 * 3 * T * 8448
+    room = int(1.05 * sequences) + (600 << 10)
+    small = min(2 * normals - 4096, room + normals)
+    assert small >= room
+    with context(512 << 20) as a, context(small) as b:
+        (want, n_want), (got, n_got) = solve(a, p), solve(b, p)
+    assert (n_want, n_got) == (1, 0)
+    assert np.array_equal(got["J"], want["J"]) and np.array_equal(got["U_new"], want["U_new"])
