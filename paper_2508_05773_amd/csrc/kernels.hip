@@ -1892,6 +1892,14 @@ template <int NOB, int G>
 constexpr int rollout_waves_per_simd() {
   return (NOB <= 16 || G >= 4) ? 2 : 1;
 }
+// Waves per SIMD that the schedule may assume.  Without rows the registers are the
+// instance merge's 134, three waves; scheduled for four, the penalty's loop over
+// obstacles waits for each one's LDS reads (60000 samples, 90 steps, 24 obstacles, four
+// lanes: 207 us against 187).
+template <int NOB>
+constexpr int rollout_waves_max() {
+  return NOB == 0 ? 3 : 8;
+}
 
 // Fused reduction of one tile (its samples' costs and applied inputs are in
 // LDS): unit weights, unit partials to HBM; the last tile of each group merges
@@ -2111,7 +2119,7 @@ __device__ __forceinline__ void tile_rollout(const SolveDesc& d, uint32_t s0, co
 
 // Rollout of one instance (a direct launch, a tile per block).
 template <int NOB, bool GUIDED, int G, bool PRE>
-__global__ __launch_bounds__(kMaxBlock) __attribute__((amdgpu_waves_per_eu(rollout_waves_per_simd<NOB, G>(), 8)))
+__global__ __launch_bounds__(kMaxBlock) __attribute__((amdgpu_waves_per_eu(rollout_waves_per_simd<NOB, G>(), rollout_waves_max<NOB>())))
 void k_rollout(const SolveDesc* __restrict__ desc) {
   __shared__ float4 s_path[kPathLds];
   __shared__ float4 s_unom[BRMPPI_MAX_T + 1];
