@@ -520,33 +520,32 @@ int ensure_scratch(brmppi_ctx* ctx, size_t bytes) {
   return 0;
 }
 
-// The precomputed normals of a call: behind the first `used` bytes of the kept
-// scratch where they fit, else in a block of the arena that the call gives back, so
-// that they never take what a later batch or request could use.  take() fails where
-// there is no room: the call then draws its normals in the rollout.
+// Room for the precomputed normals of a call: behind the first `used` bytes of the
+// kept scratch where they fit, else in free memory of the arena, which no one else can
+// take while the call holds the context's lock.  Nothing is kept, so that normals never
+// take what a later batch or request could use.  take() fails where there is no room:
+// the call then draws its normals in the rollout.
 class Normals {
  public:
   explicit Normals(brmppi_ctx* ctx) : ctx_(ctx) {}
   ~Normals() {
-    // a call that failed may have left work on its stream that still uses the block,
-    // which another stream's batch could be given
-    if (blk_.ptr && !idle_) (void)hipStreamSynchronize(ctx_->streams[0]);
-    ctx_->arena.release(blk_);
+    // a call that failed may have left work on its stream that still uses the memory
+    if (lent_) (void)hipStreamSynchronize(ctx_->streams[0]);
   }
   Normals(const Normals&) = delete;
   Normals& operator=(const Normals&) = delete;
   char* take(size_t used, size_t bytes) {
     used = round_up(used, 256);
     if (ctx_->scratch.bytes >= used + bytes) return ctx_->scratch.ptr + used;
-    blk_ = ctx_->arena.alloc(bytes);
-    return blk_.ptr;
+    char* p = ctx_->arena.lend(bytes);
+    lent_ = p != nullptr;
+    return p;
   }
-  void idle() { idle_ = true; }   // the call's stream has been waited for
+  void idle() { lent_ = false; }   // the call's stream has been waited for
 
  private:
   brmppi_ctx* ctx_;
-  Block blk_;
-  bool idle_ = false;
+  bool lent_ = false;
 };
 
 // ---------------------------------------------------------------------------

@@ -82,6 +82,14 @@ class Arena {
     free_[off] = len;
     b = Block{};
   }
+  // The first free block of n bytes, not taken: its bytes are the caller's while it
+  // holds the lock under which blocks are taken (nullptr: none).
+  char* lend(size_t n) const {
+    n = round_up(std::max<size_t>(n, 1), 256);
+    for (auto& kv : free_)
+      if (kv.second >= n) return base_ + kv.first;
+    return nullptr;
+  }
   bool fits(size_t n) const {
     n = round_up(std::max<size_t>(n, 1), 256);
     for (auto& kv : free_)
