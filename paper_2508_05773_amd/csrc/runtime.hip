@@ -557,12 +557,19 @@ constexpr size_t kDirectCostBytes = size_t(1) << 20;
 // Larger results come in pieces of this size through two halves of the pinned
 // buffer: the device fills one while the host empties the other.
 // (3001 applied sequences of 37 steps, 1.4 MB: 191 us for the update and its
-// download; by a pitched copy to the caller's pageable memory 900 us)
+// download; by a pitched copy to the caller's pageable memory 890 us).  The pitched
+// copy's cost is by the row, so rows of a piece and longer are left to it (the update,
+// its costs and sequences of 4 steps, pieces / pitched copy: 32768 samples 179 / 212 us,
+// 50000 255 / 252, 65536 305 / 290, 130000 562 / 459, 300000 1330 / 1226).
 constexpr size_t kPieceBytes = size_t(256) << 10;
 
 // n_rows rows of `row` floats, `pitch` apart at src on the device, to dense rows at dst
 int download_rows(brmppi_ctx* ctx, hipStream_t s, float* dst, size_t row, const char* src, size_t pitch, size_t n_rows,
                   const char* piece) {
+  if (row * sizeof(float) >= kPieceBytes) {
+    HIPCHK(hipMemcpy2D(dst, row * sizeof(float), src, pitch * sizeof(float), row * sizeof(float), n_rows, hipMemcpyDeviceToHost));
+    return 0;
+  }
   constexpr size_t kPiece = kPieceBytes / sizeof(float);
   const size_t total = (n_rows - 1) * pitch + row;
   const size_t n_pieces = (total + kPiece - 1) / kPiece;

@@ -197,3 +197,10 @@ def test_which_launch_draws(S, T, n_obs, drawn):
         B.brmppi_set_launch(c.h, 256, 3)
         want = B.brmppi_solve_ex(c.h, B.ProblemBuffers(p, controller=0), want_J=True)
     assert np.array_equal(got["J"], want["J"]) and np.array_equal(got["U_new"], want["U_new"])
+
+
+@pytest.mark.parametrize("S", [65535, 65536, 65537])
+def test_downloads_at_the_piece_size(ctx, S):
+    """Applied sequences whose rows are just under, exactly and just over the size from
+    which they are copied whole.  Against the FP64 oracle at the stated bars, as above."""
+    test_downloads_in_pieces(ctx, S, 2)
