@@ -146,9 +146,9 @@ inline DrawnLds drawn_lds(int bucket, uint32_t T, size_t fused) {
   return l;
 }
 // the rollouts of a batch's tiles (each of block / variant_lanes(variant_in_kernel(bucket))
-// samples of its instance); grid at most n_tiles
+// samples of its instance); grid at most n_tiles; guided: some instance is
 hipError_t launch_rollout_batch(const SolveDesc* descs, const Tile* tiles, uint32_t n_tiles, BatchCounters* ctr,
-                                uint32_t grid, uint32_t block, hipStream_t stream);
+                                uint32_t grid, uint32_t block, bool guided, hipStream_t stream);
 // dynamic LDS of the fused epilogue for a tile of `per_tile` samples: the
 // tile's applied inputs [3T][per_tile + 1] (later reused for the n_groups
 // merge scales), costs, weights, unit minima and scales, unit partials
@@ -193,7 +193,7 @@ hipError_t launch_normals_dump(uint32_t seed_lo, uint32_t seed_hi, uint32_t inst
 hipError_t launch_box_muller_dump(const uint32_t* r, uint32_t n, float* out, hipStream_t stream);
 hipError_t launch_fill_u32(uint32_t* p, uint32_t value, size_t n, hipStream_t stream);
 // occupancy of the batched rollout for a block size (blocks per CU)
-int rollout_batch_blocks_per_cu(uint32_t block);
+int rollout_batch_blocks_per_cu(uint32_t block, bool guided);
 
 // footprint discs of a parameter set, and whether it is other than the rear
 // axle alone (the point eq. (16) uses)

@@ -658,6 +658,9 @@ __device__ __forceinline__ float collision_pen(const ObsL* __restrict__ sobs, in
     sincospif(2.0f * th2, &s2, &c2);
   }
   float pen = 0.0f;
+  // four obstacles' LDS reads at a time (3 instances of 2000 samples in a batch, 40 steps,
+  // 24 obstacles: one at a time 147 us, 101)
+#pragma unroll 4
   for (int o = 0; o < n_obs; ++o) {
     const ObsL ob = sobs[o];
     float qx = px, qy = py;
@@ -2271,7 +2274,11 @@ void k_rollout_drawn(const SolveArgs) {
 // -> this: 64 instances (1024 to 16384 samples, 20 to 80 steps, up to 16
 // obstacles) 765 -> 745 us a call (687 since), 48 served requests (up to 32768
 // samples, 100 steps, 32 obstacles) 2813 -> 2125 us (2032 since).
-__global__ __launch_bounds__(kMaxBlock) __attribute__((amdgpu_waves_per_eu(2, 8)))
+// A batch without guidance has a kernel of its own (GUIDED false): 120 registers and
+// less LDS, four waves per SIMD where the common one has two (16 instances of 32768
+// samples, 60 steps: 296 -> 270 us, with the penalty over 24 obstacles 720 -> 542).
+template <bool GUIDED>
+__global__ __launch_bounds__(kMaxBlock) __attribute__((amdgpu_waves_per_eu(2, GUIDED ? 8 : 4)))
 void k_rollout_batch(const SolveDesc* __restrict__ descs, const Tile* __restrict__ tiles, uint32_t n_tiles,
                      BatchCounters* __restrict__ ctr) {
   __shared__ float4 s_path[kPathLds];
@@ -2279,7 +2286,7 @@ void k_rollout_batch(const SolveDesc* __restrict__ descs, const Tile* __restrict
   __shared__ ObsL s_obs[BRMPPI_MAX_OBS];
   __shared__ uint32_t s_tile;
   constexpr int kNrm2 = kMaxBlock / 2 * coop_stride<16, 2>() / 4, kNrm4 = kMaxBlock / 4 * coop_stride<32, 4>() / 4;
-  __shared__ float4 s_nrm4[kNrm2 > kNrm4 ? kNrm2 : kNrm4];
+  __shared__ float4 s_nrm4[!GUIDED ? 1 : (kNrm2 > kNrm4 ? kNrm2 : kNrm4)];
   float* s_nrm = reinterpret_cast<float*>(s_nrm4);
   for (uint32_t it = 0;; ++it) {
     uint32_t tix;
@@ -2290,17 +2297,21 @@ void k_rollout_batch(const SolveDesc* __restrict__ descs, const Tile* __restrict
     tile_start(d, st);
     stage_tile(d, s_path, s_unom, s_obs, st, (int)blockDim.x);
     __syncthreads();
-    auto run = [&](auto NOB, auto GUIDED, auto G) __attribute__((always_inline)) {
-      tile_rollout<decltype(NOB)::value, decltype(GUIDED)::value, decltype(G)::value, kOwnDraw>(
+    auto run = [&](auto NOB, auto GD, auto G) __attribute__((always_inline)) {
+      tile_rollout<decltype(NOB)::value, decltype(GD)::value, decltype(G)::value, kOwnDraw>(
           d, tl.s0, st, s_path, s_unom, s_obs, nullptr, 0, nullptr, s_nrm);
     };
     using std::integral_constant;
-    switch (d.bucket) {
-      case 0: run(integral_constant<int, 0>{}, std::false_type{}, integral_constant<int, 1>{}); break;
-      case 2: run(integral_constant<int, 2>{}, std::true_type{}, integral_constant<int, 1>{}); break;
-      case 8: run(integral_constant<int, 8>{}, std::true_type{}, integral_constant<int, 1>{}); break;
-      case 16: run(integral_constant<int, 16>{}, std::true_type{}, integral_constant<int, 2>{}); break;
-      default: run(integral_constant<int, 32>{}, std::true_type{}, integral_constant<int, 4>{}); break;
+    if constexpr (!GUIDED) {
+      run(integral_constant<int, 0>{}, std::false_type{}, integral_constant<int, 1>{});
+    } else {
+      switch (d.bucket) {
+        case 0: run(integral_constant<int, 0>{}, std::false_type{}, integral_constant<int, 1>{}); break;
+        case 2: run(integral_constant<int, 2>{}, std::true_type{}, integral_constant<int, 1>{}); break;
+        case 8: run(integral_constant<int, 8>{}, std::true_type{}, integral_constant<int, 1>{}); break;
+        case 16: run(integral_constant<int, 16>{}, std::true_type{}, integral_constant<int, 2>{}); break;
+        default: run(integral_constant<int, 32>{}, std::true_type{}, integral_constant<int, 4>{}); break;
+      }
     }
     __syncthreads();
   }
@@ -2611,16 +2622,18 @@ hipError_t launch_rollout_drawn(int bucket, SolveArgs& args, uint32_t grid, size
 }
 
 hipError_t launch_rollout_batch(const SolveDesc* descs, const Tile* tiles, uint32_t n_tiles, BatchCounters* ctr,
-                                uint32_t grid, uint32_t block, hipStream_t stream) {
+                                uint32_t grid, uint32_t block, bool guided, hipStream_t stream) {
   if (block == 0 || block > (uint32_t)kMaxBlock || (block % 64) != 0) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(k_rollout_batch, dim3(grid), dim3(block), 0, stream, descs, tiles, n_tiles, ctr);
+  if (guided) hipLaunchKernelGGL(k_rollout_batch<true>, dim3(grid), dim3(block), 0, stream, descs, tiles, n_tiles, ctr);
+  else hipLaunchKernelGGL(k_rollout_batch<false>, dim3(grid), dim3(block), 0, stream, descs, tiles, n_tiles, ctr);
   return hipGetLastError();
 }
 
-int rollout_batch_blocks_per_cu(uint32_t block) {
+int rollout_batch_blocks_per_cu(uint32_t block, bool guided) {
   int nb = 0;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_rollout_batch, (int)block, 0) != hipSuccess) return 1;
-  return nb > 0 ? nb : 1;
+  const hipError_t e = guided ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_rollout_batch<true>, (int)block, 0)
+                              : hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_rollout_batch<false>, (int)block, 0);
+  return e == hipSuccess && nb > 0 ? nb : 1;
 }
 
 hipError_t launch_noise(const NoiseArgs& a, uint32_t count, uint32_t T, const Upload& up, hipStream_t stream) {

@@ -722,6 +722,7 @@ struct BatchPlan {
   size_t off_descs = 0, off_tiles = 0, off_ritems = 0, off_counters = 0, header_bytes = 0;
   size_t out_floats = 0, total = 0;
   uint32_t block = 256;              // of the rollout launch
+  bool guided = false;               // some instance is
 };
 
 // samples of a tile of this instance in a batched launch of `block` threads
@@ -732,6 +733,7 @@ uint32_t batch_tile(const brmppi_ctx* ctx, const brmppi_problem& p, uint32_t blo
 void plan_layout(brmppi_ctx* ctx, const brmppi_problem* const* ps, uint32_t n, BatchPlan& bp) {
   bp.layouts.resize(n);
   bp.block = ctx->forced.block ? ctx->forced.block : 256;
+  bp.guided = std::any_of(ps, ps + n, [](const brmppi_problem* p) { return !(p->flags & BRMPPI_GUIDANCE_OFF); });
   size_t n_tiles = 0, n_r = 0;
   std::vector<uint32_t> rows_item(n);
   reduce_rows(ps, n, ctx->n_cu, rows_item.data());
@@ -855,8 +857,8 @@ BatchPlanCache& plan_cache(brmppi_ctx* ctx) {
   return *static_cast<BatchPlanCache*>(ctx->plan_cache.get());
 }
 
-uint32_t persistent_grid(brmppi_ctx* ctx, uint32_t block, size_t n_tiles) {
-  const int per_cu = rollout_batch_blocks_per_cu(block);
+uint32_t persistent_grid(brmppi_ctx* ctx, uint32_t block, bool guided, size_t n_tiles) {
+  const int per_cu = rollout_batch_blocks_per_cu(block, guided);
   const size_t g = (size_t)ctx->n_cu * (size_t)std::max(per_cu, 1);
   return (uint32_t)std::max<size_t>(1, std::min(g, n_tiles));
 }
@@ -872,8 +874,8 @@ int enqueue_batch(brmppi_ctx* ctx, hipStream_t st, char* base, const BatchPlan& 
   const uint32_t nr = (uint32_t)bp.ritems.size();
   const uint32_t g_r = std::max<uint32_t>(1, std::min<uint32_t>(nr, (uint32_t)ctx->n_cu * 8));
   const uint32_t nt = (uint32_t)bp.tiles.size();
-  const uint32_t g_roll = persistent_grid(ctx, bp.block, nt);
-  auto L0 = [&] { return launch_rollout_batch(descs, tiles, nt, ctr, g_roll, bp.block, st); };
+  const uint32_t g_roll = persistent_grid(ctx, bp.block, bp.guided, nt);
+  auto L0 = [&] { return launch_rollout_batch(descs, tiles, nt, ctr, g_roll, bp.block, bp.guided, st); };
   if (timing) {
     if (int rc = timed(ctx, st, 0, L0)) return rc;
   } else {
@@ -924,7 +926,7 @@ int run_batch(brmppi_ctx* ctx, hipStream_t s, char* base, const BatchPlan& bp, B
   } else {
     // the captured launches bake in every pointer and count: key on them
     std::vector<uint64_t> key = {(uint64_t)(uintptr_t)base, bp.tiles.size(), bp.ritems.size(),
-                                 (uint64_t)(uintptr_t)s, bp.descs.size(), (uint64_t)(uintptr_t)ctr, bp.block};
+                                 (uint64_t)(uintptr_t)s, bp.descs.size(), (uint64_t)(uintptr_t)ctr, bp.block, bp.guided};
     if (key != ctx->graph_key || !ctx->graph_exec) {
       drop_graph(ctx);
       HIPCHK(hipStreamBeginCapture(s, hipStreamCaptureModeThreadLocal));

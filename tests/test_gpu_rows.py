@@ -204,3 +204,34 @@ def test_downloads_at_the_piece_size(ctx, S):
     """Applied sequences whose rows are just under, exactly and just over the size from
     which they are copied whole.  Against the FP64 oracle at the stated bars, as above."""
     test_downloads_in_pieces(ctx, S, 2)
+
+
+def test_batches_without_guidance(ctx):
+    """Batches of unguided instances, with and without the penalty, over the kinds of
+    rows that the penalty tells apart: bit for bit the plain solves, also where a batch
+    of the same sizes has a guided instance."""
+    with B.Context(arena_bytes=512 << 20, n_streams=1, max_controllers=64) as c:
+        prm = W.make_params(0.05, disc_tractor=(0.0, 2.0), disc_trailer=(1.5,))
+        probs = []
+        for flags in (W.FLAG_GUIDANCE_OFF, W.FLAG_GUIDANCE_OFF | W.FLAG_COLLISION_PENALTY):
+            for kind in ("rest", "moving", "e4"):
+                for n_obs in (0, 3, 4, 9, 32):
+                    probs.append(problem(kind, n_obs, flags))
+            p = problem("e4", 7, flags)
+            p.params.update(prm)
+            probs.append(p)
+        pbs = []
+        for i, p in enumerate(probs):
+            q = p.copy(S=1 + 67 * i, T=1 + i % 9, u_nom=p.u_nom[:1].repeat(1 + i % 9, axis=0))
+            c.set_path(i, q.path, q.ds)
+            pbs.append(B.ProblemBuffers(q, controller=i))
+        guided = problem("moving", 9)
+        c.set_path(63, guided.path, guided.ds)
+        plain = [B.brmppi_solve(c.h, pb)[0].copy() for pb in pbs]
+        for block in (0, 64, 192):
+            B.brmppi_set_launch(c.h, block, 0)
+            for extra in ([], [B.ProblemBuffers(guided, controller=63)], []):
+                got = B.brmppi_solve_batch(c.h, pbs + extra)[0]
+                for i, v in enumerate(plain):
+                    assert np.array_equal(got[i], v), (block, len(extra), i)
+        B.brmppi_set_launch(c.h, 0, 0)
