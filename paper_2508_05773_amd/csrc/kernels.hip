@@ -1168,19 +1168,29 @@ __device__ __forceinline__ void rollout_sample(const SolveDesc& d, uint32_t s, b
         // lanes 0 and 1 hold the hitch rows; the others add exact zeros
         acc_row(A[0], H[0], H[0].L + fmaf(ka, bt_h[0], nz_h[0]));
       }
+      // A footprint's rows on one lane go one by one: two at a time they spill (16
+      // instances of 32768 samples, 60 steps, two obstacles around two discs in a batch:
+      // 1335 us, 1040; with four lanes pairs are 4 % faster).
+      constexpr bool kPairs = ROWS != kRowsDisc || G > 1;
+      if constexpr (kPairs) {
 #pragma unroll
-      for (int j = 0; j < NSL; j += 2) {
-        if (G * j < kMinRows || G * j < n_obs) {
-          ObsL oa, ob;
-          if constexpr (kObsRegs) oa = ob_r[j];
-          else oa = sobs[gi + G * j];
-          if (j + 1 < NSL) {
-            if constexpr (kObsRegs) ob = ob_r[j + 1 < NSL ? j + 1 : 0];
-            else ob = sobs[gi + G * (j + 1)];
+        for (int j = 0; j < NSL; j += 2) {
+          if (G * j < kMinRows || G * j < n_obs) {
+            ObsL oa, ob;
+            if constexpr (kObsRegs) oa = ob_r[j];
+            else oa = sobs[gi + G * j];
+            if (j + 1 < NSL) {
+              if constexpr (kObsRegs) ob = ob_r[j + 1 < NSL ? j + 1 : 0];
+              else ob = sobs[gi + G * (j + 1)];
+            }
+            obs_row(j, oa, A[j % NV]);
+            if (j + 1 < NSL) obs_row(j + 1, ob, A[(j + 1) % NV]);
           }
-          obs_row(j, oa, A[j % NV]);
-          if (j + 1 < NSL) obs_row(j + 1, ob, A[(j + 1) % NV]);
         }
+      } else {
+#pragma unroll
+        for (int j = 0; j < NSL; ++j)
+          if (G * j < n_obs) obs_row(j, sobs[gi + G * j], A[j % NV]);
       }
 #pragma unroll
       for (int n = NV / 2; n >= 1; n /= 2) {
@@ -1214,7 +1224,8 @@ __device__ __forceinline__ void rollout_sample(const SolveDesc& d, uint32_t s, b
       }
 #pragma unroll
       for (int j = 0; j < NSL; ++j) {
-        if (G * (j & ~1) < kMinRows || G * (j & ~1) < n_obs) bt_o[j] = fmaf(O[j].Q, U1, fmaf(O[j].P, U0, O[j].L));
+        const int row = G * (kPairs ? j & ~1 : j);
+        if ((kPairs && row < kMinRows) || row < n_obs) bt_o[j] = fmaf(O[j].Q, U1, fmaf(O[j].P, U0, O[j].L));
       }
     } else {
       U0 = G0 * uj;
