@@ -191,9 +191,9 @@ def main():
     roll_ms = prof["rollout"]["ms"] / max(prof["rollout"]["count"], 1)
     # the closed loop draws the normals of several updates per noise launch
     noise_ms = prof["noise"]["ms"] / args.steps if prof["noise"]["count"] else 0.0
-    # variants 1-4 draw the normals in the separate noise kernel: the rollout
-    # kernel's own algorithmic work then excludes the Box-Muller flops
-    noise_in_kernel = prof["noise"]["count"] == 0
+    # a separate noise kernel has a time of its own: the rollout kernel's algorithmic
+    # work then excludes the Box-Muller flops
+    noise_in_kernel = prof["noise"]["ms"] == 0.0
     flops = rollout_flops(S, T, n_obs, noise_in_kernel=noise_in_kernel)
     achieved = flops / (roll_ms * 1e-3) / 1e12
     traffic = load_traffic()
@@ -221,8 +221,9 @@ def main():
         "roofline": {
             "bound": "alu", "achieved": achieved, "peak": PEAK_FP32_TFLOPS, "unit": "TFLOP/s",
             "frac": achieved / PEAK_FP32_TFLOPS, "traffic": traffic,
-            "kernel": "k_rollout (8-obstacle bucket)", "launch_shape": {"block_variant": shape},
-            "noise_kernel_ms_per_update": noise_ms, "noise_launches": prof["noise"]["count"], "flops_per_launch": flops, "avg_launch_ms": roll_ms,
+            "kernel": ("k_rollout_drawn" if noise_in_kernel and prof["noise"]["count"] else "k_rollout") + " (8-obstacle bucket)",
+            "launch_shape": {"block_variant": shape},
+            "noise_kernel_ms_per_update": noise_ms, "noise_launches": 0 if noise_in_kernel else prof["noise"]["count"], "flops_per_launch": flops, "avg_launch_ms": roll_ms,
             "launches": prof["rollout"]["count"], "peak_nonpacked": PEAK_FP32_NONPACKED_TFLOPS,
             "frac_nonpacked": achieved / PEAK_FP32_NONPACKED_TFLOPS,
             "flops_per_sample_step": flops_per_sample_step(n_obs),
@@ -380,10 +381,10 @@ def large_leg(B, W, ctx, tune_file):
         shape = json.load(open(tune_file)).get("plain_32_3") if tune_file else None
     except (OSError, ValueError):
         pass
-    # a table entry with precomputed normals falls back to the one-lane form
+    # a table entry with precomputed normals falls back to the four-lane form
     # with in-kernel normals when the noise buffer does not fit: no noise launch
     if shape and noise_in_kernel and shape[1] != 0:
-        shape = [shape[0], 0]
+        shape = [shape[0], 6]
     return {"workload": "S=65536, T=100, 32 ellipses, three-piece spline path with cusps",
             "launch_shape": {"block_variant": shape},
             "p50_ms": pct(lat, 50), "p99_ms": pct(lat, 99),

@@ -315,10 +315,11 @@ int brmppi_autotune(brmppi_ctx* ctx);
  * the kernel; 1 = one lane, noise from the parallel kernel; 2 / 3 / 4 = two /
  * four / eight lanes per sample, noise from the parallel kernel (eight lanes and
  * block 256 up to 8192 samples: drawn ahead of the steps by the rollout's own
- * launch; a batched launch takes the block size and its own forms; a plain solve whose normals
- * would take more than 2 GiB or half the arena draws them in the kernel).  block
- * 0 restores the tuned/default choice.  EINVAL for a block outside 64..256 or
- * not a multiple of 64, or a variant above 4. */
+ * launch, unless few samples have a long horizon of many rows; a batched launch
+ * takes the block size and its own forms; a plain solve whose normals would take
+ * more than 2 GiB or half the arena, or find no room in it, draws them in the
+ * kernel).  block 0 restores the tuned/default choice.  EINVAL for a block outside
+ * 64..256 or not a multiple of 64, or a variant above 4. */
 int brmppi_set_launch(brmppi_ctx* ctx, uint32_t block, uint32_t variant);
 /* Kernel timings accumulated under BRMPPI_CTX_PROFILE (every kernel of the
  * blocking calls) or BRMPPI_CTX_PROFILE_ROLLOUT (rollout and noise only), from

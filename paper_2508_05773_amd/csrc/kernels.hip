@@ -21,9 +21,9 @@
 //
 // A sample's state, barrier rates and row terms stay in registers.  Obstacles
 // (with their shape matrices) and a window of the path are staged in LDS per
-// tile.  Positions are carried relative to the start position and progress
-// relative to the start progress so that FP32 keeps sub-micrometre resolution
-// far from the origin.
+// tile.  Positions are carried relative to the start position, headings to the
+// quarter turn nearest the start heading and progress to the start progress, so
+// that FP32 keeps sub-micrometre resolution far from the origin.
 #include <math.h>
 
 #include <type_traits>
@@ -1897,11 +1897,13 @@ __device__ __forceinline__ void group_merge(const SolveDesc& d, uint32_t gu0, ui
 }
 
 // Waves per SIMD the register allocation must leave room for.  Up to 16
-// obstacle slots every launch shape fits two waves (the one-lane forms with a
-// few spilled values, which still pays: at one wave per SIMD nothing hides the
-// step's latency), and so do the four- and eight-lane forms with 32 slots (a
-// lane holds 8 or 4 obstacle rows); the one- and two-lane forms with 32 slots
-// would spill hundreds of values, so they keep the whole register file.
+// obstacle slots every launch shape is held to two waves, and so are the four- and
+// eight-lane forms with 32 slots (a lane holds 8 or 4 obstacle rows).  The forms that
+// the default shape takes spill 0 to 20 values there (58 with 16 slots on two lanes that
+// draw), which still pays: at one wave per SIMD nothing hides the step's latency.  Of the
+// others, one lane with precomputed normals spills 176 (8 slots) and 632 (16), one lane
+// that draws 208 (16 slots).  The one- and two-lane forms with 32 slots keep the whole
+// register file (112 spilled with one lane and precomputed normals, none otherwise).
 template <int NOB, int G>
 constexpr int rollout_waves_per_simd() {
   return (NOB <= 16 || G >= 4) ? 2 : 1;
@@ -2175,7 +2177,7 @@ void k_rollout(const SolveDesc* __restrict__ desc) {
 
 // Rollout of one instance of up to one block per CU: eight lanes per sample on
 // the block's first four waves, one on each SIMD.  The normals of a run of steps
-// (as many as LDS holds: the horizon in one to three runs) are drawn by all eight
+// (as many as LDS holds: 50 steps of 8 rows in two runs, 162 of 32 in 14) are drawn by all eight
 // waves before the first four take the steps: two waves on a SIMD draw in half
 // the time of one, which issues an instruction every 4 cycles where most take 2 of
 // the pipe.  (Four waves that draw while the others take the steps cost the
@@ -2184,7 +2186,8 @@ void k_rollout(const SolveDesc* __restrict__ desc) {
 // an update is one launch.  Measured against the noise kernel's launch and then
 // the rollout's: that update 62.7 -> 57.2 us, 512 samples of 20 steps 40.9 -> 37.8,
 // 5000 of 120 steps without guidance 61.2 -> 54.2, with 8 obstacles 124.0 -> 119.6,
-// 4096 of 60 steps and 32 rows 140 on both sides (its normals take three runs).
+// 4096 of 60 steps and 32 rows 140 on both sides (its normals take three runs; drawn_fits
+// has the limit of that).
 // What bounds it is the chain of steps, 0.6 us each, at one wave a SIMD.
 template <int NOB, bool GUIDED>
 __global__ __launch_bounds__(2 * kMaxBlock) __attribute__((amdgpu_waves_per_eu(2, 2)))
@@ -2277,14 +2280,14 @@ void k_rollout_drawn(const SolveArgs) {
 // instance's constraint bucket (d.bucket): one lane per sample up to eight
 // rows, two up to 16, four up to 32.  One launch per bucket, one after the
 // other, left the device to the last tiles of each; a bucket too small for a
-// launch of its own ran in the next heavier kernel.  Every form fits the 256
-// registers of two waves per SIMD.  What bounds it is the vector pipe: at two
+// launch of its own ran in the next heavier kernel.  The forms are held to the 256
+// registers of two waves per SIMD; 106 of their values spill.  What bounds it is the vector pipe: at two
 // waves per SIMD about 2700 of its cycles a wave and step (2 per FP32
 // instruction on vector registers, 4 per FP64, comparison or scalar-operand
 // one, 8 per transcendental), 80 % of the launch.  Measured, launch per bucket
 // -> this: 64 instances (1024 to 16384 samples, 20 to 80 steps, up to 16
-// obstacles) 765 -> 745 us a call (687 since), 48 served requests (up to 32768
-// samples, 100 steps, 32 obstacles) 2813 -> 2125 us (2032 since).
+// obstacles) 765 -> 745 us a call (685 since), 48 served requests (up to 32768
+// samples, 100 steps, 32 obstacles) 2813 -> 2125 us (2030 since).
 // A batch without guidance has a kernel of its own (GUIDED false): 120 registers and
 // less LDS, four waves per SIMD where the common one has two (16 instances of 32768
 // samples, 60 steps: 296 -> 270 us, with the penalty over 24 obstacles 720 -> 542).

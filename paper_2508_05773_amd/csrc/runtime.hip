@@ -167,8 +167,8 @@ void reduce_rows(const brmppi_problem* const* ps, uint32_t n, int n_cu, uint32_t
 }
 
 // largest precomputed-noise buffer a plain solve may take; it is also held to
-// half of the context's arena.  Beyond it the solve draws its normals in the
-// rollout kernel (one lane per sample).
+// half of the context's arena.  Beyond it, and where the arena has no room for them,
+// the solve draws its normals in the rollout kernel (variant_in_kernel).
 constexpr size_t kMaxNoiseBytes = size_t(2) << 30;
 // closed loop: normals of up to this many bytes are drawn per noise launch,
 // and at most this many updates share one descriptor upload and noise launch
